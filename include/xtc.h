@@ -115,9 +115,18 @@ typedef enum {
  *                  per workgroup (8 waves) sharing one input patch;
  *                  other shapes run the tap-major kernel;
  *                  bf16: chunks of 16, k = ((ic/16)*R*S + kh*S + kw)*16 +
- *                  ic%16, needs C % 16 == 0, even W, pad_w <= 2,
+ *                  ic%16.  lds_pad -1 (the kernel for rows of about 56
+ *                  pixels) needs C % 16 == 0, even W, pad_w <= 2,
  *                  OW - pad_w <= 60, a 4-byte-aligned X and a 16-byte-
- *                  aligned W; other shapes run the channel-major kernel;
+ *                  aligned W; other shapes run a patch kernel, its tile
+ *                  chosen by shape.  lds_pad 0 (the patch kernels: 3x3
+ *                  layers of any stride, padding, row length and batch)
+ *                  needs C % 8 == 0, a 16-byte-aligned W and a patch that
+ *                  fits in LDS; other shapes run the channel-major kernel.
+ *                  In the patch kernels groups of waves may share a tile,
+ *                  each reducing every second or fourth chunk, and their
+ *                  sums are added in group order (lds_stages 1: two groups
+ *                  for 64x128, four for 32x64; 2: none, two for 32x64);
  *                3: bf16 only, row streaming for 3x3 stride-1 layers of 64
  *                input channels: a workgroup walks down a band of output
  *                rows of one image with all C*R*S weights of its 64 output

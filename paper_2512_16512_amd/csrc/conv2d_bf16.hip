@@ -13,6 +13,8 @@
 // 16-byte aligned).  The fragments are those of the bf16 GEMM: one
 // ds_read_b128 per A fragment from k-contiguous padded rows, and two gfx950
 // transpose reads per B fragment from the pixel-contiguous B tile.
+#include <algorithm>
+
 #include "lds_dma.h"
 #include "mfma_bf16.h"
 #include "tile_map.h"
@@ -467,8 +469,507 @@ conv2d_bf16_halo_kernel(ConvArgs p) {
     }
 }
 
-// Shapes the halo kernel covers; anything else runs the gather kernel with
-// 64x128 tiles.
+// ---------------------------------------------------------------------------
+// Patch kernel (k_order = 2 outside the halo kernel's class) for 3x3
+// convolutions of any stride, padding, row length, alignment and batch, with
+// a channel count that is a multiple of 8.  The gather kernel above loads
+// every input value once per tap, two bytes at a time, and its reduction is
+// one serial chain of small steps: 32x128x28x28 -> 128 took 92.7 us (80
+// TFLOP/s) and one image of it 90.7 us, both bound by that chain; this kernel
+// takes 19.0 us (390 TFLOP/s; per chunk LDS is busy about 2300 clocks, half
+// of it with fragments, and the matrix cores 1152) and 9.0 us.  Here, as
+// in the halo kernel, a stage of 16 channels stages its input patch once for
+// all nine taps, without that kernel's restrictions:
+//  - a workgroup computes BM output channels x BN consecutive pixels of the
+//    flattened (image, output row, output column) order.  Padded input rows
+//    are numbered through the batch (PH per image), so that a tile that
+//    crosses into the next image still reads one contiguous run of them, and
+//    small images share tiles;
+//  - the input rows a tile reads are one contiguous run of bytes per image
+//    and channel.  They are copied as they are, in aligned 16-byte units
+//    (which never cross a page), straight into a raw LDS area, and so are the
+//    288 bytes that a chunk has per output channel in the OIHW weights: about
+//    nine copy instructions per wave and chunk, no registers, RD chunks ahead
+//    of the matrix cores.  Loads to registers of the cells' own pieces (one
+//    dword per channel and column pair, 16 bytes per weight slab at 144-byte
+//    strides) took 24.2 us where this takes 19.0;
+//  - between two barriers the waves then turn the raw chunk into cells: 16
+//    bytes hold 8 channels of one padded row and column ([8-channel
+//    half][row][column], WPA columns per row), or 8 channels of one (tap,
+//    output channel).  A pixel's fragment at tap (kh, kw) is the cell kh*WPA +
+//    kw past its own.  Cells in the padding hold zeros from the start of the
+//    kernel and are never written;
+//  - KS groups of waves share one tile, group g reducing the chunks g, g +
+//    KS, ... in its own LDS areas; their sums are added in group order at the
+//    end.  With few tiles (a small batch or a small image) this divides the
+//    serial chain of chunks by KS.
+namespace patch_bf16 {
+constexpr int MI = 32, CC = 16, NTAP = 9;
+constexpr int W_ROW = CC * NTAP * 2;              // raw weight bytes per output channel and chunk
+template <int BM_, int BN_, int WM_, int WN_, int KS_, int RD_>
+struct Cfg {
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KS = KS_, RD = RD_;
+    static constexpr int NWN = BN / WN, NWAVES = (BM / WM) * NWN;   // waves per group
+    static constexpr int NTG = NWAVES * 64, NT = NTG * KS;          // threads per group, in all
+    static constexpr int TM = WM / MI, TN = WN / MI;
+    static constexpr int NSLAB = (2 * BM + NTG - 1) / NTG;          // weight slabs per thread
+    static constexpr int NBW = (BM * W_ROW / 1024 + NWAVES - 1) / NWAVES;   // weight copies per wave
+    static constexpr int WRAW = NBW * NWAVES * 1024;
+    static constexpr int W_BYTES = NTAP * BM * CC * 2;              // [tap][oc][16 channels]
+    static constexpr int SU0 = BN >= 128 ? 64 : 32;                 // smaller of the two slot sizes compiled
+    static constexpr int RED_BYTES = (KS - 1) * NWAVES * TM * TN * 4096;    // partial sums
+};
+constexpr int kMaxLds = 160 * 1024;
+}  // namespace patch_bf16
+
+// Division of n < 2^31 by a launch constant d: (n * mul) >> (32 + shift) with
+// mul = ceil(2^(31 + l) / d), l = ceil(log2 d): the rounding of mul adds less
+// than n / 2^(31 + l) < 1 / d.
+struct FastDiv {
+    unsigned mul;
+    int shift;       // l - 1; -1: d is 1
+    int d;
+};
+inline FastDiv fast_div(int d) {
+    int l = 0;
+    while ((1ll << l) < d) ++l;
+    return FastDiv{(unsigned)(((1ull << (31 + l)) + d - 1) / d), l - 1, d};
+}
+__device__ __forceinline__ int div_by(int n, const FastDiv &f) {
+    return f.shift < 0 ? n : (int)(__umulhi((unsigned)n, f.mul) >> f.shift);
+}
+
+// Launch geometry of the patch kernel (computed on the host).
+struct PatchArgs {
+    ConvArgs c;
+    FastDiv by_ohw, by_ow, by_ppr;
+    int PH;      // padded input rows an image's outputs read: (OH-1)*stride_h + R
+    int WPA;     // cells per stored patch row
+    int PPR;     // items per row: column pairs (PAIR) or columns
+    int half;    // bytes of one 8-channel half of the patch
+};
+
+// SU: 16-byte units a channel's raw slot holds; NI: patch items (a column
+// pair, PAIR, or a column, of one half) per thread.
+template <typename CFG, int SU, int NI, bool PAIR>
+__global__ void __launch_bounds__(CFG::NT)
+conv2d_bf16_patch_kernel(PatchArgs pa) {
+    using namespace patch_bf16;
+    typedef Bf16Mfma<MI> MF;
+    constexpr int BM = CFG::BM, BN = CFG::BN, WM = CFG::WM, WN = CFG::WN, KS = CFG::KS, RD = CFG::RD;
+    constexpr int TM = CFG::TM, TN = CFG::TN, NTG = CFG::NTG, NSLAB = CFG::NSLAB, NBW = CFG::NBW;
+    constexpr int NBX = CC * SU / CFG::NTG;                     // input copies per wave and chunk
+    static_assert(NBX * CFG::NTG == CC * SU, "a chunk's units split evenly");
+    constexpr int RAW = CFG::WRAW + NBX * CFG::NWAVES * 1024;   // raw bytes per chunk: weights, input
+    static_assert((RD - 1) * (NBW + NBX) < 64, "vmcnt range");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char psm[];
+
+    const ConvArgs &p = pa.c;
+    const int tid = threadIdx.x;
+    const int kg = __builtin_amdgcn_readfirstlane(tid / NTG);   // K group of this wave
+    const int t = tid % NTG;                                    // thread inside its group
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wm = wave / CFG::NWN, wn = wave % CFG::NWN;
+    const int l32 = lane & 31, lgrp = lane >> 5;
+
+    const int C = p.C, H = p.H, Wd = p.W, OC = p.OC, OH = p.OH, OW = p.OW, OHW = OH * OW;
+    const int N = p.Nb * OHW;
+    const int PH = pa.PH, WPA = pa.WPA, PPR = pa.PPR, HALF = pa.half;
+    const int tiles_m = (OC + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+    int tm, tn;
+    tile_coords(blockIdx.x, gridDim.x, tiles_m, tiles_n, p.raster, p.xcd_remap, tm, tn);
+    const int m0 = tm * BM, q0 = tn * BN;
+
+    // the tile's pixels run from (img0, oh0) to (img1, oh1)
+    const int img0 = div_by(q0, pa.by_ohw), oh0 = div_by(q0 - img0 * OHW, pa.by_ow);
+    const int q1 = min(q0 + BN, N) - 1;
+    const int img1 = div_by(q1, pa.by_ohw), oh1 = div_by(q1 - img1 * OHW, pa.by_ow);
+    const int prow0 = oh0 * p.sh;                                  // first padded row, counted from img0
+    // input rows the tile reads of image i: first and count (0: none)
+    auto seg_first = [&](int i) { return max((i == img0 ? oh0 * p.sh : 0) - p.ph, 0); };
+    auto seg_rows = [&](int i) {
+        return max(min((i == img1 ? oh1 : OH - 1) * p.sh + 2 - p.ph, H - 1) - seg_first(i) + 1, 0);
+    };
+    // 16-byte units that hold `rows` rows from any position
+    auto seg_units = [&](int rows) { return rows > 0 ? (rows * Wd * 2 + 29) >> 4 : 0; };
+    const int area_bytes = RD * RAW + CFG::W_BYTES + 2 * HALF;
+    unsigned char *const raw = psm + kg * area_bytes;              // [RD][weights | input]
+    unsigned char *const cells = raw + RD * RAW;                   // weights | patch halves
+
+    // zeros into every patch cell (the padding keeps them)
+    const u32x4_t zero4 = {0u, 0u, 0u, 0u};
+    for (int o = t * 16; o < 2 * HALF; o += NTG * 16)
+        *reinterpret_cast<u32x4_t *>(cells + CFG::W_BYTES + o) = zero4;
+
+    // Two tables, built once by the first threads of each group in its raw
+    // area.  Per unit u of a channel's slot: {byte offset of its segment's
+    // first input row in channel 0, 16 * (u within the segment), -1 past the
+    // last unit}.  Per input row r: {that byte offset, position of the row in
+    // the slot (before the segment's misalignment), its patch cell, -}.
+    const int plane = __builtin_amdgcn_readfirstlane(H * Wd * 2);   // bytes per channel plane
+    const int xmis = (int)(reinterpret_cast<unsigned long long>(p.X) & 15);
+    int2 *const utab = reinterpret_cast<int2 *>(raw);               // [SU]
+    int4 *const rtab = reinterpret_cast<int4 *>(raw + SU * 8);      // rows
+    int nrows = 0;
+    {
+        int ub = 0;
+        for (int i = img0; i <= img1; ++i) {
+            const int n = seg_rows(i), f = seg_first(i), nu = seg_units(n);
+            const int start = xmis + (i * C * H + f) * Wd * 2;
+            for (int u = t; u < nu; u += NTG) utab[ub + u] = make_int2(start, u * 16);
+            for (int r = t; r < n; r += NTG)
+                rtab[nrows + r] = make_int4(start, ub * 16 + r * Wd * 2,
+                                            ((i - img0) * PH + f + r + p.ph - prow0) * WPA + p.pw, 0);
+            nrows += n;
+            ub += nu;
+        }
+        for (int u = ub + t; u < SU; u += NTG) utab[u] = make_int2(0, -1);
+    }
+    __syncthreads();
+
+    // Raw copies.  Weights: unit (output channel, u < 18); input: unit
+    // (channel < 16, u < SU).  Offsets are for chunk 0; a chunk adds a scalar
+    // offset, a multiple of 16 bytes for both.
+    int woff[NBW], xoff[NBX];
+    unsigned whi = 0;                                               // bit k: unit of the upper 8 channels
+#pragma unroll
+    for (int k = 0; k < NBW; ++k) {
+        const int v = (wave * NBW + k) * 64 + lane, oc = v / 18, u = v - oc * 18;
+        woff[k] = oc < BM && m0 + oc < OC ? (m0 + oc) * C * NTAP * 2 + u * 16 : kOOB;
+        whi |= (u >= 9 ? 1u : 0u) << k;
+    }
+    unsigned xhi = 0;
+#pragma unroll
+    for (int k = 0; k < NBX; ++k) {
+        const int v = (wave * NBX + k) * 64 + lane, ch = v / SU;
+        const int2 e = utab[v - ch * SU];
+        xoff[k] = e.y >= 0 ? ((e.x + ch * plane) & ~15) + e.y : kOOB;
+        xhi |= (ch >= 8 ? 1u : 0u) << k;
+    }
+    const i32x4 rw = make_rsrc(p.Wt, OC * C * NTAP * 2);
+    const i32x4 rx = make_rsrc(reinterpret_cast<const unsigned char *>(p.X) - xmis,
+                               (xmis + p.Nb * C * plane + 15) & ~15);
+    const unsigned raw_lds = __builtin_amdgcn_readfirstlane(lds_address(raw));
+    // copies of chunk kc into ring slot s (zeros past the last channel)
+    auto issue = [&](int kc, int s) __attribute__((always_inline)) {
+        const int c0 = kc * CC;
+        const bool lo = c0 < C, hi = c0 + 8 < C;
+        const int wso = lo ? c0 * NTAP * 2 : 0, xso = lo ? c0 * plane : 0;
+        const unsigned base = raw_lds + s * RAW;
+#pragma unroll
+        for (int k = 0; k < NBW; ++k)
+            dma16_so(rw, base + (wave * NBW + k) * 1024, lo && (hi || !((whi >> k) & 1)) ? woff[k] : kOOB, wso);
+#pragma unroll
+        for (int k = 0; k < NBX; ++k)
+            dma16_so(rx, base + CFG::WRAW + (wave * NBX + k) * 1024,
+                     lo && (hi || !((xhi >> k) & 1)) ? xoff[k] : kOOB, xso);
+    };
+
+    // This thread's patch items: source (raw byte of channel 0 of its half,
+    // before the segment's misalignment), that misalignment's constant part
+    // and the cell it fills (-1: none).
+    constexpr int slot = SU * 16;
+    int isrc[NI], imis[NI], idst[NI];
+    const int nitems = nrows * PPR;
+#pragma unroll
+    for (int k = 0; k < NI; ++k) {
+        const int j = t + k * NTG, h = j >= nitems ? 1 : 0, jh = j - h * nitems;
+        isrc[k] = 0; imis[k] = 0; idst[k] = -1;
+        if (jh < nitems) {
+            const int r = div_by(jh, pa.by_ppr), iw = (jh - r * PPR) * (PAIR ? 2 : 1);
+            const int4 e = rtab[r];
+            isrc[k] = 8 * h * slot + e.y + iw * 2;
+            imis[k] = e.x + 8 * h * plane;
+            idst[k] = CFG::W_BYTES + h * HALF + (e.z + iw) * 16;
+        }
+    }
+    auto repack = [&](int s) __attribute__((always_inline)) {
+        const unsigned char *R = raw + s * RAW;
+#pragma unroll
+        for (int k = 0; k < NSLAB; ++k) {
+            // slab j: output channel j >> 1, channels 8(j & 1) .. +7, nine taps
+            const int j = t + k * NTG, oc = j >> 1, h = j & 1;
+            if (j < 2 * BM) {
+                u32x4_t ws[NTAP];
+#pragma unroll
+                for (int q = 0; q < NTAP; ++q)
+                    ws[q] = *reinterpret_cast<const u32x4_t *>(R + j * (W_ROW / 2) + q * 16);
+                auto wv = [&](int e) __attribute__((always_inline)) {   // halfword e = channel e / 9, tap e % 9
+                    return (ws[e >> 3][(e >> 1) & 3] >> (16 * (e & 1))) & 0xffffu;
+                };
+                unsigned char *D = cells + (oc * CC + 8 * (h ^ ((oc >> 3) & 1))) * 2;
+#pragma unroll
+                for (int q = 0; q < NTAP; ++q) {
+                    u32x4_t v;
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) v[d] = wv(2 * d * NTAP + q) | (wv((2 * d + 1) * NTAP + q) << 16);
+                    *reinterpret_cast<u32x4_t *>(D + q * BM * CC * 2) = v;
+                }
+            }
+        }
+        const unsigned char *X = R + CFG::WRAW;
+#pragma unroll
+        for (int k = 0; k < NI; ++k) {
+            if (idst[k] >= 0) {
+                u32x4_t ev, od;   // the item's column (pair: its even and odd one)
+                unsigned v[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const unsigned char *q = X + isrc[k] + c * slot + ((imis[k] + c * plane) & 15);
+                    v[c] = PAIR ? *reinterpret_cast<const unsigned *>(q) : *reinterpret_cast<const unsigned short *>(q);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    ev[j] = (v[2 * j] & 0xffffu) | (v[2 * j + 1] << 16);
+                    od[j] = (v[2 * j] >> 16) | (v[2 * j + 1] & 0xffff0000u);
+                }
+                *reinterpret_cast<u32x4_t *>(cells + idst[k]) = ev;
+                if constexpr (PAIR) *reinterpret_cast<u32x4_t *>(cells + idst[k] + 16) = od;
+            }
+        }
+    };
+
+    // Fragment bases.  A (weights): output channel wm*WM + 32i + l32, the
+    // lane group's 8 channels (halves swapped when bit 3 of the channel is
+    // set: conflict-free).  B: the cell of this lane's pixel at tap (0, 0).
+    const int a_base = ((wm * WM + l32) * CC + 8 * (lgrp ^ ((l32 >> 3) & 1))) * 2;
+    int b_base[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int q = q0 + wn * WN + j * MI + l32;
+        int cell = 0;
+        if (q < N) {
+            const int img = div_by(q, pa.by_ohw), pix = q - img * OHW;
+            const int oh = div_by(pix, pa.by_ow), ow = pix - oh * OW;
+            cell = ((img - img0) * PH + oh * p.sh - prow0) * WPA + ow * p.sw;
+        }
+        b_base[j] = CFG::W_BYTES + lgrp * HALF + cell * 16;
+    }
+
+    typename MF::acc_t acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < MF::NACC; ++r) acc[i][j][r] = 0.f;
+
+    auto compute = [&]() __attribute__((always_inline)) {
+        u16x8 af[2][TM], bfr[2][TN];
+        auto frags = [&](int tap, int fb) __attribute__((always_inline)) {
+            const int kh = tap / 3, kw = tap - 3 * kh;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                af[fb][i] = *reinterpret_cast<const u16x8 *>(cells + a_base + (tap * BM + i * MI) * CC * 2);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                bfr[fb][j] = *reinterpret_cast<const u16x8 *>(cells + b_base[j] + kh * WPA * 16 + kw * 16);
+        };
+        frags(0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int tap = 0; tap < NTAP; ++tap) {
+            if (tap + 1 < NTAP) frags(tap + 1, (tap + 1) & 1);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = MF::mma(af[tap & 1][i], bfr[tap & 1][j], acc[i][j]);
+            // the next tap's reads between this tap's instructions (the
+            // scheduler would otherwise sink each read to just before its use)
+            constexpr int NM = TM * TN, ND = TM + TN, PER = (ND + NM - 1) / NM;
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                  // MFMA
+                if (tap + 1 < NTAP && m * PER < ND) __builtin_amdgcn_sched_group_barrier(0x100, PER, 0);  // DS read
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // Every group runs the same number of trips (chunks past the last one
+    // are copied as zeros), so the barriers match.  A trip:
+    // wait for this wave's copies of its chunk, barrier (every wave's have
+    // landed and every wave is done with the cells), repack, barrier (cells
+    // complete, raw slot read), refill the slot, compute.
+    const int nchunk = (C + CC - 1) / CC;
+    const int trips = (nchunk + KS - 1) / KS;
+    __syncthreads();                        // the tables have been read
+#pragma unroll
+    for (int s = 0; s < RD; ++s) issue(kg + s * KS, s);
+    for (int it = 0; it < trips; ++it) {
+        const int s = RD == 1 ? 0 : it % RD;
+        wait_vmcnt_and_lds<(RD - 1) * (NBW + NBX)>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        repack(s);
+        asm volatile("" ::: "memory");
+        wait_vmcnt_and_lds<(RD - 1) * (NBW + NBX)>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        issue(kg + (it + RD) * KS, s);
+        compute();
+    }
+    wait_vmcnt<0>();  // no copy may still be writing LDS when it is reused or the workgroup ends
+
+    if constexpr (KS > 1) {
+        // groups 1 .. KS-1 leave their sums in LDS (each lane its own
+        // registers, lane-contiguous); group 0 adds them in group order
+        float *red = reinterpret_cast<float *>(psm);
+        __syncthreads();
+        if (kg > 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        red[((((kg - 1) * CFG::NWAVES + wave) * TM + i) * TN + j) * 1024 + r * 64 + lane] = acc[i][j][r];
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int g = 1; g < KS; ++g)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        acc[i][j][r] += red[((((g - 1) * CFG::NWAVES + wave) * TM + i) * TN + j) * 1024 + r * 64 + lane];
+    }
+
+    // Output: pixels and channels outside Y are stored at an out-of-range
+    // offset, which drops them.
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.Y, 0, N * OC * 4, 0x00020000);
+    const bool whole = m0 + BM <= OC;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int q = q0 + wn * WN + j * MI + l32;
+        const int img = div_by(q, pa.by_ohw), pix = q - img * OHW;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int oc = m0 + wm * WM + i * MI + 4 * lgrp;
+            const int off = q < N ? (img * OC + oc) * OHW * 4 + pix * 4 : kOOB;
+#pragma unroll
+            for (int r = 0; r < MF::NACC; ++r) {
+                const int row = 8 * (r >> 2) + (r & 3);   // MF::row without the lane's part
+                const float v = (p.relu && acc[i][j][r] < 0.f) ? 0.f : acc[i][j][r];
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), ry,
+                                                      whole || oc + row < OC ? off : kOOB, row * OHW * 4, 0);
+            }
+        }
+    }
+}
+
+// Shapes whose patch kernel launch is laid out in *pa and *lds (bytes): 3x3,
+// whole 8-channel cells, 16-byte aligned weights, and a patch that fits SU
+// units per channel, NI items per thread and the LDS.
+template <typename CFG, int SU, int NI>
+bool patch_bf16_geom(const ConvArgs &a, bool pair, PatchArgs *pa, size_t *lds) {
+    using namespace patch_bf16;
+    if (a.R != 3 || a.S != 3 || a.C % 8 != 0) return false;
+    if ((reinterpret_cast<uintptr_t>(a.Wt) & 15) != 0) return false;
+    const long long OHW = (long long)a.OH * a.OW, N = a.Nb * OHW;
+    // output rows a tile can touch, and image borders among them (between
+    // two images the padded rows advance by 3 instead of stride_h)
+    const long long span = std::min<long long>((CFG::BN - 1 + a.OW - 1) / a.OW + 1, (long long)a.Nb * a.OH);
+    const long long cross = std::min<long long>((std::min<long long>(CFG::BN, N) - 1 + OHW - 1) / OHW, a.Nb - 1);
+    const long long wpa = std::max<long long>((long long)(a.OW - 1) * a.sw + 3, (long long)a.pw + a.W);
+    if (a.sh > 64 || wpa > 8192) return false;
+    const long long rows = (span - 1) * a.sh + 3 + cross * std::max(3 - a.sh, 0);
+    const long long half = (rows * wpa * 16 + 511) / 512 * 512;   // whole KiB for both halves
+    const long long raw = CFG::WRAW + (long long)CC * SU * 16;
+    const long long bytes = std::max<long long>(CFG::KS * (CFG::RD * raw + CFG::W_BYTES + 2 * half), CFG::RED_BYTES);
+    if (bytes > kMaxLds) return false;
+    const long long inrows = std::min<long long>(rows, (cross + 1) * (long long)a.H);   // rows inside the images
+    const long long ppr = pair ? a.W / 2 : a.W;
+    if (inrows * 2 * ppr > (long long)NI * CFG::NTG) return false;
+    const long long units = inrows * a.W * 2 / 16 + 3 * (cross + 1);   // 16-byte units per channel
+    if (units > SU || SU * 8 + inrows * 16 > raw) return false;        // (the tables share the raw area)
+    pa->c = a;
+    pa->by_ohw = fast_div(a.OH * a.OW);
+    pa->by_ow = fast_div(a.OW);
+    pa->by_ppr = fast_div((int)ppr);
+    pa->PH = (a.OH - 1) * a.sh + 3;
+    pa->WPA = (int)wpa;
+    pa->PPR = (int)ppr;
+    pa->half = (int)half;
+    *lds = (size_t)bytes;
+    return true;
+}
+
+template <typename CFG, int SU, int NI, bool PAIR>
+hipError_t launch_patch(const PatchArgs &pa, size_t lds, hipStream_t s) {
+    const int N = pa.c.Nb * pa.c.OH * pa.c.OW;
+    const unsigned tiles = (unsigned)(((pa.c.OC + CFG::BM - 1) / CFG::BM) * ((N + CFG::BN - 1) / CFG::BN));
+    PatchArgs args = pa;
+    void *kargs[] = {&args};
+    return hipLaunchKernel(reinterpret_cast<const void *>(&conv2d_bf16_patch_kernel<CFG, SU, NI, PAIR>),
+                           dim3(tiles), dim3(CFG::NT), kargs, lds, s);
+}
+
+// Tries the patch kernel with tile CFG (with its smaller slot and item count
+// only, if `small_only`: long rows leave the others little to gain); false if
+// the shape is outside it.
+template <typename CFG>
+bool try_patch_bf16(const ConvArgs &a, hipStream_t s, hipError_t *err, bool small_only = false) {
+    const bool pair = a.W % 2 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 3) == 0;
+    PatchArgs pa;
+    size_t lds;
+    if (patch_bf16_geom<CFG, CFG::SU0, 4>(a, pair, &pa, &lds))
+        *err = pair ? launch_patch<CFG, CFG::SU0, 4, true>(pa, lds, s) : launch_patch<CFG, CFG::SU0, 4, false>(pa, lds, s);
+    else if (!small_only && patch_bf16_geom<CFG, 2 * CFG::SU0, 9>(a, pair, &pa, &lds))
+        *err = pair ? launch_patch<CFG, 2 * CFG::SU0, 9, true>(pa, lds, s)
+                    : launch_patch<CFG, 2 * CFG::SU0, 9, false>(pa, lds, s);
+    else
+        return false;
+    return true;
+}
+
+// Outside the patch kernel's class: 128x128 gather tiles for more than 64
+// output channels, 64x64 when 64x128 tiles leave CUs idle.
+hipError_t launch_conv_bf16_gather(const ConvArgs &a, hipStream_t s) {
+    const long long N = (long long)a.Nb * a.OH * a.OW;
+    if (a.OC > 64) return launch_conv_bf16<128, 128, 32, 64, 64, 32, 8>(a, s);
+    if ((N + 127) / 128 < 256) return launch_conv_bf16<64, 64, 32, 32, 32, 32, 8>(a, s);
+    return launch_conv_bf16<64, 128, 32, 32, 64, 32, 8>(a, s);
+}
+
+typedef patch_bf16::Cfg<64, 256, 64, 64, 1, 2> PatchL;
+typedef patch_bf16::Cfg<64, 128, 32, 64, 1, 1> PatchM;
+typedef patch_bf16::Cfg<64, 128, 32, 64, 2, 1> PatchM2;
+typedef patch_bf16::Cfg<32, 64, 32, 32, 2, 1> PatchS2;
+typedef patch_bf16::Cfg<32, 64, 32, 32, 4, 1> PatchS4;
+
+template <typename CFG>
+hipError_t launch_conv_bf16_patch(const ConvArgs &a, hipStream_t s) {
+    hipError_t err;
+    if (try_patch_bf16<CFG>(a, s, &err)) return err;
+    return launch_conv_bf16_gather(a, s);
+}
+
+// The tile and split for a shape.  Every tile but PatchM's takes the LDS of a
+// whole CU, so its time doubles when the workgroups pass 256: the smallest
+// tile, with the reduction split furthest, that stays within one round
+// (128x28x28 -> 128 at batch 1, 8, 32: 32x64/4 9.0, 20.8, - us; 64x128/2
+// 11.6, 12.4, 24.2; 64x256 16.3, 16.9, 19.0; 64x128 12.5, 13.5, 20.2), and
+// past that 64x128 tiles, of which two fit a CU (64x57x57 -> 128 at batch 32:
+// 40.1 us against 50.9 with 64x256).
+hipError_t launch_conv_bf16_patch_auto(const ConvArgs &a, hipStream_t s) {
+    const long long N = (long long)a.Nb * a.OH * a.OW;
+    auto tiles = [&](int bm, int bn) { return (a.OC + bm - 1) / bm * ((N + bn - 1) / bn); };
+    hipError_t err;
+    if (tiles(32, 64) <= 256 && (try_patch_bf16<PatchS4>(a, s, &err) || try_patch_bf16<PatchS2>(a, s, &err)))
+        return err;
+    if (tiles(64, 128) <= 256 && try_patch_bf16<PatchM2>(a, s, &err)) return err;
+    if (tiles(64, 128) > 256 && tiles(64, 256) <= 256 && try_patch_bf16<PatchL>(a, s, &err, true)) return err;
+    if (try_patch_bf16<PatchM>(a, s, &err) || try_patch_bf16<PatchS2>(a, s, &err)) return err;
+    return launch_conv_bf16_gather(a, s);
+}
+
+// Shapes the halo kernel covers; anything else runs the patch kernel (which
+// itself falls back to the gather kernel).
 inline bool bf16_halo_eligible(const ConvArgs &a) {
     using namespace halo_bf16;
     if (a.R != 3 || a.S != 3 || a.sh != 1 || a.sw != 1) return false;
@@ -481,7 +982,7 @@ inline bool bf16_halo_eligible(const ConvArgs &a) {
 }
 
 hipError_t launch_conv_bf16_halo(const ConvArgs &a, hipStream_t s) {
-    if (!bf16_halo_eligible(a)) return launch_conv_bf16<64, 128, 32, 32, 64, 32, 8>(a, s);
+    if (!bf16_halo_eligible(a)) return launch_conv_bf16_patch_auto(a, s);
     const int OHW = a.OH * a.OW;
     const unsigned tiles = (unsigned)(((a.OC + halo_bf16::BM - 1) / halo_bf16::BM) * a.Nb *
                                       ((OHW + halo_bf16::BN - 1) / halo_bf16::BN));
@@ -881,6 +1382,15 @@ hipError_t launch_conv_bf16_rows(const ConvArgs &a, hipStream_t s) {
                           (BM / WM) * (BN / WN) * 64, (int)sizeof(int2)>                      \
     }
 
+// lds_stages names the split of the reduction over groups of waves: 2 the
+// smaller one of a tile (none; two groups for 32x64), 1 the larger (two; four)
+#define XTC_CONV_BF16_PATCH_INSTANCE(CFG, STAGES)                                             \
+    ConvInstance {                                                                            \
+        make_sched(CFG::BM, CFG::BN, 16, CFG::WM, CFG::WN, 32, 32, 16, STAGES, 0, 0, 2),       \
+            &launch_conv_bf16_patch<CFG>,                                                     \
+            &occupancy_of<&conv2d_bf16_patch_kernel<CFG, CFG::SU0, 4, true>, CFG::NT, 0>       \
+    }
+
 const ConvInstance kConvBf16Instances[] = {
     ConvInstance{make_sched(64, 256, 16, 64, 64, 32, 32, 16, 2, -1, 0, 2),  // halo, 3x3 stride 1
                  &launch_conv_bf16_halo,
@@ -888,8 +1398,13 @@ const ConvInstance kConvBf16Instances[] = {
     ConvInstance{make_sched(64, 64, 16, 32, 32, 32, 32, 16, 2, -1, 0, 3),  // row streaming, 3x3 s1, C 64
                  &launch_conv_bf16_rows,
                  &occupancy_of<&conv2d_bf16_rows_kernel, rows_bf16::NT, 0>},
-    XTC_CONV_BF16_INSTANCE(64, 128, 32, 32, 64, 32, 8),   // default for OC <= 64
-    XTC_CONV_BF16_INSTANCE(128, 128, 32, 64, 64, 32, 8),  // default for OC > 64
+    XTC_CONV_BF16_PATCH_INSTANCE(PatchL, 2),
+    XTC_CONV_BF16_PATCH_INSTANCE(PatchM, 2),
+    XTC_CONV_BF16_PATCH_INSTANCE(PatchM2, 1),
+    XTC_CONV_BF16_PATCH_INSTANCE(PatchS2, 2),
+    XTC_CONV_BF16_PATCH_INSTANCE(PatchS4, 1),
+    XTC_CONV_BF16_INSTANCE(64, 128, 32, 32, 64, 32, 8),   // outside the patch kernel's class
+    XTC_CONV_BF16_INSTANCE(128, 128, 32, 64, 64, 32, 8),  // the same for OC > 64
     XTC_CONV_BF16_INSTANCE(64, 64, 32, 32, 32, 32, 8),    // few output pixels
     XTC_CONV_BF16_INSTANCE(64, 128, 64, 32, 64, 32, 8),
     XTC_CONV_BF16_INSTANCE(64, 128, 64, 32, 64, 16, 8),   // 16x16x32 instruction tile

@@ -180,15 +180,10 @@ xtc_status xtc_default_schedule(xtc_op op, xtc_dtype dt, int64_t M, int64_t N, i
         // the row-streaming kernel (3x3 stride 1, 64 input channels, rows of
         // at most 64 pixels; 32x64x56x56 -> 64: 15.3 us kernel span against
         // 17 us for the halo-tiled kernel), which runs the halo-tiled kernel
-        // outside its class, and that one the 64x128 gather kernel outside
-        // its own (not 3x3 stride 1, odd widths, rows far from 56 pixels);
-        // the gather kernel with 128x128 tiles for more than 64 output
-        // channels, 64x64 when 64x128 tiles leave CUs idle
+        // outside its class, that one the patch kernel (any other 3x3 layer
+        // of whole 8-channel groups, its tile and split chosen from the
+        // layer's shape), and that one the gather kernel
         *out = make_sched(64, 64, 16, 32, 32, 32, 32, 16, 2, -1, 0, 3);
-        if (M > 64)
-            *out = make_sched(128, 128, 32, 64, 64, 32, 32, 16, 2, 8, 0);
-        else if (tiles(64, 128) < cus)
-            *out = make_sched(64, 64, 32, 32, 32, 32, 32, 16, 2, 8, 0);
         out->raster = 0;
         return XTC_OK;
     }

@@ -914,7 +914,7 @@ def _conv_f32_gather(s: dict, k_order: int, stages: int, dims) -> LdsCost:
 def conv_launch(dtype: str, s: dict, N, C, H, W, OC, R, S, stride, pad):
     """LDS cost of one conv launch of instance ``s``, or None when the kernel
     it runs for this shape is not modelled (the few-channel kernel's gather
-    form, when the patch does not fit)."""
+    form, when the patch does not fit; the bf16 patch kernel)."""
     sh, sw = (stride, stride) if isinstance(stride, int) else stride
     ph, pw = (pad, pad) if isinstance(pad, int) else pad
     OH, OW = (H + 2 * ph - R) // sh + 1, (W + 2 * pw - S) // sw + 1
@@ -951,11 +951,16 @@ def conv_launch(dtype: str, s: dict, N, C, H, W, OC, R, S, stride, pad):
         s = dict(s, k_order=2, block_n=256)   # the launcher falls back to the halo kernel
     if dtype == "bf16" and s["k_order"] == 2:
         span = (256 - 1 + OW - 1) // OW + 1
-        if halo_class and C % 16 == 0 and W % 2 == 0 and pw <= 2 and OW - pw + 3 <= 63 and span + 2 <= 8:
+        if (s.get("lds_pad", -1) < 0 and halo_class and C % 16 == 0 and W % 2 == 0 and pw <= 2 and OW - pw + 3 <= 63
+                and span + 2 <= 8):
             return conv_bf16_halo_launch(N, C, H, W, OC, ph, pw, a_swizzle=True, rotate=True,
                                          store_order=True)
-        # the halo launcher falls back to the gather kernel's 64x128 tiles
-        s = dict(s, k_order=0, block_m=64, block_n=128, block_k=32, wave_m=32, wave_n=64, mfma_m=32,
+        # then the patch kernel (not modelled) for 3x3 layers of whole
+        # 8-channel groups, then the gather kernel with a tile by shape
+        if R == 3 and S == 3 and C % 8 == 0:
+            return None
+        bm, bn = (128, 128) if OC > 64 else (64, 64) if _cdiv(N * OH * OW, 128) < 256 else (64, 128)
+        s = dict(s, k_order=0, block_m=bm, block_n=bn, block_k=32, wave_m=bm // 2, wave_n=bn // 2, mfma_m=32,
                  lds_pad=8)
     if dtype == "bf16" and s["k_order"] == 0:
         return conv_bf16_gather_launch(s["block_m"], s["block_n"], s["block_k"], s["wave_m"], s["wave_n"],

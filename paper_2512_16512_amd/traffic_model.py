@@ -468,6 +468,61 @@ def _cdiv(a: int, b: int) -> int:
     return -(-a // b)
 
 
+# (block_m, block_n, lds_stages) of the bf16 patch kernels -> (waves per group,
+# groups, raw chunks in flight)
+_BF16_PATCH = {(64, 256, 2): (4, 1, 2), (64, 128, 2): (4, 1, 1), (64, 128, 1): (4, 2, 1),
+               (32, 64, 2): (2, 2, 1), (32, 64, 1): (2, 4, 1)}
+
+
+def bf16_patch_tile(N, C, H, W, OC, R, S, stride, pad, only=None):
+    """(block_m, block_n) of the bf16 patch kernel the library runs for this
+    layer (16-byte aligned operands), or None outside its class; ``only``: the
+    one compiled tile an explicit schedule names.  Follows the launcher."""
+    sh = sw = stride
+    ph = pw = pad
+    OH, OW = (H + 2 * ph - R) // sh + 1, (W + 2 * pw - S) // sw + 1
+    OHW, pix = OH * OW, N * OH * OW
+
+    def fits(key, small_only=False):
+        bm, bn, _ = key
+        waves, groups, depth = _BF16_PATCH[key]
+        span = min((bn - 1 + OW - 1) // OW + 1, N * OH)
+        cross = min((min(bn, pix) - 1 + OHW - 1) // OHW, N - 1)
+        wpa = max((OW - 1) * sw + 3, pw + W)
+        if R != 3 or S != 3 or C % 8 or sh > 64 or wpa > 8192:
+            return False
+        rows = (span - 1) * sh + 3 + cross * max(3 - sh, 0)
+        half = _cdiv(rows * wpa * 16, 512) * 512
+        inrows = min(rows, (cross + 1) * H)
+        ppr = W // 2 if W % 2 == 0 else W
+        units = inrows * W * 2 // 16 + 3 * (cross + 1)
+        wraw = _cdiv(bm * 288 // 1024, waves) * waves * 1024
+        su0 = 64 if bn >= 128 else 32
+        for su, ni in [(su0, 4)] if small_only else [(su0, 4), (2 * su0, 9)]:
+            raw = wraw + 16 * su * 16
+            lds = groups * (depth * raw + 288 * bm + 2 * half)
+            red = (groups - 1) * bm * bn * 4
+            if (max(lds, red) <= 160 * 1024 and inrows * 2 * ppr <= ni * waves * 64 and units <= su
+                    and su * 8 + inrows * 16 <= raw):
+                return True
+        return False
+
+    def tiles(bm, bn):
+        return _cdiv(OC, bm) * _cdiv(pix, bn)
+
+    if only is not None:
+        return only[:2] if fits(only) else None
+    if tiles(32, 64) <= 256 and (fits((32, 64, 1)) or fits((32, 64, 2))):
+        return 32, 64
+    if tiles(64, 128) <= 256 and fits((64, 128, 1)):
+        return 64, 128
+    if tiles(64, 128) > 256 and tiles(64, 256) <= 256 and fits((64, 256, 2), True):
+        return 64, 256
+    if fits((64, 128, 2)):
+        return 64, 128
+    return (32, 64) if fits((32, 64, 2)) else None
+
+
 def conv_grid(dtype: str, s: dict, N, C, H, W, OC, R, S, stride, pad):
     """The tile grid of the kernel the library runs for conv instance ``s``
     on this shape: (BM, tiles_m, tiles_n, segments, forced XCD remap or
@@ -526,11 +581,15 @@ def conv_grid(dtype: str, s: dict, N, C, H, W, OC, R, S, stride, pad):
         s = dict(s, k_order=2, block_n=256)
     if dtype == "bf16" and s["k_order"] == 2:
         span = (256 - 1 + OW - 1) // OW + 1
-        if halo_class and C % 16 == 0 and W % 2 == 0 and pw <= 2 and OW - pw + 3 <= 63 and span + 2 <= 8:
+        if (s.get("lds_pad", -1) < 0 and halo_class and C % 16 == 0 and W % 2 == 0 and pw <= 2 and OW - pw + 3 <= 63
+                and span + 2 <= 8):
             tn, seg = per_image(256)
             return 64, _cdiv(OC, 64), tn, seg, None
-        s = dict(s, block_m=64, block_n=128)           # the gather kernel's 64x128 tiles
-        bm = 64
+        only = None if s["lds_pad"] < 0 else (s["block_m"], s["block_n"], s["lds_stages"])
+        bm, bn = bf16_patch_tile(N, C, H, W, OC, R, S, stride, pad, only) or (
+            # the gather kernel, its tile by shape
+            (128, 128) if OC > 64 else (64, 64) if _cdiv(N * OHW, 128) < 256 else (64, 128))
+        s = dict(s, block_m=bm, block_n=bn)
     if dtype == "bf16":
         tn, seg = flattened(s["block_n"])
         return bm, _cdiv(OC, bm), tn, seg, None

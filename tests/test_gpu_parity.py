@@ -234,6 +234,38 @@ def test_conv_small_int_exact_every_instance(x, shape):
             assert np.array_equal(got, ref), "conv %s %s: not bit-exact" % (shape, s)
 
 
+@pytest.mark.parametrize("N,C,H,W,OC,stride,pad", [
+    (5, 16, 7, 7, 33, (1, 1), (1, 1)),     # six images in one 256-pixel tile, odd rows
+    (3, 24, 14, 14, 70, (1, 1), (1, 1)),   # half a chunk left over, planes 8 bytes off 16-byte units
+    (2, 40, 28, 30, 96, (2, 2), (1, 1)),   # stride 2, tiles that cross an image
+    (1, 8, 9, 60, 65, (1, 2), (0, 2)),     # one half chunk, strides and pads of their own per axis
+    (4, 16, 3, 3, 16, (3, 3), (2, 2)),     # rows between images advance by less than the stride
+    (1, 72, 33, 57, 31, (1, 1), (3, 3)),   # padding of a whole kernel, odd width, five chunks
+    (2, 16, 1, 1, 40, (1, 1), (1, 1)),     # a single pixel
+])
+def test_conv_bf16_patch_edges(x, N, C, H, W, OC, stride, pad):
+    """The bf16 patch kernels (every tile and split) where their patch can go
+    wrong: image borders inside a tile, rows at any 2-byte position, channels
+    past the last chunk.  X starts 1, 2 and 8 elements past a 16-byte
+    boundary; the elements around it hold NaN.  Bit-exact (small integers)."""
+    import torch
+    X = xi.f32_to_bf16_bits(xi.small_int_f32(41, (N, C, H, W)))
+    Wt = xi.f32_to_bf16_bits(xi.small_int_f32(42, (OC, C, 3, 3)))
+    ref = oracle.conv2d(X, Wt, stride=stride, pad=pad)
+    Wd = to_dev(Wt)
+    for off in (1, 2, 8):
+        flat = np.full(X.size + 24, 0x7FC0, dtype=np.uint16)
+        flat[off:off + X.size] = X.ravel()
+        Fd = to_dev(flat)
+        for s in [s for s in x.xtc_sched_list(x.XTC_OP_CONV2D, x.XTC_BF16) if s.k_order >= 2] + [None]:
+            Yd = torch.full(ref.shape, 7.0, dtype=torch.float32, device="cuda")
+            say("bf16 patch", (N, C, H, W, OC, stride, pad), off, s)
+            st = x.xtc_conv2d_nchw(N, C, H, W, OC, 3, 3, *stride, *pad, Fd.data_ptr() + 2 * off, Wd.data_ptr(),
+                                   Yd.data_ptr(), x.XTC_BF16, s, torch.cuda.current_stream().cuda_stream)
+            assert st == 0, x.xtc_status_str(st)
+            assert np.array_equal(to_host(Yd), ref), (off, s)
+
+
 # ---------------------------------------------------------- closed forms
 
 
