@@ -216,30 +216,15 @@ xtc_status xtc_default_schedule(xtc_op op, xtc_dtype dt, int64_t M, int64_t N, i
         out->raster = 0;
         return XTC_OK;
     }
-    bool mid = false, big = false;
+    bool mid = false;
     if (dt == XTC_F32) {
-        // Direct-to-LDS tiles from 256x256 (a tile per CU) through 256x128
-        // and 128x128 (two tiles per CU); the reduction-split kernels for
-        // long reductions with a narrow operand; 64x64 direct-to-LDS tiles
-        // down to half a tile per CU (these won from 512x1024x128 to
-        // 2048^3); below that, the largest reduction-split tile that still
-        // gives one tile per CU (measured over 16x16 .. 128x128 tiles on
-        // shapes from 256^3 to 4096^3 and skinny ones such as 128x128x4096
-        // and 64x4096x1024).
-        if (tiles(256, 256) >= cus) {
-            // eight 128x64 waves, one workgroup per CU: half the copy
-            // traffic per FLOP of 256x128 tiles (4096^3: 141.3 -> 145.3
-            // TFLOP/s in one sweep)
-            *out = make_sched(256, 256, 32, 128, 64, 32, 32, 2, 2, -1, 0);
-            big = true;
-        } else if (tiles(256, 128) >= 2 * cus) {
-            // eight 64x64 waves: a quarter less copy traffic per FLOP than
-            // 128x128 (4096^3: 139.6 -> 142.5 TFLOP/s)
-            *out = make_sched(256, 128, 32, 64, 64, 32, 32, 2, 2, -1, 0);
-            big = true;
-        } else if (tiles(128, 128) >= 2 * cus) {
-            *out = make_sched(128, 128, 32, 64, 64, 32, 32, 2, 2, -1, 0);
-        } else if (K >= 2048 && (M < N ? M : N) <= 32 && tiles(32, 32) >= cus) {
+        // The reduction-split kernels for long reductions with a narrow
+        // operand; the direct-to-LDS tiles where they give the CUs enough
+        // work; below that, the largest reduction-split tile that still gives
+        // one tile per CU (measured over 16x16 .. 128x128 tiles on shapes from
+        // 256^3 to 4096^3 and skinny ones such as 128x128x4096 and
+        // 64x4096x1024).
+        if (K >= 2048 && (M < N ? M : N) <= 32 && tiles(32, 32) >= cus) {
             // One operand has at most 32 rows (or columns) and the
             // reduction is long: the product streams the other operand from
             // HBM.  The reduction-split kernels read it straight into
@@ -259,13 +244,48 @@ xtc_status xtc_default_schedule(xtc_op op, xtc_dtype dt, int64_t M, int64_t N, i
                 out->raster = 4;
             }
             return XTC_OK;
-        } else if (tiles(64, 64) >= cus / 2) {
-            *out = make_sched(64, 64, 32, 32, 32, 32, 32, 2, 2, -1, 0);
-            // at most one tile per CU and a long reduction: two groups of
-            // four waves per tile, each on half of the K-steps, so that each
+        } else if (tiles(64, 64) >= cus / 2 || tiles(64, 32) >= 160) {
+            // The CU with the most tiles sets the time: ceil(tiles / 256)
+            // tiles of block_m * block_n work at the rate the kernel reaches
+            // with that many of its workgroups on a CU.  The rates (shares of
+            // the matrix peak with 1, 2, 3 and more tiles per CU) are from
+            // 20 shapes between 512x1024x768 and 4096^3; the estimate is
+            // within 12% on those with K >= 1000 and picks the fastest tile
+            // on all but one (5% slower).  Against the fixed thresholds used
+            // before: 1536^3 76.9 -> 71.1 us, 2999^3 586 -> 478,
+            // 512x1024x768 16.0 -> 12.1, 128x4096x1024 20.0 -> 16.0.
+            struct Tile {
+                int m, n;
+                double rate[4];
+            };
+            static const Tile kTiles[] = {
+                {256, 256, {.93, .93, .93, .93}}, {256, 128, {.84, .90, .90, .90}},
+                {128, 128, {.76, .82, .82, .82}}, {128, 64, {.62, .82, .82, .82}},
+                {64, 64, {.63, .74, .77, .77}},   {64, 32, {.45, .57, .65, .70}},
+            };
+            const Tile *best = nullptr;
+            double least = 0;
+            for (const Tile &t : kTiles) {
+                const int64_t per_cu = cdiv(tiles(t.m, t.n), cus);
+                const double cost = (double)per_cu * t.m * t.n / t.rate[per_cu < 4 ? per_cu - 1 : 3];
+                if (!best || cost < least) {
+                    best = &t;
+                    least = cost;
+                }
+            }
+            if (best->m == 256 && best->n == 256)        // eight 128x64 waves
+                *out = make_sched(256, 256, 32, 128, 64, 32, 32, 2, 2, -1, 0);
+            else if (best->m == 256)                     // eight 64x64 waves
+                *out = make_sched(256, 128, 32, 64, 64, 32, 32, 2, 2, -1, 0);
+            else
+                *out = make_sched(best->m, best->n, 32, best->m / 2, best->n == 32 ? 32 : best->n / 2, 32, 32, 2,
+                                  2, -1, 0);
+            // few tiles per CU and a long reduction: two groups of four
+            // waves per 64x64 tile, each on half of the K-steps, so that each
             // SIMD holds two waves (1000^3: 24.3 -> 22.2 us, 1024^3: 23.7 ->
-            // 22.5 us; no gain with several tiles per CU, a loss for K = 128)
-            if (tiles(64, 64) <= cus && K >= 512) out->k_split = 2;
+            // 22.5 us; no gain with several tiles per CU, a loss for K = 128);
+            // the 64x32 tile, two waves without it, always has them
+            if (best->n == 32 || (best->n == 64 && best->m == 64 && tiles(64, 64) <= cus && K >= 512)) out->k_split = 2;
             mid = true;
         } else if (tiles(64, 32) >= cus)
             *out = make_sched(64, 32, 16, 64, 32, 32, 32, 2, 0, 0, 0, 0, 4);
@@ -286,7 +306,7 @@ xtc_status xtc_default_schedule(xtc_op op, xtc_dtype dt, int64_t M, int64_t N, i
             *out = make_sched(64, 64, 64, 32, 32, 32, 32, 16, 2, 8, 0);
     }
     const int64_t t = tiles(out->block_m, out->block_n);
-    out->raster = (mid || big) ? 4 : (t >= 64 ? 8 : 0);
+    out->raster = mid ? 4 : (t >= 64 ? 8 : 0);
     // The register-fed reduction-split tiles: column-major order (graph
     // replays interleaved on one machine: 256^3 3.36 -> 3.25 us, 256x258x512
     // 5.77 -> 5.57 us, the 256x1024x128 matmul+relu 4.91 -> 4.78 us)
@@ -385,7 +405,7 @@ xtc_status matmul_impl(int64_t M, int64_t N, int64_t K, const void *A, int64_t l
     const bool b_rows = aligned16(B) && (ldb * elt) % 16 == 0;
     bool vec;
     switch (inst->vec_rule) {
-        case kARowsOnly: vec = K == 0 || (a_rows && (K * elt) % 16 == 0); break;
+        case kWholeK: vec = (K * elt) % 16 == 0; break;
         case kWholeChunks:
             vec = K == 0 || (a_rows && b_rows && (K * elt) % 16 == 0 && (N * elt) % 16 == 0);
             break;

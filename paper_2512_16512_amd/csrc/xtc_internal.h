@@ -58,7 +58,7 @@ hipError_t occupancy_of(int K, int *wg_per_cu) {
 enum VecRule {
     kRowsAligned = 0,  // 16-byte aligned A and B rows (base pointers and leading dimensions)
     kWholeChunks = 1,  // that, and K and N multiples of 16 bytes of elements
-    kARowsOnly = 2,    // 16-byte aligned A rows and K a multiple of 16 bytes (B read per element)
+    kWholeK = 2,       // K a multiple of 16 bytes of elements (rows at any element boundary)
 };
 
 // One compiled kernel instance.

@@ -446,7 +446,7 @@ def gemm_f32_dma_stage(BM, BN, BK, WM, WN, MI, swz_a=swz_a_f32) -> LdsCost:
     fragment set, TM ds_read_b128 A fragments and 4*TN ds_read_b32 B
     values per wave (B rows swizzled by lane group)."""
     KG = 2 if MI == 32 else 4
-    KCH, SWB = 4 * KG, 16 // KG
+    KCH, SWB = 4 * KG, 16 // KG if BN >= 64 else 0
     RA, CA, RB = BK * 4, BK // 4, BN * 4
     TM, TN = WM // MI, WN // MI
     cost = LdsCost()
