@@ -548,6 +548,184 @@ gemm_bf16_dma_kernel(GemmArgs p) {
         }
 }
 
+// ---------------------------------------------------------------------------
+// Register-fed reduction-split kernel (lds_stages = 0, k_split = KS) for
+// products with few output tiles: few rows or columns, or all three extents
+// small.  The LDS-staged kernels give 32x1000x2048 sixteen 64x64 tiles, each
+// one serial chain of stages (29.3 us, 150 GB/s); here a 16*TM x 32 tile is
+// shared by KS waves, wave g reducing the 32-k steps g, g + KS, ..., with the
+// operands straight from memory to the 16x16x32 instruction's registers
+// through a ring of D register buffers, so that a CU keeps KS*(D-1) steps of
+// loads in flight (32x1000x2048: 5.4 us; 8 waves in place of 4 gain nothing,
+// the loads of a CU being the limit).  No LDS, no barrier before the end.
+//  - A: a lane's 8 consecutive k of its row, one 16-byte load;
+//  - B is row-major, and the instruction wants 8 consecutive k of one column
+//    per lane.  Lane c of 16 loads the dword of columns 2c, 2c + 1 of eight
+//    rows (64 contiguous bytes per row), and the low halves make the fragment
+//    of the even columns, the high halves that of the odd ones: two column
+//    blocks per load, interleaved in C, no transpose;
+//  - buffer loads need 4-byte alignment and are range-checked per dword.
+//    ODD takes rows at any 2-byte boundary: A as the dwords that cover the
+//    8 values, shifted by the row's parity, B as single values;
+//  - A values past K (of the next row) are cleared in the fragments of the
+//    last step, so that they do not multiply the zeros of B as infinities.
+// The partial tiles are added through LDS in the order g = 0, 1, ..., KS-1.
+template <int TM, int KS, int D, bool ODD>
+__global__ void __launch_bounds__(KS * 64)
+gemm_bf16_ksplit_kernel(GemmArgs p) {
+    typedef Bf16Mfma<16> MF;
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int BM = 16 * TM, BN = 32, BK = 32;
+    constexpr int NREG = TM * 2 * 4;
+    __shared__ float red[KS][NREG][64];
+
+    const int lane = threadIdx.x & 63;
+    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lrow = lane & 15, lgrp = lane >> 4;
+    const int M = p.M, N = p.N, K = p.K, lda = p.lda, ldb = p.ldb;
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+    int tm, tn;
+    tile_coords(blockIdx.x, gridDim.x, tiles_m, tiles_n, p.raster, p.xcd_remap, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+
+    // resources from the dword that holds the first element to the dword
+    // that holds the last one
+    const unsigned long long abase = reinterpret_cast<unsigned long long>(p.A);
+    const unsigned long long bbase = reinterpret_cast<unsigned long long>(p.B);
+    const int amis = ODD ? (int)(abase & 2) : 0, bmis = ODD ? (int)(bbase & 2) : 0;
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void *>(abase - amis), 0, (amis + ((M - 1) * lda + K) * 2 + 3) & ~3, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void *>(bbase - bmis), 0, K > 0 ? (bmis + ((K - 1) * ldb + N) * 2 + 3) & ~3 : 0,
+        0x00020000);
+    unsigned aoff[TM];                 // byte offset of the lane's row (floored to a dword)
+    unsigned ash[TM];                  // 2 where the row starts in the middle of a dword
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int r = m0 + i * 16 + lrow, o = amis + r * lda * 2;
+        aoff[i] = r < M ? (unsigned)o & ~3u : (unsigned)kOOB;
+        ash[i] = (unsigned)o & 2;
+    }
+    const int c0 = n0 + 2 * lrow;      // the lane's column pair
+    const int boff = c0 < N ? bmis + c0 * 2 : kOOB;
+    const int boff1 = c0 + 1 < N ? bmis + c0 * 2 + 2 : kOOB;   // (ODD)
+
+    constexpr int NB = ODD ? 16 : 8;
+    u32x4 fa[D][TM];
+    unsigned fx[D][TM];                // (ODD) the dword after the 16 bytes
+    unsigned fb[D][NB];
+    auto load = [&](const int buf, const int kt) __attribute__((always_inline)) {
+        const int kb = kt * BK + 8 * lgrp;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int off = kb < K ? (int)(aoff[i] + (unsigned)kb * 2u) : kOOB;
+            fa[buf][i] = __builtin_amdgcn_raw_buffer_load_b128(ra, off, 0, 0);
+            if constexpr (ODD) fx[buf][i] = __builtin_amdgcn_raw_buffer_load_b32(ra, off, 16, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            // unsigned: an out-of-range column plus a row offset stays past
+            // the end (spans are below 2^31 - 48 bytes)
+            const unsigned ro = (unsigned)min(kb + e, K) * (unsigned)ldb * 2u;
+            if constexpr (ODD) {
+                const bool ok = kb + e < K;   // the last dword may hold a value past the end
+                fb[buf][2 * e] = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(
+                    rb, ok ? (int)(ro + (unsigned)boff) : kOOB, 0, 0);
+                fb[buf][2 * e + 1] = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(
+                    rb, ok ? (int)(ro + (unsigned)boff1) : kOOB, 0, 0);
+            } else {
+                fb[buf][e] = __builtin_amdgcn_raw_buffer_load_b32(rb, (int)(ro + (unsigned)boff), 0, 0);
+            }
+        }
+    };
+
+    typename MF::acc_t acc[TM][2];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+
+    auto compute = [&](const int buf, const int kt) __attribute__((always_inline)) {
+        u32x4 b[2];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if constexpr (ODD) {
+                b[0][q] = fb[buf][4 * q] | (fb[buf][4 * q + 2] << 16);
+                b[1][q] = fb[buf][4 * q + 1] | (fb[buf][4 * q + 3] << 16);
+            } else {
+                b[0][q] = (fb[buf][2 * q] & 0xffffu) | (fb[buf][2 * q + 1] << 16);
+                b[1][q] = (fb[buf][2 * q] >> 16) | (fb[buf][2 * q + 1] & 0xffff0000u);
+            }
+        }
+        const int left = K - (kt * BK + 8 * lgrp);          // k values left at this lane's 8
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            u32x4 a = fa[buf][i];
+            if constexpr (ODD) {
+                const unsigned w[5] = {a[0], a[1], a[2], a[3], fx[buf][i]};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) a[q] = __builtin_amdgcn_alignbyte(w[q + 1], w[q], ash[i]);
+            }
+            if ((kt + 1) * BK > K) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    a[q] &= (2 * q < left ? 0xffffu : 0u) | (2 * q + 1 < left ? 0xffff0000u : 0u);
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = MF::mma(__builtin_bit_cast(u16x8, a), __builtin_bit_cast(u16x8, b[j]), acc[i][j]);
+        }
+    };
+
+    // D K-steps per iteration; steps past the end are loaded as zeros, so
+    // that the wait counts stay exact, and not computed.
+    const int KT = (K + BK - 1) / BK;
+#pragma unroll
+    for (int d = 0; d + 1 < D; ++d) load(d, g + d * KS);
+    for (int base = g; base < KT; base += D * KS) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            load((d + D - 1) % D, base + (d + D - 1) * KS);
+            if (d == 0 || base + d * KS < KT) compute(d, base + d * KS);
+        }
+    }
+
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[g][(i * 4 + r) * 2 + j][lane] = acc[i][j][r];
+    __syncthreads();
+    float *__restrict__ C = p.C;
+    const int ldc = p.ldc;
+    for (int q = g; q < NREG / 2; q += KS) {       // register pair (i, r) of both column blocks
+        float v0 = red[0][2 * q][lane], v1 = red[0][2 * q + 1][lane];
+#pragma unroll
+        for (int h = 1; h < KS; ++h) {
+            v0 += red[h][2 * q][lane];
+            v1 += red[h][2 * q + 1][lane];
+        }
+        const int row = m0 + (q >> 2) * 16 + 4 * lgrp + (q & 3);
+        if (row < M) {
+            float *c = C + row * ldc + c0;
+            if (c0 < N) c[0] = (p.relu && v0 < 0.f) ? 0.f : v0;
+            if (c0 + 1 < N) c[1] = (p.relu && v1 < 0.f) ? 0.f : v1;
+        }
+    }
+}
+
+template <int TM, int KS, int D, bool ODD>
+hipError_t launch_bf16_ksplit(const GemmArgs &a, hipStream_t s) {
+    const unsigned tiles = (unsigned)(((a.M + 16 * TM - 1) / (16 * TM)) * ((a.N + 31) / 32));
+    GemmArgs args = a;
+    void *kargs[] = {&args};
+    return hipLaunchKernel(reinterpret_cast<const void *>(&gemm_bf16_ksplit_kernel<TM, KS, D, ODD>), dim3(tiles),
+                           dim3(KS * 64), kargs, 0, s);
+}
+
 template <int BM, int BN, int BK, int WM, int WN, int MI, int STAGES>
 hipError_t launch_bf16_dma(const GemmArgs &a, hipStream_t s) {
     typedef Bf16DmaCfg<BM, BN, BK, WM, WN, MI, STAGES> G;
@@ -593,6 +771,15 @@ hipError_t launch_bf16(const GemmArgs &a, hipStream_t s) {
                           (BM / WM) * (BN / WN) * 64, 0>                                      \
     }
 
+// Register-fed reduction split: KS waves per 16*TM x 32 tile, D steps in
+// flight; the ODD form for rows off a 4-byte boundary.
+#define XTC_BF16_KSPLIT_INSTANCE(TM, KS, D)                                                   \
+    GemmInstance {                                                                            \
+        make_sched(16 * TM, 32, 32, 16 * TM, 32, 16, 16, 32, 0, 0, 0, 0, KS),                  \
+            &launch_bf16_ksplit<TM, KS, D, false>, &launch_bf16_ksplit<TM, KS, D, true>,      \
+            kRowsDword, &occupancy_of<&gemm_bf16_ksplit_kernel<TM, KS, D, false>, KS * 64, 0> \
+    }
+
 const GemmInstance kBf16Instances[] = {
     XTC_BF16_DMA_INSTANCE(256, 256, 32, 128, 64, 32, 4),  // default for large problems
     XTC_BF16_DMA_INSTANCE(256, 256, 64, 128, 64, 32, 2),
@@ -602,6 +789,9 @@ const GemmInstance kBf16Instances[] = {
     XTC_BF16_DMA_INSTANCE(64, 128, 32, 32, 64, 32, 4),
     XTC_BF16_DMA_INSTANCE(64, 128, 64, 32, 64, 32, 2),
     XTC_BF16_DMA_INSTANCE(128, 128, 64, 64, 64, 16, 2),
+    XTC_BF16_KSPLIT_INSTANCE(1, 4, 3),   // 16x32 tiles: few rows
+    XTC_BF16_KSPLIT_INSTANCE(2, 4, 3),   // 32x32 tiles
+    XTC_BF16_KSPLIT_INSTANCE(4, 4, 3),   // 64x32 tiles
     XTC_BF16_INSTANCE(256, 256, 64, 128, 64, 32, 8),
     XTC_BF16_INSTANCE(128, 128, 64, 64, 64, 32, 8),
     XTC_BF16_INSTANCE(64, 64, 64, 32, 32, 32, 8),         // small problems

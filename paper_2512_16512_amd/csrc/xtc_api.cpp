@@ -294,9 +294,23 @@ xtc_status xtc_default_schedule(xtc_op op, xtc_dtype dt, int64_t M, int64_t N, i
         else
             *out = make_sched(16, 16, 32, 16, 16, 16, 16, 4, 0, 0, 0, 0, 4);
     } else {
+        // The register-fed reduction-split kernels where their 64x32 tiles do
+        // not outnumber the CUs (32x1000x2048: 29.7 us with LDS-staged tiles,
+        // 5.4; 512^3: 6.7, 4.5; 512x1024x768: 8.6, 6.8; past it the staged
+        // tiles win: 1024^3 10.7 against 13.1) or one operand is narrow
+        // (10000x30x2000: 70.7, 13.0; 32768x16x4096: 48.2, 46.4); else the
         // direct-to-LDS tiles from 256x256 down to 64x128 (half a tile per
-        // CU), then the register-staged 64x64 tiles
-        if (tiles(256, 256) >= cus)
+        // CU), then the register-staged 64x64 tiles.
+        if (tiles(64, 32) <= cus || (M < N ? M : N) <= 32) {
+            // Of the three, the tile with the least work on the fullest CU: a
+            // k-step of 16*TM rows costs TM row loads and 8 column loads,
+            // about 56, 72 and 104 clocks (the order it gives matches the
+            // measured one on 14 of 15 shapes, and is 17% off on the other).
+            const int64_t c16 = sat_mul(cdiv(tiles(16, 32), cus), 56), c32 = sat_mul(cdiv(tiles(32, 32), cus), 72),
+                          c64 = sat_mul(cdiv(tiles(64, 32), cus), 104);
+            const int bm = c16 <= c32 && c16 <= c64 ? 16 : c32 <= c64 ? 32 : 64;
+            *out = make_sched(bm, 32, 32, bm, 32, 16, 16, 32, 0, 0, 0, 0, 4);
+        } else if (tiles(256, 256) >= cus)
             *out = make_sched(256, 256, 32, 128, 64, 32, 32, 16, 4, -1, 0);
         else if (tiles(128, 128) >= cus)
             *out = make_sched(128, 128, 32, 64, 64, 32, 32, 16, 4, -1, 0);
@@ -405,6 +419,9 @@ xtc_status matmul_impl(int64_t M, int64_t N, int64_t K, const void *A, int64_t l
     const bool b_rows = aligned16(B) && (ldb * elt) % 16 == 0;
     bool vec;
     switch (inst->vec_rule) {
+        case kRowsDword:
+            vec = aligned_to(A, 4) && aligned_to(B, 4) && (lda * elt) % 4 == 0 && (ldb * elt) % 4 == 0;
+            break;
         case kWholeK: vec = (K * elt) % 16 == 0; break;
         case kWholeChunks:
             vec = K == 0 || (a_rows && b_rows && (K * elt) % 16 == 0 && (N * elt) % 16 == 0);

@@ -58,6 +58,7 @@ hipError_t occupancy_of(int K, int *wg_per_cu) {
 enum VecRule {
     kRowsAligned = 0,  // 16-byte aligned A and B rows (base pointers and leading dimensions)
     kWholeChunks = 1,  // that, and K and N multiples of 16 bytes of elements
+    kRowsDword = 3,    // 4-byte aligned A and B rows (base pointers and leading dimensions)
     kWholeK = 2,       // K a multiple of 16 bytes of elements (rows at any element boundary)
 };
 

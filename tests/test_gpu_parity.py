@@ -234,6 +234,36 @@ def test_conv_small_int_exact_every_instance(x, shape):
             assert np.array_equal(got, ref), "conv %s %s: not bit-exact" % (shape, s)
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (16, 32, 32), (17, 33, 33), (5, 31, 7), (64, 32, 128), (65, 66, 390),
+                                   (3, 300, 1030), (130, 2, 96)])
+@pytest.mark.parametrize("oa,ob,pa,pb", [(0, 0, 0, 0), (2, 4, 2, 6), (1, 0, 0, 1), (3, 7, 1, 3)])
+def test_bf16_register_fed_split_edges(x, M, N, K, oa, ob, pa, pb):
+    """The bf16 register-fed reduction-split tiles at the edges of their tiles
+    and k-steps, with operands ``oa``/``ob`` elements past a 16-byte boundary
+    and rows padded by ``pa``/``pb``: 4-byte aligned rows and rows at any
+    2-byte boundary.  Infinities around and between the rows must not reach
+    the result.  Bit-exact (small integers)."""
+    import torch
+    A = xi.f32_to_bf16_bits(xi.small_int_f32(51, (M, K)))
+    B = xi.f32_to_bf16_bits(xi.small_int_f32(52, (K, N)))
+    ref = oracle.matmul(A, B)
+
+    def place(arr, pad, off):
+        ld = arr.shape[1] + pad
+        flat = np.full(off + arr.shape[0] * ld + 16, 0x7F80, dtype=np.uint16)   # +inf
+        flat[off:off + arr.shape[0] * ld].reshape(-1, ld)[:, :arr.shape[1]] = arr
+        return to_dev(flat)
+
+    Ad, Bd = place(A, pa, oa), place(B, pb, ob)
+    for s in [s for s in x.xtc_sched_list(x.XTC_OP_MATMUL, x.XTC_BF16) if s.k_split > 1] + [None]:
+        Cd = torch.full((M, N), 7.0, dtype=torch.float32, device="cuda")
+        say("bf16 split", (M, N, K), (oa, ob, pa, pb), s)
+        st = x.xtc_matmul(M, N, K, Ad.data_ptr() + 2 * oa, K + pa, Bd.data_ptr() + 2 * ob, N + pb, Cd.data_ptr(), N,
+                          x.XTC_BF16, s, torch.cuda.current_stream().cuda_stream)
+        assert st == 0, x.xtc_status_str(st)
+        assert np.array_equal(to_host(Cd), ref), s
+
+
 @pytest.mark.parametrize("N,C,H,W,OC,stride,pad", [
     (5, 16, 7, 7, 33, (1, 1), (1, 1)),     # six images in one 256-pixel tile, odd rows
     (3, 24, 14, 14, 70, (1, 1), (1, 1)),   # half a chunk left over, planes 8 bytes off 16-byte units
