@@ -7,9 +7,11 @@ kernels of ``libxtc.so``.  The functions ``xtc_matmul``, ``xtc_conv2d_nchw``,
 are Python ints holding device addresses; the stream is a ``hipStream_t`` as
 an int, 0 for the null stream).  ``matmul`` and ``conv2d_nchw`` are
 conveniences over torch device tensors (torch provides memory and the
-current stream, nothing else).
+current stream, nothing else); the plain calls among theirs go through
+``_binding.so`` (csrc/torch_binding.cpp), which saves the interpreter's share
+of a call.
 
-If the library has not been built, importing this package raises
+If the library or the binding has not been built, importing this package raises
 ``ImportError``: there is no fallback implementation.
 """
 from __future__ import annotations
@@ -117,6 +119,19 @@ def _load():
 
 _lib = _load()
 
+
+def _load_binding():
+    # needs torch; without it the conveniences below cannot be called either
+    try:
+        import torch  # noqa: F401
+    except ImportError:
+        return None
+    from . import _binding
+    return _binding
+
+
+_fast = _load_binding()
+
 # Every symbol include/xtc.h declares.
 EXPORTS = ("xtc_matmul", "xtc_conv2d_nchw", "xtc_matmul_relu", "xtc_conv2d_nchw_relu",
            "xtc_default_schedule", "xtc_sched_occupancy", "xtc_sched_check",
@@ -222,6 +237,10 @@ def matmul(a, b, out=None, sched=None, relu=False):
     ``a`` [M,K] and ``b`` [K,N] are both float32 or both bfloat16 CUDA tensors
     with unit column stride; ``out`` is float32 [M,N] (allocated when None).
     Enqueued on torch's current stream."""
+    if sched is None and _fast is not None:
+        c = _fast.matmul(a, b, out, relu)
+        if c is not None:
+            return c
     import torch
     _check_rowmajor(a, "a")
     _check_rowmajor(b, "b")
@@ -253,6 +272,10 @@ def conv2d_nchw(x, w, stride=1, pad=0, out=None, sched=None, relu=False):
     """Zero-padded cross-correlation of NCHW ``x`` with OIHW ``w`` (both
     float32 or both bfloat16, contiguous CUDA tensors) into a float32 NCHW
     ``out`` (relu fused into the epilogue when ``relu``)."""
+    if sched is None and _fast is not None:
+        y = _fast.conv2d_nchw(x, w, stride, pad, out, relu)
+        if y is not None:
+            return y
     import torch
     if x.dim() != 4 or w.dim() != 4 or not x.is_contiguous() or not w.is_contiguous():
         raise ValueError("x and w must be contiguous 4-D tensors")

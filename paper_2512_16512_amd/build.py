@@ -1,8 +1,10 @@
-"""Build ``libxtc.so`` (the gfx950 kernels and the C ABI) in-tree with hipcc.
+"""Build ``libxtc.so`` (the gfx950 kernels and the C ABI) and ``_binding.so``
+(its entry points over torch tensors, host code only) in-tree.
 
-Every translation unit is compiled for gfx950 only, with packed-fp32
-instruction selection disabled, then linked into one shared library next to
-this file.  Run ``python paper_2512_16512_amd/build.py`` (a plain script: importing the
+Every translation unit of the library is compiled with hipcc for gfx950 only,
+with packed-fp32 instruction selection disabled, then linked into one shared
+library next to this file; the binding is compiled against torch's headers and
+linked to it.  Run ``python paper_2512_16512_amd/build.py`` (a plain script: importing the
 package needs the built library) or call ``build()``.
 """
 from __future__ import annotations
@@ -10,11 +12,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libxtc.so")
+BINDING = os.path.join(HERE, "_binding.so")
 OBJDIR = os.path.join(HERE, "_build")
 
 SOURCES = ["gemm_f32.hip", "gemm_bf16.hip", "conv2d_f32.hip", "conv2d_bf16.hip", "xtc_api.cpp"]
@@ -39,10 +43,44 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
+def _run(cmd, what: str, verbose: bool) -> None:
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("%s failed:\n%s%s" % (what, r.stdout, r.stderr))
+
+
+def _compile_binding(verbose: bool) -> str:
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    obj = os.path.join(OBJDIR, "torch_binding.o")
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+          "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+          "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
+          "-isystem", sysconfig.get_paths()["include"],
+          "-c", os.path.join(CSRC, "torch_binding.cpp"), "-o", obj], "torch_binding.cpp", verbose)
+    return obj
+
+
+def _link_binding(obj: str, verbose: bool) -> None:
+    # torch's libraries are already loaded when the binding is imported;
+    # libxtc.so is found next to it
+    import torch
+    tmp = BINDING + ".tmp%d" % os.getpid()
+    _run(["g++", "-shared", "-o", tmp, obj, "-L" + HERE, "-l:libxtc.so", "-Wl,-rpath,$ORIGIN",
+          "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"),
+          "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], "link of _binding.so", verbose)
+    os.replace(tmp, BINDING)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
-    with ThreadPoolExecutor(min(len(SOURCES), os.cpu_count() or 1)) as ex:
+    with ThreadPoolExecutor(min(len(SOURCES) + 1, os.cpu_count() or 1)) as ex:
+        binding = ex.submit(_compile_binding, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+        binding_obj = binding.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
     if verbose:
@@ -51,6 +89,7 @@ def build(verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s%s" % (r.stdout, r.stderr))
     os.replace(tmp, LIB)
+    _link_binding(binding_obj, verbose)
     return LIB
 
 
