@@ -204,7 +204,7 @@ gemm_bf16_kernel(GemmArgs p) {
 // or >= K, columns >= N or k >= K) are fetched through a buffer offset past
 // the end of the buffer, which the hardware returns as zero: this variant
 // needs K and N to be multiples of 8 and 16-byte aligned rows, and otherwise
-// the register-staged kernel above runs.
+// the kernel for rows at any 2-byte boundary below runs.
 
 // A rows hold CA = BK/8 chunks of 16 bytes; chunk c of row m sits at slot
 // c ^ swz_a(m), and an A fragment (16 bytes per lane) is one ds_read_b128.
@@ -738,6 +738,248 @@ hipError_t launch_bf16_dma(const GemmArgs &a, hipStream_t s) {
         dim3(tiles), dim3(G::NT), kargs, 0, s);
 }
 
+// ---------------------------------------------------------------------------
+// Direct-to-LDS kernel for rows at any 2-byte boundary (odd row strides or
+// bases).  Copies straight into LDS move whole dwords, so a row that starts in
+// the middle of one lands one element late.  Fixing that on the way, through
+// registers (two 16-byte loads, four lane shuffles and 15 selects and shifts
+// per chunk), ran 2047x3001x1999 at 275 TFLOP/s (89.4 us); here both operands
+// are copied as they lie, from the dword that holds their first element, and
+// the shift is undone where it costs least (55.0 us; 1531x1021x2047 with 64-row
+// tiles: 78.0 -> 24.0):
+//  - A rows: a lane's row has one parity for the whole reduction; its 16
+//    elements of a 32-k step are read with the dword after them and shifted
+//    by v_alignbyte.  Rows hold a ninth 16-byte chunk per 64 k for that
+//    dword; the 144-byte rows keep the fragment reads free of bank conflicts
+//    without a swizzle (144/16 is odd);
+//  - B rows: with an odd row stride the even and the odd k lie one column
+//    apart.  The reduction keeps them apart instead: each instruction takes
+//    either 16 even or 16 odd k (the fragments of a 32-k step are split by
+//    parity with v_perm, the transpose reads step over every second row) and
+//    has accumulators of its own.  The two sums of an element, one column
+//    apart where their parities differ, meet at the end through LDS.  The
+//    column that the shift costs is the tile's: 126 columns of output per
+//    128 stored.
+// Twice the accumulators of the aligned kernel, the same instructions per
+// FLOP.  Two LDS slots; barriers on both sides of a stage's reads, hidden by
+// the CU's second workgroup.
+template <int BM, int WM>
+struct Bf16OddCfg {
+    static constexpr int BN = 128, WN = 64, BK = 64, MI = 32, NOUT = BN - 2;
+    static constexpr int NWN = BN / WN, NWAVES = (BM / WM) * NWN, NT = NWAVES * 64;
+    static constexpr int TM = WM / MI, TN = WN / MI;
+    static constexpr int RA = BK * 2 + 16, RB = BN * 2;             // LDS row bytes
+    static constexpr int NA = (BM * RA / 1024 + NWAVES - 1) / NWAVES, NBC = BK * RB / 1024 / NWAVES;
+    static constexpr int A_BYTES = NA * NWAVES * 1024, B_BYTES = BK * RB;
+    static constexpr int STAGE_BYTES = A_BYTES + B_BYTES, LOADS = NA + NBC;
+    static constexpr int LDS_BYTES = 2 * STAGE_BYTES > BM * BN * 4 ? 2 * STAGE_BYTES : BM * BN * 4;
+    static_assert(BM * RA % 1024 == 0 && NBC * NWAVES * 1024 == B_BYTES, "whole copy blocks");
+};
+
+template <int BM, int WM>
+__global__ void __launch_bounds__((BM / WM) * 128)
+gemm_bf16_odd_kernel(GemmArgs p) {
+    typedef Bf16OddCfg<BM, WM> G;
+    typedef Bf16Mfma<32> MF;
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int TM = G::TM, TN = G::TN, BK = G::BK;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[G::LDS_BYTES];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / G::NWN, wn = wave % G::NWN;
+    const int l32 = lane & 31, lgrp = lane >> 5;
+    const int M = p.M, N = p.N, K = p.K, lda = p.lda, ldb = p.ldb;
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + G::NOUT - 1) / G::NOUT;
+    int tm, tn;
+    tile_coords(blockIdx.x, gridDim.x, tiles_m, tiles_n, p.raster, p.xcd_remap, tm, tn);
+    const int m0 = tm * BM, n0 = tn * G::NOUT;   // n0 is even
+
+    // resources from the dword that holds the first element to the one that
+    // holds the last
+    const unsigned long long abase = reinterpret_cast<unsigned long long>(p.A);
+    const unsigned long long bbase = reinterpret_cast<unsigned long long>(p.B);
+    const int amis = (int)(abase & 2), bmis = (int)(bbase & 2);
+    const i32x4 ra = make_rsrc(reinterpret_cast<const void *>(abase - amis),
+                               (amis + ((M - 1) * lda + K) * 2 + 3) & ~3);
+    const i32x4 rb = make_rsrc(reinterpret_cast<const void *>(bbase - bmis),
+                               K > 0 ? (bmis + ((K - 1) * ldb + N) * 2 + 3) & ~3 : 0);
+    const unsigned smem_base = lds_address(smem);
+
+    // copies: A unit v is row v / 9, chunk v % 9; B unit v is row v / 16,
+    // LDS slot v % 16, holding chunk slot ^ swz(row)
+    int aoff[G::NA], ak[G::NA];
+#pragma unroll
+    for (int q = 0; q < G::NA; ++q) {
+        const int v = (wave * G::NA + q) * 64 + lane, row = v / 9, c = v - row * 9;
+        ak[q] = 8 * c - 1;                        // first k the chunk can hold, less than K if any does
+        aoff[q] = row < BM && m0 + row < M ? ((amis + (m0 + row) * lda * 2) & ~3) + 16 * c : kOOB;
+    }
+    int brow[G::NBC], bcol[G::NBC];
+#pragma unroll
+    for (int q = 0; q < G::NBC; ++q) {
+        const int v = (wave * G::NBC + q) * 64 + lane;
+        brow[q] = v >> 4;
+        bcol[q] = bmis + (n0 + 8 * ((v & 15) ^ swz_b<32>(brow[q] >> 1))) * 2;
+    }
+    auto fire = [&](int kt, int st) __attribute__((always_inline)) {
+        const unsigned base = smem_base + st * G::STAGE_BYTES;
+        const int k0 = kt * BK;
+#pragma unroll
+        for (int q = 0; q < G::NA; ++q)
+            dma16(ra, base + (wave * G::NA + q) * 1024, aoff[q] != kOOB && k0 + ak[q] < K ? aoff[q] + k0 * 2 : kOOB);
+#pragma unroll
+        for (int q = 0; q < G::NBC; ++q) {
+            const int k = k0 + brow[q];
+            // the dword of the chunk's first element; a chunk past column N
+            // may read the next row (columns that are not stored)
+            dma16(rb, base + G::A_BYTES + (wave * G::NBC + q) * 1024,
+                  k < K ? (k * ldb * 2 + bcol[q]) & ~3 : kOOB);
+        }
+    };
+
+    // fragment addresses
+    int a_base[TM];
+    unsigned ash[TM];                             // 2: the row starts in the middle of a dword
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int row = wm * WM + i * 32 + l32;
+        a_base[i] = row * G::RA + 32 * lgrp;
+        ash[i] = (unsigned)(amis + (m0 + row) * lda * 2) & 2;
+    }
+    const int rsub = (lane & 15) >> 2;
+    int b_base[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int col = wn * G::WN + j * 32 + (l32 & ~15) + 4 * (lane & 3);
+        b_base[j] = G::A_BYTES + (16 * lgrp + 2 * rsub) * G::RB + (((col >> 3) ^ swz_b<32>(rsub)) << 4) + 8 * (lane & 1);
+    }
+
+    typename MF::acc_t acc[2][TM][TN];            // even k, odd k
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < MF::NACC; ++r) acc[o][i][j][r] = 0.f;
+
+    u32x4 aw[2][TM][2];
+    unsigned ax[2][TM];
+    u16x8 bf[2][2][TN];
+    auto frags = [&](int st, int ds, int fb) __attribute__((always_inline)) {
+        const unsigned char *S = smem + st * G::STAGE_BYTES;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const unsigned char *q = S + a_base[i] + ds * 64;
+            aw[fb][i][0] = *reinterpret_cast<const u32x4 *>(q);
+            aw[fb][i][1] = *reinterpret_cast<const u32x4 *>(q + 16);
+            ax[fb][i] = *reinterpret_cast<const unsigned *>(q + 32);
+        }
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const unsigned char *q = S + b_base[j] + (32 * ds + o) * G::RB;
+                const u16x4 lo = ds_read_tr16(reinterpret_cast<const unsigned short *>(q));
+                const u16x4 hi = ds_read_tr16(reinterpret_cast<const unsigned short *>(q + 8 * G::RB));
+                bf[fb][o][j] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            }
+    };
+    auto mfmas = [&](int fb, int left) __attribute__((always_inline)) {
+        // left: k values left at this lane's 16
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            unsigned x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const unsigned lo = aw[fb][i][e >> 2][e & 3];
+                const unsigned hi = e < 7 ? aw[fb][i][(e + 1) >> 2][(e + 1) & 3] : ax[fb][i];
+                x[e] = __builtin_amdgcn_alignbyte(hi, lo, ash[i]);
+            }
+            if (__builtin_expect(left < 16, 0)) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    x[e] &= (2 * e < left ? 0xffffu : 0u) | (2 * e + 1 < left ? 0xffff0000u : 0u);
+            }
+            u32x4 ev, od;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                ev[q] = __builtin_amdgcn_perm(x[2 * q + 1], x[2 * q], 0x05040100u);
+                od[q] = __builtin_amdgcn_perm(x[2 * q + 1], x[2 * q], 0x07060302u);
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[0][i][j] = MF::mma(__builtin_bit_cast(u16x8, ev), bf[fb][0][j], acc[0][i][j]);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[1][i][j] = MF::mma(__builtin_bit_cast(u16x8, od), bf[fb][1][j], acc[1][i][j]);
+        }
+    };
+
+    const int KT = (K + BK - 1) / BK;
+    fire(0, 0);
+    fire(1, 1);
+    for (int kt = 0; kt < KT; ++kt) {
+        const int st = kt & 1;
+        wait_vmcnt<G::LOADS>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const int left = K - kt * BK - 16 * lgrp;
+        frags(st, 0, 0);
+        frags(st, 1, 1);
+        mfmas(0, left);
+        mfmas(1, left - 32);
+        // every read of the slot has fed an instruction of this wave; after
+        // the barrier that holds for all waves
+        asm volatile("" ::: "memory");
+        wait_vmcnt_and_lds<G::LOADS>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        fire(kt + 2, st);
+    }
+    wait_vmcnt<0>();  // no copy may still be writing LDS when it is reused or the workgroup ends
+    __syncthreads();
+
+    // position c of an even (odd) k row holds column n0 + c - pe (po)
+    const int pe = (bmis >> 1) & 1, po = ((bmis >> 1) + ldb) & 1;
+    float *red = reinterpret_cast<float *>(smem);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < MF::NACC; ++r)
+                red[(wm * WM + i * 32 + MF::row(lane, r)) * G::BN + wn * G::WN + j * 32 + l32] = acc[1][i][j][r];
+    __syncthreads();
+    float *__restrict__ C = p.C;
+    const int ldc = p.ldc;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int c = wn * G::WN + j * 32 + l32 - pe, col = n0 + c;
+            const bool ok = c >= 0 && c < G::NOUT && col < N;
+#pragma unroll
+            for (int r = 0; r < MF::NACC; ++r) {
+                const int lr = wm * WM + i * 32 + MF::row(lane, r), row = m0 + lr;
+                if (ok && row < M) {
+                    const float v = acc[0][i][j][r] + red[lr * G::BN + c + po];
+                    C[row * ldc + col] = (p.relu && v < 0.f) ? 0.f : v;
+                }
+            }
+        }
+}
+
+template <int BM, int WM>
+hipError_t launch_bf16_odd(const GemmArgs &a, hipStream_t s) {
+    typedef Bf16OddCfg<BM, WM> G;
+    const unsigned tiles = (unsigned)(((a.M + BM - 1) / BM) * ((a.N + G::NOUT - 1) / G::NOUT));
+    GemmArgs args = a;
+    void *kargs[] = {&args};
+    return hipLaunchKernel(reinterpret_cast<const void *>(&gemm_bf16_odd_kernel<BM, WM>), dim3(tiles), dim3(G::NT),
+                           kargs, 0, s);
+}
+
 template <int BM, int BN, int BK, int WM, int WN, int MI, int PAD, bool VEC>
 hipError_t launch_bf16(const GemmArgs &a, hipStream_t s) {
     typedef GemmBf16Cfg<BM, BN, BK, WM, WN, MI, PAD, VEC> G;
@@ -759,14 +1001,14 @@ hipError_t launch_bf16(const GemmArgs &a, hipStream_t s) {
     }
 
 // Direct-to-LDS ring (lds_pad = -1: swizzled, unpadded LDS rows), b128 A
-// reads, MFMA / LDS-read interleaving.  The fallback for unaligned or
-// non-16-byte-granular operands is the register-staged kernel with the same
-// tiles.
+// reads, MFMA / LDS-read interleaving.  Unaligned or non-16-byte-granular
+// operands run the kernel for rows at any 2-byte boundary, with 128- or
+// 64-row tiles.
 #define XTC_BF16_DMA_INSTANCE(BM, BN, BK, WM, WN, MI, STAGES)                                 \
     GemmInstance {                                                                            \
         make_sched(BM, BN, BK, WM, WN, MI, MI, (MI == 32 ? 16 : 32), STAGES, -1, 0),           \
             &launch_bf16_dma<BM, BN, BK, WM, WN, MI, STAGES>,                                 \
-            &launch_bf16<BM, BN, BK, WM, WN, MI, 8, false>, kWholeChunks,                     \
+            &launch_bf16_odd<(BM >= 128 ? 128 : 64), (BM >= 128 ? 64 : 32)>, kWholeChunks,    \
             &occupancy_of<&gemm_bf16_dma_kernel<BM, BN, BK, WM, WN, MI, STAGES>,              \
                           (BM / WM) * (BN / WN) * 64, 0>                                      \
     }

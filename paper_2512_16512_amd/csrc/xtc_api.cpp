@@ -299,8 +299,7 @@ xtc_status xtc_default_schedule(xtc_op op, xtc_dtype dt, int64_t M, int64_t N, i
         // 5.4; 512^3: 6.7, 4.5; 512x1024x768: 8.6, 6.8; past it the staged
         // tiles win: 1024^3 10.7 against 13.1) or one operand is narrow
         // (10000x30x2000: 70.7, 13.0; 32768x16x4096: 48.2, 46.4); else the
-        // direct-to-LDS tiles from 256x256 down to 64x128 (half a tile per
-        // CU), then the register-staged 64x64 tiles.
+        // direct-to-LDS tiles from 256x256 down to 64x128.
         if (tiles(64, 32) <= cus || (M < N ? M : N) <= 32) {
             // Of the three, the tile with the least work on the fullest CU: a
             // k-step of 16*TM rows costs TM row loads and 8 column loads,
@@ -314,10 +313,8 @@ xtc_status xtc_default_schedule(xtc_op op, xtc_dtype dt, int64_t M, int64_t N, i
             *out = make_sched(256, 256, 32, 128, 64, 32, 32, 16, 4, -1, 0);
         else if (tiles(128, 128) >= cus)
             *out = make_sched(128, 128, 32, 64, 64, 32, 32, 16, 4, -1, 0);
-        else if (tiles(64, 128) >= cus / 2)
-            *out = make_sched(64, 128, 64, 32, 64, 32, 32, 16, 2, -1, 0);
         else
-            *out = make_sched(64, 64, 64, 32, 32, 32, 32, 16, 2, 8, 0);
+            *out = make_sched(64, 128, 64, 32, 64, 32, 32, 16, 2, -1, 0);
     }
     const int64_t t = tiles(out->block_m, out->block_n);
     out->raster = mid ? 4 : (t >= 64 ? 8 : 0);

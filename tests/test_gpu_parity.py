@@ -235,11 +235,12 @@ def test_conv_small_int_exact_every_instance(x, shape):
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (16, 32, 32), (17, 33, 33), (5, 31, 7), (64, 32, 128), (65, 66, 390),
-                                   (3, 300, 1030), (130, 2, 96)])
+                                   (3, 300, 1030), (130, 2, 96), (129, 127, 63), (127, 253, 129), (33, 126, 64)])
 @pytest.mark.parametrize("oa,ob,pa,pb", [(0, 0, 0, 0), (2, 4, 2, 6), (1, 0, 0, 1), (3, 7, 1, 3)])
-def test_bf16_register_fed_split_edges(x, M, N, K, oa, ob, pa, pb):
-    """The bf16 register-fed reduction-split tiles at the edges of their tiles
-    and k-steps, with operands ``oa``/``ob`` elements past a 16-byte boundary
+def test_bf16_row_alignment_and_tile_edges(x, M, N, K, oa, ob, pa, pb):
+    """The bf16 register-fed reduction-split tiles and the direct-to-LDS ones
+    (their form for rows at any 2-byte boundary: 126 columns a tile, 64 k a
+    step) at the edges of their tiles and k-steps, with operands ``oa``/``ob`` elements past a 16-byte boundary
     and rows padded by ``pa``/``pb``: 4-byte aligned rows and rows at any
     2-byte boundary.  Infinities around and between the rows must not reach
     the result.  Bit-exact (small integers)."""
@@ -255,9 +256,9 @@ def test_bf16_register_fed_split_edges(x, M, N, K, oa, ob, pa, pb):
         return to_dev(flat)
 
     Ad, Bd = place(A, pa, oa), place(B, pb, ob)
-    for s in [s for s in x.xtc_sched_list(x.XTC_OP_MATMUL, x.XTC_BF16) if s.k_split > 1] + [None]:
+    for s in [s for s in x.xtc_sched_list(x.XTC_OP_MATMUL, x.XTC_BF16) if s.k_split > 1 or s.lds_pad < 0] + [None]:
         Cd = torch.full((M, N), 7.0, dtype=torch.float32, device="cuda")
-        say("bf16 split", (M, N, K), (oa, ob, pa, pb), s)
+        say("bf16 edges", (M, N, K), (oa, ob, pa, pb), s)
         st = x.xtc_matmul(M, N, K, Ad.data_ptr() + 2 * oa, K + pa, Bd.data_ptr() + 2 * ob, N + pb, Cd.data_ptr(), N,
                           x.XTC_BF16, s, torch.cuda.current_stream().cuda_stream)
         assert st == 0, x.xtc_status_str(st)
