@@ -113,7 +113,13 @@ typedef enum {
  *                  chosen per launch so that workgroups split evenly;
  *                  block_n = 416 is the same with two such pixel halves
  *                  per workgroup (8 waves) sharing one input patch;
- *                  other shapes run the tap-major kernel;
+ *                  other shapes run the tap-major kernel.  lds_pad 0 (the
+ *                  patch kernels: 3x3 layers of any stride, padding, row
+ *                  length and batch) needs C % 8 == 0 and a patch that fits
+ *                  in LDS; large layers of the 56-pixel class run the
+ *                  block_n = 208 kernel, others the tap-major kernel.  Groups
+ *                  of waves may share a tile, each reducing every second
+ *                  (block_m 64, lds_stages 1) or fourth (block_m 16) stage;
  *                  bf16: chunks of 16, k = ((ic/16)*R*S + kh*S + kw)*16 +
  *                  ic%16.  lds_pad -1 (the kernel for rows of about 56
  *                  pixels) needs C % 16 == 0, even W, pad_w <= 2,

@@ -15,6 +15,7 @@
 // transpose reads per B fragment from the pixel-contiguous B tile.
 #include <algorithm>
 
+#include "fast_div.h"
 #include "lds_dma.h"
 #include "mfma_bf16.h"
 #include "tile_map.h"
@@ -521,23 +522,6 @@ struct Cfg {
 };
 constexpr int kMaxLds = 160 * 1024;
 }  // namespace patch_bf16
-
-// Division of n < 2^31 by a launch constant d: (n * mul) >> (32 + shift) with
-// mul = ceil(2^(31 + l) / d), l = ceil(log2 d): the rounding of mul adds less
-// than n / 2^(31 + l) < 1 / d.
-struct FastDiv {
-    unsigned mul;
-    int shift;       // l - 1; -1: d is 1
-    int d;
-};
-inline FastDiv fast_div(int d) {
-    int l = 0;
-    while ((1ll << l) < d) ++l;
-    return FastDiv{(unsigned)(((1ull << (31 + l)) + d - 1) / d), l - 1, d};
-}
-__device__ __forceinline__ int div_by(int n, const FastDiv &f) {
-    return f.shift < 0 ? n : (int)(__umulhi((unsigned)n, f.mul) >> f.shift);
-}
 
 // Launch geometry of the patch kernel (computed on the host).
 struct PatchArgs {

@@ -18,6 +18,9 @@
 // 0 <= ih0(q) + kh < H and 0 <= iw0(q) + kw < W, else zero.
 #include <type_traits>
 
+#include <algorithm>
+
+#include "fast_div.h"
 #include "lds_dma.h"
 #include "mfma_f32.h"
 #include "tile_map.h"
@@ -1719,6 +1722,272 @@ hipError_t launch_conv_f32_smallm(const ConvArgs &a, hipStream_t s) {
                            dim3(tiles), dim3(smallm::NT), kargs, dyn, s);
 }
 
+// ---------------------------------------------------------------------------
+// Patch kernel (k_order = 2, lds_pad = 0) for 3x3 convolutions of any stride,
+// padding, row length and batch with a channel count that is a multiple of 8.
+// The tap-major kernel gathers every input value once per tap and its tiles
+// are few and large for a small batch or image (1x128x28x28 -> 128: 112 us,
+// 14 workgroups of 512 KB of gathers each; 32 of them: 116.7 us, 63
+// TFLOP/s).  Here, as in the halo kernels, a stage of 8 channels copies its
+// input patch once for all nine taps:
+//  - a workgroup computes BM = 16*NWM output channels x BN = 16*NB consecutive
+//    pixels of the flattened (image, output row, output column) order with
+//    16x16x4 instructions, wave w of a group 16 channels and all pixels.
+//    Padded input rows are numbered through the batch (PH per image), so a
+//    tile that crosses into the next image still reads one run of them;
+//  - the patch holds, per channel, the tile's padded rows at WPA columns, so
+//    a pixel's value at tap (kh, kw) lies kh*WPA + kw past its own.  It is
+//    copied by dwords (32x128x28x28 -> 128 in 77.4 us, 61% of the matrix peak,
+//    against 116; in 16-byte units without the padding, and a select per
+//    value read instead, it took 96.5): a lane owns one cell of each 64-cell block for the
+//    whole reduction (an out-of-range offset, read as zero, for padding) and
+//    the channel is a scalar offset.  Channel planes are 16 modulo 32 dwords
+//    apart: the two planes a read phase touches use different banks;
+//  - the weights of a stage are 72 consecutive floats per output channel,
+//    copied as they are in 16-byte units (19 per row, the last empty, against
+//    bank conflicts) and read by dwords: the instructions are 32 clocks each,
+//    so the reads, 1 + NB per NB instructions, hide behind them;
+//  - KS groups of waves share a tile, group g reducing the stages g, g + KS,
+//    ... in LDS areas of its own; their sums are added in group order.
+// Two areas per group; the copies of a stage fly while the previous one is
+// computed.
+namespace patch_f32 {
+constexpr int CC = 8, NTAP = 9;
+constexpr int W_UNITS = CC * NTAP / 4 + 1;       // 16-byte units per weight row
+template <int NWM_, int NB_, int KS_>
+struct Cfg {
+    static constexpr int NWM = NWM_, NB = NB_, KS = KS_;
+    static constexpr int BM = 16 * NWM, BN = 16 * NB, NT = 64 * NWM * KS;
+    static constexpr int NBW = (BM * W_UNITS + 64 * NWM - 1) / (64 * NWM);    // weight copies per wave
+    static constexpr int W_BYTES = NBW * NWM * 1024;
+    static constexpr int RED_BYTES = (KS - 1) * NWM * NB * 1024;              // partial sums
+};
+constexpr int kMaxLds = 160 * 1024;
+}  // namespace patch_f32
+
+struct PatchF32Args {
+    ConvArgs c;
+    FastDiv by_ohw, by_ow, by_ph, by_wpa;
+    int PH;      // padded input rows an image's outputs read
+    int WPA;     // columns of a patch row
+    int nblk;    // 64-cell blocks per channel
+    int plane;   // dwords between channel planes
+};
+
+// NPB: most blocks per channel.
+template <typename CFG, int NPB>
+__global__ void __launch_bounds__(64 * CFG::NWM * CFG::KS)
+conv2d_f32_patch_kernel(PatchF32Args pa) {
+    using namespace patch_f32;
+    typedef F32Mfma<16> MF;
+    constexpr int NWM = CFG::NWM, NB = CFG::NB, KS = CFG::KS, BM = CFG::BM, BN = CFG::BN, NBW = CFG::NBW;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char fsm[];
+
+    const ConvArgs &p = pa.c;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kg = wv / NWM, wave = wv % NWM;      // K group, wave inside it
+    const int l16 = lane & 15, lgrp = lane >> 4;
+    const int C = p.C, H = p.H, Wd = p.W, OC = p.OC, OW = p.OW, OHW = p.OH * p.OW;
+    const int N = p.Nb * OHW, PH = pa.PH, WPA = pa.WPA;
+    const int tiles_m = (OC + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+    int tm, tn;
+    tile_coords(blockIdx.x, gridDim.x, tiles_m, tiles_n, p.raster, p.xcd_remap, tm, tn);
+    const int m0 = tm * BM, q0 = tn * BN;
+    const int img0 = div_by(q0, pa.by_ohw), oh0 = div_by(q0 - img0 * OHW, pa.by_ow);
+    const int q1 = min(q0 + BN, N) - 1;
+    const int img1 = div_by(q1, pa.by_ohw), oh1 = div_by(q1 - img1 * OHW, pa.by_ow);
+    const int prow0 = oh0 * p.sh;                  // first padded row, counted from img0
+    const int nrows = (img1 - img0) * PH + oh1 * p.sh + 3 - prow0;
+
+    const int plane_b = __builtin_amdgcn_readfirstlane(H * Wd * 4);   // bytes per input channel
+    const int slot_bytes = CFG::W_BYTES + CC * pa.plane * 4;
+    unsigned char *const area = fsm + kg * 2 * slot_bytes;            // [2][weights | patch]
+    const unsigned area_lds = __builtin_amdgcn_readfirstlane(lds_address(area));
+
+    // this lane's cell of each block of the patch
+    int xoff[NPB];
+#pragma unroll
+    for (int q = 0; q < NPB; ++q) {
+        const int i = q * 64 + lane, r = div_by(i, pa.by_wpa), iw = i - r * WPA - p.pw;
+        const int pr = prow0 + r, di = div_by(pr, pa.by_ph), ih = pr - di * PH - p.ph;
+        const bool ok = r < nrows && ih >= 0 && ih < H && iw >= 0 && iw < Wd;
+        xoff[q] = ok ? (((img0 + di) * C * H + ih) * Wd + iw) * 4 : kOOB;
+    }
+    int woff[NBW];
+#pragma unroll
+    for (int q = 0; q < NBW; ++q) {
+        const int v = (wave * NBW + q) * 64 + lane, oc = v / W_UNITS, u = v - oc * W_UNITS;
+        woff[q] = oc < BM && m0 + oc < OC && u + 1 < W_UNITS ? (m0 + oc) * C * NTAP * 4 + u * 16 : kOOB;
+    }
+    const i32x4 rx = make_rsrc(p.X, p.Nb * C * plane_b);
+    const i32x4 rw = make_rsrc(p.Wt, OC * C * NTAP * 4);
+    auto issue = [&](int ks, int s) __attribute__((always_inline)) {   // stage ks (zeros past the last) into slot s
+        const int c0 = ks * CC;
+        const bool live = c0 < C;
+        const int wso = live ? c0 * NTAP * 4 : 0, xso = live ? c0 * plane_b : 0;
+        const unsigned base = area_lds + s * slot_bytes;
+#pragma unroll
+        for (int q = 0; q < NBW; ++q) dma16_so(rw, base + (wave * NBW + q) * 1024, live ? woff[q] : kOOB, wso);
+        for (int ch = wave; ch < CC; ch += NWM) {
+            const unsigned pl = base + CFG::W_BYTES + ch * pa.plane * 4;
+#pragma unroll
+            for (int q = 0; q < NPB; ++q)
+                if (q < pa.nblk) dma4_so(rx, pl + q * 256, live ? xoff[q] : kOOB, xso + ch * plane_b);
+        }
+    };
+
+    // fragment bases (dwords): weights of output channel 16*wave + l16 and
+    // channel lgrp of the stage; the cell of this lane's pixel, channel lgrp
+    const int a_base = (wave * 16 + l16) * (W_UNITS * 4) + lgrp * NTAP;
+    int b_base[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const int q = q0 + j * 16 + l16;
+        int cell = 0;
+        if (q < N) {
+            const int img = div_by(q, pa.by_ohw), pix = q - img * OHW;
+            const int oh = div_by(pix, pa.by_ow), ow = pix - oh * OW;
+            cell = ((img - img0) * PH + oh * p.sh - prow0) * WPA + ow * p.sw;
+        }
+        b_base[j] = CFG::W_BYTES / 4 + lgrp * pa.plane + cell;
+    }
+
+    typename MF::acc_t acc[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[j][r] = 0.f;
+
+    auto compute = [&](int s) __attribute__((always_inline)) {
+        const float *S = reinterpret_cast<const float *>(area + s * slot_bytes);
+        float a[2], b[2][NB];
+        // step: tap, then the lower or upper four channels
+        auto frags = [&](int step, int fb) __attribute__((always_inline)) {
+            const int tap = step >> 1, h = step & 1, kh = tap / 3, kw = tap - 3 * kh;
+            a[fb] = S[a_base + 4 * h * NTAP + tap];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) b[fb][j] = S[b_base[j] + 4 * h * pa.plane + kh * WPA + kw];
+        };
+        frags(0, 0);
+#pragma unroll
+        for (int step = 0; step < 2 * NTAP; ++step) {
+            if (step + 1 < 2 * NTAP) frags(step + 1, (step + 1) & 1);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[j] = MF::mma(a[step & 1], b[step & 1][j], acc[j]);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                         // MFMA
+                if (step + 1 < 2 * NTAP) {                                                                 // DS reads
+                    if (j == 0) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                    else __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // Every group runs the same number of trips, so the barriers match.
+    const int trips = (C / CC + KS - 1) / KS;
+    issue(kg, 0);
+    wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    for (int it = 0; it < trips; ++it) {
+        // the other slot's reads ended before the barrier
+        if (it + 1 < trips) issue(kg + (it + 1) * KS, (it + 1) & 1);
+        compute(it & 1);
+        asm volatile("" ::: "memory");
+        wait_vmcnt_and_lds<0>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
+
+    if constexpr (KS > 1) {
+        // groups 1 .. KS-1 leave their sums in LDS, group 0 adds them in group order
+        float *red = reinterpret_cast<float *>(fsm);
+        if (kg > 0) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) red[((((kg - 1) * NWM + wave) * NB + j) * 4 + r) * 64 + lane] = acc[j][r];
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int g = 1; g < KS; ++g)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[j][r] += red[((((g - 1) * NWM + wave) * NB + j) * 4 + r) * 64 + lane];
+    }
+
+    // rows of the accumulators: output channel 4*lgrp + r.  Pixels and
+    // channels outside Y go to an out-of-range offset and are dropped.
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.Y, 0, N * OC * 4, 0x00020000);
+    const int oc = m0 + wave * 16 + 4 * lgrp;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const int q = q0 + j * 16 + l16, img = div_by(q, pa.by_ohw), pix = q - img * OHW;
+        const int off = q < N ? ((img * OC + oc) * OHW + pix) * 4 : kOOB;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float v = (p.relu && acc[j][r] < 0.f) ? 0.f : acc[j][r];
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), ry, oc + r < OC ? off : kOOB,
+                                                  r * OHW * 4, 0);
+        }
+    }
+}
+
+template <typename CFG, int NPB>
+bool patch_f32_geom(const ConvArgs &a, PatchF32Args *pa, size_t *lds) {
+    using namespace patch_f32;
+    if (a.R != 3 || a.S != 3 || a.C % CC != 0 || a.sh > 64) return false;
+    const long long OHW = (long long)a.OH * a.OW, N = a.Nb * OHW;
+    // output rows a tile can touch, and image borders among them (between
+    // two images the padded rows advance by 3 instead of stride_h)
+    const long long span = std::min<long long>((CFG::BN - 1 + a.OW - 1) / a.OW + 1, (long long)a.Nb * a.OH);
+    const long long cross = std::min<long long>((std::min<long long>(CFG::BN, N) - 1 + OHW - 1) / OHW, a.Nb - 1);
+    const long long wpa = (long long)(a.OW - 1) * a.sw + 3;
+    if (wpa > 8192) return false;
+    const long long rows = (span - 1) * a.sh + 3 + cross * std::max(3 - a.sh, 0);
+    const long long nblk = (rows * wpa + 63) / 64;
+    if (nblk > NPB) return false;
+    const long long plane = (nblk * 64 + 31) / 32 * 32 + 16;
+    const long long bytes = std::max<long long>((long long)CFG::KS * 2 * (CFG::W_BYTES + CC * plane * 4), CFG::RED_BYTES);
+    if (bytes > kMaxLds) return false;
+    pa->c = a;
+    pa->PH = (a.OH - 1) * a.sh + 3;
+    pa->WPA = (int)wpa;
+    pa->nblk = (int)nblk;
+    pa->plane = (int)plane;
+    pa->by_ohw = fast_div((int)OHW);
+    pa->by_ow = fast_div(a.OW);
+    pa->by_ph = fast_div(pa->PH);
+    pa->by_wpa = fast_div((int)wpa);
+    *lds = (size_t)bytes;
+    return true;
+}
+
+// Tries the patch kernel with tile CFG; false if the shape is outside it.
+template <typename CFG>
+bool try_patch_f32(const ConvArgs &a, hipStream_t s, hipError_t *err) {
+    PatchF32Args pa;
+    size_t lds;
+    const void *fn;
+    if (patch_f32_geom<CFG, 10>(a, &pa, &lds))
+        fn = reinterpret_cast<const void *>(&conv2d_f32_patch_kernel<CFG, 10>);
+    else if (patch_f32_geom<CFG, 24>(a, &pa, &lds))
+        fn = reinterpret_cast<const void *>(&conv2d_f32_patch_kernel<CFG, 24>);
+    else
+        return false;
+    const int N = a.Nb * a.OH * a.OW;
+    const unsigned tiles = (unsigned)(((a.OC + CFG::BM - 1) / CFG::BM) * ((N + CFG::BN - 1) / CFG::BN));
+    void *kargs[] = {&pa};
+    *err = hipLaunchKernel(fn, dim3(tiles), dim3(CFG::NT), kargs, lds, s);
+    return true;
+}
+
 // Shapes the halo kernel covers; anything else runs the tap-major kernel
 // with the same 64x256 tiles.
 inline bool halo_eligible(const ConvArgs &a) {
@@ -1763,6 +2032,8 @@ inline int halo16_tile_px(const ConvArgs &a) {
 template <int STAGES, int NH>
 hipError_t launch_conv_f32_halo16(const ConvArgs &a, hipStream_t s) {
     const int pt = halo16_tile_px<NH>(a);
+    if constexpr (NH == 2)   // one pixel half per workgroup before the unbalanced tiles (57-wide rows: 86.4 -> 67.4 us)
+        if (pt == 0 && halo16_tile_px<1>(a) > 0) return launch_conv_f32_halo16<STAGES, 1>(a, s);
     if (pt == 0) return launch_conv_f32_halo<STAGES>(a, s);
     ConvArgs args = a;
     args.tile_px = pt;
@@ -1772,6 +2043,31 @@ hipError_t launch_conv_f32_halo16(const ConvArgs &a, hipStream_t s) {
     void *kargs[] = {&args};
     return hipLaunchKernel(reinterpret_cast<const void *>(&conv2d_f32_halo16_kernel<STAGES, NH>),
                            dim3(tiles), dim3(halo16::Cfg<NH>::NT), kargs, 0, s);
+}
+
+typedef patch_f32::Cfg<4, 13, 1> PatchF32L;
+typedef patch_f32::Cfg<4, 7, 1> PatchF32M;
+typedef patch_f32::Cfg<4, 4, 2> PatchF32M2;
+typedef patch_f32::Cfg<4, 2, 2> PatchF32N;
+typedef patch_f32::Cfg<1, 2, 4> PatchF32T;
+
+// The patch instances: the balanced halo kernel where the shape is in its
+// class and gives it three quarters of the CUs (8x64x57x57 -> 128: 40.4 us
+// against 43.3), 208-pixel tiles in place of 112-pixel ones past two of those
+// per CU (32x64x57x57 -> 128: 142.7 against 163.0), and outside the patch
+// kernel's class the tap-major kernel.
+template <typename CFG>
+hipError_t launch_conv_f32_patch(const ConvArgs &a, hipStream_t s) {
+    const long long N = (long long)a.Nb * a.OH * a.OW;
+    auto tiles = [&](int bn) { return (a.OC + 63) / 64 * ((N + bn - 1) / bn); };
+    if (tiles(208) >= 192 && halo16_tile_px<1>(a) > 0) return launch_conv_f32_halo16<2, 1>(a, s);
+    hipError_t err;
+    if (CFG::NB == 7 && tiles(112) > 512 && try_patch_f32<PatchF32L>(a, s, &err)) return err;
+    if (try_patch_f32<CFG>(a, s, &err) || try_patch_f32<PatchF32N>(a, s, &err) || try_patch_f32<PatchF32M>(a, s, &err))
+        return err;
+    if (a.OC > 64) return launch_conv_f32_tap<128, 128, 64, 64, 2, 3>(a, s);
+    if (tiles(256) < 256) return launch_conv_f32_tap<64, 64, 32, 32, 2, 4>(a, s);
+    return launch_conv_f32_tap<64, 256, 64, 64, 2, 2>(a, s);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int MI, int PAD>
@@ -1812,6 +2108,14 @@ hipError_t launch_conv_f32(const ConvArgs &a, hipStream_t s) {
                           (BM / WM) * (BN / WN) * 64, 0>                                      \
     }
 
+// Patch kernels (lds_pad = 0; lds_stages 1: the reduction split over two
+// groups of waves, four for 16 output channels).
+#define XTC_CONV_F32_PATCH_INSTANCE(CFG, STAGES)                                              \
+    ConvInstance {                                                                            \
+        make_sched(CFG::BM, CFG::BN, 8, 16, CFG::BN, 16, 16, 4, STAGES, 0, 0, 2),              \
+            &launch_conv_f32_patch<CFG>, &occupancy_of<&conv2d_f32_patch_kernel<CFG, 10>, CFG::NT, 0> \
+    }
+
 const ConvInstance kConvInstances[] = {
     ConvInstance{make_sched(64, 208, 8, 16, 208, 16, 16, 4, 2, -1, 0, 2),  // balanced halo, 3x3 stride 1
                  &launch_conv_f32_halo16<2, 1>,
@@ -1822,6 +2126,10 @@ const ConvInstance kConvInstances[] = {
     ConvInstance{make_sched(64, 256, 8, 64, 64, 32, 32, 2, 2, -1, 0, 2),   // halo, 3x3 stride 1
                  &launch_conv_f32_halo<2>,
                  &occupancy_of<&conv2d_f32_halo_kernel<2>, halo::NT, 0>},
+    XTC_CONV_F32_PATCH_INSTANCE(PatchF32M, 2),
+    XTC_CONV_F32_PATCH_INSTANCE(PatchF32M2, 1),
+    XTC_CONV_F32_PATCH_INSTANCE(PatchF32N, 1),
+    XTC_CONV_F32_PATCH_INSTANCE(PatchF32T, 1),
     XTC_CONV_TAP_INSTANCE(64, 256, 64, 64, 2, 2),    // the halo instance's fallback
     XTC_CONV_TAP_INSTANCE(64, 128, 32, 64, 2, 3),
     XTC_CONV_TAP_INSTANCE(64, 64, 32, 32, 2, 4),

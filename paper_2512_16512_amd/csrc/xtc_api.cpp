@@ -203,6 +203,25 @@ xtc_status xtc_default_schedule(xtc_op op, xtc_dtype dt, int64_t M, int64_t N, i
             out->raster = 0;
             return XTC_OK;
         }
+        if (K % 72 == 0 && !(M <= 64 && K == 576 && tiles(64, 416) >= cus - cus / 8)) {
+            // 3x3 layers of whole 8-channel stages, but for the benchmark
+            // layer's kind: the patch kernels, with the largest tile that
+            // stays within a workgroup per CU (each of the split ones takes
+            // most of a CU's LDS), 64x112 past that (64x128 output channels x
+            // pixels at 28x28, batch 1, 8, 32: 16x32 tiles 10.1, 63.9, - us;
+            // 64x64 27.9, 29.7, 109; 64x112 50.4, 51.6, 77.9; the tap-major
+            // kernel took 112, 113, 116)
+            if (tiles(16, 32) <= cus)
+                *out = make_sched(16, 32, 8, 16, 32, 16, 16, 4, 1, 0, 0, 2);
+            else if (tiles(64, 32) <= cus)
+                *out = make_sched(64, 32, 8, 16, 32, 16, 16, 4, 1, 0, 0, 2);
+            else if (tiles(64, 64) <= cus)
+                *out = make_sched(64, 64, 8, 16, 64, 16, 16, 4, 1, 0, 0, 2);
+            else
+                *out = make_sched(64, 112, 8, 16, 112, 16, 16, 4, 2, 0, 0, 2);
+            out->raster = 0;
+            return XTC_OK;
+        }
         *out = make_sched(64, 208, 8, 16, 208, 16, 16, 4, 2, -1, 0, 2);
         // two pixel halves per workgroup (one patch and one weight copy for
         // 416 pixels) once that still gives about a workgroup per CU

@@ -911,10 +911,18 @@ def _conv_f32_gather(s: dict, k_order: int, stages: int, dims) -> LdsCost:
     return conv_f32_reg_launch(BM, BN, 32, WM, WN, 32, 4, *dims, vec=False)
 
 
+def _halo16_fits(nh, OH, OW, halo_class, C, pw) -> bool:
+    """The shape is in the balanced halo kernel's class with ``nh`` halves."""
+    if not halo_class or C % 8 or pw > 4 or OW - pw + 5 > 63:
+        return False
+    t = _cdiv(OH * OW, 208 * nh)
+    return (_cdiv(OH * OW, t) - 1 + OW - 1) // OW + 1 + 2 <= (8 if nh == 1 else 10)
+
+
 def conv_launch(dtype: str, s: dict, N, C, H, W, OC, R, S, stride, pad):
     """LDS cost of one conv launch of instance ``s``, or None when the kernel
     it runs for this shape is not modelled (the few-channel kernel's gather
-    form, when the patch does not fit; the bf16 patch kernel)."""
+    form, when the patch does not fit; the patch kernels)."""
     sh, sw = (stride, stride) if isinstance(stride, int) else stride
     ph, pw = (pad, pad) if isinstance(pad, int) else pad
     OH, OW = (H + 2 * ph - R) // sh + 1, (W + 2 * pw - S) // sw + 1
@@ -922,8 +930,12 @@ def conv_launch(dtype: str, s: dict, N, C, H, W, OC, R, S, stride, pad):
     dims = (N, C, H, W, OC, R, S, sh, sw, ph, pw)
     if dtype == "f32" and s["block_m"] == 16 and s["lds_stages"] == 0:
         return conv_f32_smallm_patch_launch(N, C, H, W, OC, R, S, sh, sw, ph, pw)
+    if dtype == "f32" and s["k_order"] == 2 and s.get("lds_pad", -1) == 0:
+        return None                                      # the patch kernels
     if dtype == "f32" and s["k_order"] == 2 and s["block_n"] in (208, 416):
         nh = 1 if s["block_n"] == 208 else 2
+        if nh == 2 and not _halo16_fits(2, OH, OW, halo_class, C, pw):
+            nh = 1                                       # one half per workgroup where two do not fit
         if halo_class and C % 8 == 0 and pw <= 4 and OW - pw + 5 <= 63:
             # the launcher's pixel tile: the fewest tiles per image of at most 208*nh
             ohw = OH * OW

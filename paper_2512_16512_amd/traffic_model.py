@@ -593,8 +593,13 @@ def conv_grid(dtype: str, s: dict, N, C, H, W, OC, R, S, stride, pad):
     if dtype == "bf16":
         tn, seg = flattened(s["block_n"])
         return bm, _cdiv(OC, bm), tn, seg, None
+    if s["k_order"] == 2 and s["lds_pad"] == 0:        # the fp32 patch kernels: not modelled
+        return None
     if s["k_order"] == 2 and s["block_n"] in (208, 416):
         nh = 1 if s["block_n"] == 208 else 2
+        if nh == 2 and halo_class:                     # one half per workgroup where two do not fit
+            pt = _cdiv(OHW, _cdiv(OHW, 416))
+            nh = 2 if (pt - 1 + OW - 1) // OW + 1 + 2 <= 10 else 1
         if halo_class and C % 8 == 0 and pw <= 4 and OW - pw + 5 <= 63:
             t = _cdiv(OHW, 208 * nh)
             pt = _cdiv(OHW, t)

@@ -297,6 +297,43 @@ def test_conv_bf16_patch_edges(x, N, C, H, W, OC, stride, pad):
             assert np.array_equal(to_host(Yd), ref), (off, s)
 
 
+@pytest.mark.parametrize("N,C,H,W,OC,stride,pad", [
+    (5, 16, 7, 7, 33, (1, 1), (1, 1)),     # several images in a tile, odd rows
+    (3, 24, 14, 14, 70, (1, 1), (1, 1)),   # an odd number of stages, OC past a tile
+    (2, 40, 28, 30, 96, (2, 2), (1, 1)),   # stride 2, tiles that cross an image
+    (1, 8, 9, 60, 65, (1, 2), (0, 2)),     # one stage, strides and pads of their own per axis
+    (4, 16, 3, 3, 17, (3, 3), (2, 2)),     # rows between images advance by less than the stride
+    (1, 72, 33, 57, 31, (1, 1), (3, 3)),   # padding of a whole kernel
+    (2, 16, 1, 1, 40, (1, 1), (1, 1)),     # a single pixel
+    (9, 8, 33, 33, 128, (1, 1), (1, 1)),   # more than two 112-pixel tiles per CU
+    (26, 8, 51, 52, 64, (1, 1), (1, 1)),   # the balanced halo kernel's class
+])
+def test_conv_f32_patch_edges(x, N, C, H, W, OC, stride, pad):
+    """The fp32 patch kernels (every tile and split) where their patch can go
+    wrong, X and W one and three floats past a 16-byte boundary with NaN
+    around them.  Bit-exact (small integers)."""
+    import torch
+    X = xi.small_int_f32(43, (N, C, H, W))
+    Wt = xi.small_int_f32(44, (OC, C, 3, 3))
+    ref = oracle.conv2d(X, Wt, stride=stride, pad=pad)
+
+    def place(arr, off):
+        flat = np.full(arr.size + 24, np.nan, dtype=np.float32)
+        flat[off:off + arr.size] = arr.ravel()
+        return to_dev(flat)
+
+    for ox, ow in ((0, 0), (1, 3)):
+        Xd, Wd = place(X, ox), place(Wt, ow)
+        for s in [s for s in x.xtc_sched_list(x.XTC_OP_CONV2D, x.XTC_F32) if s.k_order == 2] + [None]:
+            Yd = torch.full(ref.shape, 7.0, dtype=torch.float32, device="cuda")
+            say("f32 patch", (N, C, H, W, OC, stride, pad), ox, s)
+            st = x.xtc_conv2d_nchw(N, C, H, W, OC, 3, 3, *stride, *pad, Xd.data_ptr() + 4 * ox,
+                                   Wd.data_ptr() + 4 * ow, Yd.data_ptr(), x.XTC_F32, s,
+                                   torch.cuda.current_stream().cuda_stream)
+            assert st == 0, x.xtc_status_str(st)
+            assert np.array_equal(to_host(Yd), ref), (ox, s)
+
+
 # ---------------------------------------------------------- closed forms
 
 
