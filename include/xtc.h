@@ -228,7 +228,9 @@ xtc_status xtc_matmul(int64_t M, int64_t N, int64_t K,
  *  XTC_ERR_TOO_LARGE.
  *  dtype XTC_F32 or XTC_BF16 (else XTC_ERR_BAD_DTYPE); each reduces in
  *  the order its schedule's k_order selects (bf16: 0, 2 or 3).
- *  sched NULL selects the default conv schedule.
+ *  sched NULL selects the default conv schedule, but for pointwise layers
+ *  (1x1, stride 1, no padding; bf16: C >= 32), which the matmul kernels
+ *  compute per image, with xtc_default_schedule's matmul rules.
  * Errors as for xtc_matmul; XTC_ERR_TOO_LARGE also when C*R*S exceeds the
  * kernel's k-offset table capacity (xtc_conv_max_k()).
  */

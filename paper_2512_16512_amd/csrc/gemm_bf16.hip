@@ -73,7 +73,7 @@ gemm_bf16_kernel(GemmArgs p) {
     const int m0 = tm * BM, n0 = tn * BN;
 
     const unsigned short *__restrict__ A = static_cast<const unsigned short *>(p.A);
-    const unsigned short *__restrict__ B = static_cast<const unsigned short *>(p.B);
+    const unsigned short *__restrict__ B = static_cast<const unsigned short *>(p.b_of(blockIdx.y));
     const int lda = p.lda, ldb = p.ldb;
 
     vec_t ra[G::A_LOADS], rb[G::B_LOADS];
@@ -177,7 +177,7 @@ gemm_bf16_kernel(GemmArgs p) {
         __syncthreads();
     }
 
-    float *__restrict__ C = p.C;
+    float *__restrict__ C = p.c_of(blockIdx.y);
     const int ldc = p.ldc;
 #pragma unroll
     for (int i = 0; i < G::TM; ++i)
@@ -298,7 +298,7 @@ gemm_bf16_dma_kernel(GemmArgs p) {
     const int m0 = tm * BM, n0 = tn * BN;
 
     const i32x4 ra = make_rsrc(p.A, ((M - 1) * p.lda + K) * 2);
-    const i32x4 rb = make_rsrc(p.B, ((K - 1) * p.ldb + N) * 2);
+    const i32x4 rb = make_rsrc(p.b_of(blockIdx.y), ((K - 1) * p.ldb + N) * 2);
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const unsigned smem_base = lds_address(smem);
 
@@ -531,7 +531,7 @@ gemm_bf16_dma_kernel(GemmArgs p) {
     }
     wait_vmcnt<0>();  // no copy may still be writing LDS when the workgroup ends
 
-    float *__restrict__ C = p.C;
+    float *__restrict__ C = p.c_of(blockIdx.y);
     const int ldc = p.ldc;
 #pragma unroll
     for (int i = 0; i < G::TM; ++i)
@@ -591,7 +591,7 @@ gemm_bf16_ksplit_kernel(GemmArgs p) {
     // resources from the dword that holds the first element to the dword
     // that holds the last one
     const unsigned long long abase = reinterpret_cast<unsigned long long>(p.A);
-    const unsigned long long bbase = reinterpret_cast<unsigned long long>(p.B);
+    const unsigned long long bbase = reinterpret_cast<unsigned long long>(p.b_of(blockIdx.y));
     const int amis = ODD ? (int)(abase & 2) : 0, bmis = ODD ? (int)(bbase & 2) : 0;
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
         reinterpret_cast<void *>(abase - amis), 0, (amis + ((M - 1) * lda + K) * 2 + 3) & ~3, 0x00020000);
@@ -699,7 +699,7 @@ gemm_bf16_ksplit_kernel(GemmArgs p) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) red[g][(i * 4 + r) * 2 + j][lane] = acc[i][j][r];
     __syncthreads();
-    float *__restrict__ C = p.C;
+    float *__restrict__ C = p.c_of(blockIdx.y);
     const int ldc = p.ldc;
     for (int q = g; q < NREG / 2; q += KS) {       // register pair (i, r) of both column blocks
         float v0 = red[0][2 * q][lane], v1 = red[0][2 * q + 1][lane];
@@ -722,7 +722,7 @@ hipError_t launch_bf16_ksplit(const GemmArgs &a, hipStream_t s) {
     const unsigned tiles = (unsigned)(((a.M + 16 * TM - 1) / (16 * TM)) * ((a.N + 31) / 32));
     GemmArgs args = a;
     void *kargs[] = {&args};
-    return hipLaunchKernel(reinterpret_cast<const void *>(&gemm_bf16_ksplit_kernel<TM, KS, D, ODD>), dim3(tiles),
+    return hipLaunchKernel(reinterpret_cast<const void *>(&gemm_bf16_ksplit_kernel<TM, KS, D, ODD>), dim3(tiles, (unsigned)a.batch),
                            dim3(KS * 64), kargs, 0, s);
 }
 
@@ -735,7 +735,7 @@ hipError_t launch_bf16_dma(const GemmArgs &a, hipStream_t s) {
     return hipLaunchKernel(
         reinterpret_cast<const void *>(
             &gemm_bf16_dma_kernel<BM, BN, BK, WM, WN, MI, STAGES>),
-        dim3(tiles), dim3(G::NT), kargs, 0, s);
+        dim3(tiles, (unsigned)a.batch), dim3(G::NT), kargs, 0, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -798,7 +798,7 @@ gemm_bf16_odd_kernel(GemmArgs p) {
     // resources from the dword that holds the first element to the one that
     // holds the last
     const unsigned long long abase = reinterpret_cast<unsigned long long>(p.A);
-    const unsigned long long bbase = reinterpret_cast<unsigned long long>(p.B);
+    const unsigned long long bbase = reinterpret_cast<unsigned long long>(p.b_of(blockIdx.y));
     const int amis = (int)(abase & 2), bmis = (int)(bbase & 2);
     const i32x4 ra = make_rsrc(reinterpret_cast<const void *>(abase - amis),
                                (amis + ((M - 1) * lda + K) * 2 + 3) & ~3);
@@ -951,7 +951,7 @@ gemm_bf16_odd_kernel(GemmArgs p) {
             for (int r = 0; r < MF::NACC; ++r)
                 red[(wm * WM + i * 32 + MF::row(lane, r)) * G::BN + wn * G::WN + j * 32 + l32] = acc[1][i][j][r];
     __syncthreads();
-    float *__restrict__ C = p.C;
+    float *__restrict__ C = p.c_of(blockIdx.y);
     const int ldc = p.ldc;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -976,7 +976,7 @@ hipError_t launch_bf16_odd(const GemmArgs &a, hipStream_t s) {
     const unsigned tiles = (unsigned)(((a.M + BM - 1) / BM) * ((a.N + G::NOUT - 1) / G::NOUT));
     GemmArgs args = a;
     void *kargs[] = {&args};
-    return hipLaunchKernel(reinterpret_cast<const void *>(&gemm_bf16_odd_kernel<BM, WM>), dim3(tiles), dim3(G::NT),
+    return hipLaunchKernel(reinterpret_cast<const void *>(&gemm_bf16_odd_kernel<BM, WM>), dim3(tiles, (unsigned)a.batch), dim3(G::NT),
                            kargs, 0, s);
 }
 
@@ -988,7 +988,7 @@ hipError_t launch_bf16(const GemmArgs &a, hipStream_t s) {
     void *kargs[] = {&args};
     return hipLaunchKernel(
         reinterpret_cast<const void *>(&gemm_bf16_kernel<BM, BN, BK, WM, WN, MI, PAD, VEC>),
-        dim3(tiles), dim3(G::NT), kargs, 0, s);
+        dim3(tiles, (unsigned)a.batch), dim3(G::NT), kargs, 0, s);
 }
 
 #define XTC_BF16_INSTANCE(BM, BN, BK, WM, WN, MI, PAD)                                        \

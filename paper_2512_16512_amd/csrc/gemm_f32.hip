@@ -78,7 +78,7 @@ gemm_f32_kernel(GemmArgs p) {
     const int m0 = tm * BM, n0 = tn * BN;
 
     const float *__restrict__ A = static_cast<const float *>(p.A);
-    const float *__restrict__ B = static_cast<const float *>(p.B);
+    const float *__restrict__ B = static_cast<const float *>(p.b_of(blockIdx.y));
     const int lda = p.lda, ldb = p.ldb;
 
     vec_t ra[G::A_LOADS], rb[G::B_LOADS];
@@ -165,7 +165,7 @@ gemm_f32_kernel(GemmArgs p) {
     }
 
     // Epilogue: accumulators -> C, masked on the edges.
-    float *__restrict__ C = p.C;
+    float *__restrict__ C = p.c_of(blockIdx.y);
     const int ldc = p.ldc;
 #pragma unroll
     for (int i = 0; i < G::TM; ++i)
@@ -187,7 +187,7 @@ hipError_t launch_f32(const GemmArgs &a, hipStream_t s) {
     GemmArgs args = a;
     void *kargs[] = {&args};
     return hipLaunchKernel(reinterpret_cast<const void *>(&gemm_f32_kernel<BM, BN, BK, WM, WN, MI, PAD, VEC>),
-                           dim3(tiles), dim3(G::NT), kargs, 0, s);
+                           dim3(tiles, (unsigned)a.batch), dim3(G::NT), kargs, 0, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -278,7 +278,7 @@ gemm_f32_dma_kernel(GemmArgs p) {
     const int m0 = tm * BM, n0 = tn * BN;
 
     const i32x4 ra = make_rsrc(p.A, ((M - 1) * p.lda + K) * 4);
-    const i32x4 rb = make_rsrc(p.B, ((K - 1) * p.ldb + N) * 4);
+    const i32x4 rb = make_rsrc(p.b_of(blockIdx.y), ((K - 1) * p.ldb + N) * 4);
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const unsigned smem_base = lds_address(smem);
 
@@ -474,7 +474,7 @@ gemm_f32_dma_kernel(GemmArgs p) {
                                             r * 64 + lane];
     }
 
-    float *__restrict__ C = p.C;
+    float *__restrict__ C = p.c_of(blockIdx.y);
     const int ldc = p.ldc;
 #pragma unroll
     for (int i = 0; i < G::TM; ++i)
@@ -497,7 +497,7 @@ hipError_t launch_f32_dma(const GemmArgs &a, hipStream_t s) {
     void *kargs[] = {&args};
     return hipLaunchKernel(
         reinterpret_cast<const void *>(&gemm_f32_dma_kernel<BM, BN, BK, WM, WN, MI, STAGES, KSW, TAIL>),
-        dim3(tiles), dim3(G::NT * KSW), kargs, 0, s);
+        dim3(tiles, (unsigned)a.batch), dim3(G::NT * KSW), kargs, 0, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -532,7 +532,7 @@ gemm_f32_ksplit_kernel(GemmArgs p) {
     const int m0 = tm * BM, n0 = tn * BN;
 
     const float *__restrict__ A = static_cast<const float *>(p.A);
-    const float *__restrict__ B = static_cast<const float *>(p.B);
+    const float *__restrict__ B = static_cast<const float *>(p.b_of(blockIdx.y));
     const int lda = p.lda, ldb = p.ldb;
 
     // Branch-free loads: buffer loads whose offset is moved past the end of
@@ -647,7 +647,7 @@ gemm_f32_ksplit_kernel(GemmArgs p) {
 #pragma unroll
             for (int r = 0; r < MF::NACC; ++r) red[g][(i * TN + j) * MF::NACC + r][lane] = acc[i][j][r];
     __syncthreads();
-    float *__restrict__ C = p.C;
+    float *__restrict__ C = p.c_of(blockIdx.y);
     const int ldc = p.ldc;
     for (int q = g; q < NREG; q += KS) {
         float v = red[0][q][lane];
@@ -668,7 +668,7 @@ hipError_t launch_f32_ksplit(const GemmArgs &a, hipStream_t s) {
     void *kargs[] = {&args};
     return hipLaunchKernel(
         reinterpret_cast<const void *>(&gemm_f32_ksplit_kernel<MI, TM, TN, KS, U, D, TAIL>),
-        dim3(tiles), dim3(KS * 64), kargs, 0, s);
+        dim3(tiles, (unsigned)a.batch), dim3(KS * 64), kargs, 0, s);
 }
 
 #define XTC_F32_INSTANCE(BM, BN, BK, WM, WN, MI, PAD)                                         \

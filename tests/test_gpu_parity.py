@@ -334,6 +334,36 @@ def test_conv_f32_patch_edges(x, N, C, H, W, OC, stride, pad):
             assert np.array_equal(to_host(Yd), ref), (ox, s)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,C,H,W,OC,off", [
+    (1, 32, 1, 1, 1, 0),       # one pixel, one channel out
+    (3, 33, 5, 7, 17, 1),      # odd everything: images at any element boundary
+    (70, 64, 4, 4, 40, 0),     # more images than tiles per image
+    (2, 128, 28, 28, 256, 0),  # whole 16-byte rows
+    (2, 96, 14, 14, 64, 2),    # 8-byte rows, 4-byte aligned base
+    (2, 16, 13, 13, 16, 0),    # fewer than 32 channels
+])
+def test_pointwise_conv_by_the_matmul_kernels(x, dtype, N, C, H, W, OC, off):
+    """1x1, stride 1, no padding without a schedule: one product per image.
+    X starts ``off`` elements past a 16-byte boundary, with infinities around
+    it.  Bit-exact (small integers)."""
+    import torch
+    X, Wt = xi.small_int_f32(61, (N, C, H, W)), xi.small_int_f32(62, (OC, C, 1, 1))
+    if dtype == "bf16":
+        X, Wt = xi.f32_to_bf16_bits(X), xi.f32_to_bf16_bits(Wt)
+    ref = oracle.relu(oracle.conv2d(X, Wt))
+    flat = np.full(X.size + 24, 0x7F80 if dtype == "bf16" else np.inf, dtype=X.dtype)
+    flat[off:off + X.size] = X.ravel()
+    Xd, Wd = to_dev(flat), to_dev(Wt)
+    Yd = torch.full(ref.shape, 7.0, dtype=torch.float32, device="cuda")
+    say("pointwise", dtype, (N, C, H, W, OC), off)
+    st = x.xtc_conv2d_nchw_relu(N, C, H, W, OC, 1, 1, 1, 1, 0, 0, Xd.data_ptr() + off * X.itemsize, Wd.data_ptr(),
+                                Yd.data_ptr(), x.XTC_F32 if dtype == "f32" else x.XTC_BF16, None,
+                                torch.cuda.current_stream().cuda_stream)
+    assert st == 0, x.xtc_status_str(st)
+    assert np.array_equal(to_host(Yd), ref)
+
+
 # ---------------------------------------------------------- closed forms
 
 
