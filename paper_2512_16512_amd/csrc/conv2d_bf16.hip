@@ -911,12 +911,14 @@ bool try_patch_bf16(const ConvArgs &a, hipStream_t s, hipError_t *err, bool smal
     return true;
 }
 
-// Outside the patch kernel's class: 128x128 gather tiles for more than 64
-// output channels, 64x64 when 64x128 tiles leave CUs idle.
+// Outside the patch kernel's class: 64x64 gather tiles up to four 64x128
+// tiles per CU (7x7 stride-2 first layers of 224x224 images, batch 4, 64
+// channels: 15.3 us against 19.0 with 64x128 tiles; batch 16, 784 tiles, 38.2
+// and 38.6), past that 64x128, and 128x128 for more than 64 output channels.
 hipError_t launch_conv_bf16_gather(const ConvArgs &a, hipStream_t s) {
     const long long N = (long long)a.Nb * a.OH * a.OW;
+    if ((a.OC + 63) / 64 * ((N + 127) / 128) < 1024) return launch_conv_bf16<64, 64, 32, 32, 32, 32, 8>(a, s);
     if (a.OC > 64) return launch_conv_bf16<128, 128, 32, 64, 64, 32, 8>(a, s);
-    if ((N + 127) / 128 < 256) return launch_conv_bf16<64, 64, 32, 32, 32, 32, 8>(a, s);
     return launch_conv_bf16<64, 128, 32, 32, 64, 32, 8>(a, s);
 }
 

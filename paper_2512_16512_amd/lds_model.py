@@ -971,7 +971,8 @@ def conv_launch(dtype: str, s: dict, N, C, H, W, OC, R, S, stride, pad):
         # 8-channel groups, then the gather kernel with a tile by shape
         if R == 3 and S == 3 and C % 8 == 0:
             return None
-        bm, bn = (128, 128) if OC > 64 else (64, 64) if _cdiv(N * OH * OW, 128) < 256 else (64, 128)
+        few = _cdiv(OC, 64) * _cdiv(N * OH * OW, 128) < 1024
+        bm, bn = (64, 64) if few else (128, 128) if OC > 64 else (64, 128)
         s = dict(s, k_order=0, block_m=bm, block_n=bn, block_k=32, wave_m=bm // 2, wave_n=bn // 2, mfma_m=32,
                  lds_pad=8)
     if dtype == "bf16" and s["k_order"] == 0:

@@ -588,7 +588,7 @@ def conv_grid(dtype: str, s: dict, N, C, H, W, OC, R, S, stride, pad):
         only = None if s["lds_pad"] < 0 else (s["block_m"], s["block_n"], s["lds_stages"])
         bm, bn = bf16_patch_tile(N, C, H, W, OC, R, S, stride, pad, only) or (
             # the gather kernel, its tile by shape
-            (128, 128) if OC > 64 else (64, 64) if _cdiv(N * OHW, 128) < 256 else (64, 128))
+            (64, 64) if _cdiv(OC, 64) * _cdiv(N * OHW, 128) < 1024 else (128, 128) if OC > 64 else (64, 128))
         s = dict(s, block_m=bm, block_n=bn)
     if dtype == "bf16":
         tn, seg = flattened(s["block_n"])
