@@ -279,7 +279,7 @@ struct Bf16DmaCfg {
 // Either way the ring's reuse is ordered by waits and the barrier, not by
 // the latency of the copies.  Scheduling-group barriers interleave the LDS
 // reads of the next k-step with the MFMAs of the current one.
-template <int BM, int BN, int BK, int WM, int WN, int MI, int STAGES>
+template <int BM, int BN, int BK, int WM, int WN, int MI, int STAGES, bool BATCH = false>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64)
 gemm_bf16_dma_kernel(GemmArgs p) {
     typedef Bf16DmaCfg<BM, BN, BK, WM, WN, MI, STAGES> G;
@@ -298,7 +298,7 @@ gemm_bf16_dma_kernel(GemmArgs p) {
     const int m0 = tm * BM, n0 = tn * BN;
 
     const i32x4 ra = make_rsrc(p.A, ((M - 1) * p.lda + K) * 2);
-    const i32x4 rb = make_rsrc(p.b_of(blockIdx.y), ((K - 1) * p.ldb + N) * 2);
+    const i32x4 rb = make_rsrc(BATCH ? p.b_of(blockIdx.y) : p.B, ((K - 1) * p.ldb + N) * 2);
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const unsigned smem_base = lds_address(smem);
 
@@ -531,7 +531,7 @@ gemm_bf16_dma_kernel(GemmArgs p) {
     }
     wait_vmcnt<0>();  // no copy may still be writing LDS when the workgroup ends
 
-    float *__restrict__ C = p.c_of(blockIdx.y);
+    float *__restrict__ C = BATCH ? p.c_of(blockIdx.y) : p.C;
     const int ldc = p.ldc;
 #pragma unroll
     for (int i = 0; i < G::TM; ++i)
@@ -732,10 +732,12 @@ hipError_t launch_bf16_dma(const GemmArgs &a, hipStream_t s) {
     const unsigned tiles = (unsigned)(((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN));
     GemmArgs args = a;
     void *kargs[] = {&args};
-    return hipLaunchKernel(
-        reinterpret_cast<const void *>(
-            &gemm_bf16_dma_kernel<BM, BN, BK, WM, WN, MI, STAGES>),
-        dim3(tiles, (unsigned)a.batch), dim3(G::NT), kargs, 0, s);
+    // the batched form apart: in the plain one the two address products in
+    // front of the main loop cost 8192^3 0.9% (850 -> 858 us)
+    const void *fn = a.batch > 1
+                         ? reinterpret_cast<const void *>(&gemm_bf16_dma_kernel<BM, BN, BK, WM, WN, MI, STAGES, true>)
+                         : reinterpret_cast<const void *>(&gemm_bf16_dma_kernel<BM, BN, BK, WM, WN, MI, STAGES, false>);
+    return hipLaunchKernel(fn, dim3(tiles, (unsigned)a.batch), dim3(G::NT), kargs, 0, s);
 }
 
 // ---------------------------------------------------------------------------

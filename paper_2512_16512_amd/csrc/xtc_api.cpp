@@ -420,8 +420,8 @@ int32_t xtc_sched_list(xtc_op op, xtc_dtype dt, xtc_sched *out, int32_t cap) {
 namespace {
 
 // Launches schedule s on checked operands: `batch` products of A with the
-// matrices stride_b bytes apart from B, into those stride_c floats apart
-// from C.
+// matrices stride_b bytes apart from B, into those stride_c bytes apart from
+// C.
 xtc_status launch_matmul(const xtc_sched &s, xtc_dtype dtype, int M, int N, int K, const void *A, int lda,
                          const void *B, int ldb, float *C, int ldc, int relu, int batch, int64_t stride_b,
                          int64_t stride_c, void *stream) {
@@ -432,7 +432,7 @@ xtc_status launch_matmul(const xtc_sched &s, xtc_dtype dtype, int M, int N, int 
     a.A = A; a.lda = lda; a.B = B; a.ldb = ldb; a.C = C; a.ldc = ldc;
     a.raster = s.raster; a.xcd_remap = s.xcd_remap;
     a.relu = relu;
-    a.batch = batch; a.stride_b = stride_b; a.stride_c = stride_c;
+    a.batch = batch; a.stride_b = (unsigned)stride_b; a.stride_c = (unsigned)stride_c;
     const int64_t elt = dtype == XTC_F32 ? 4 : 2, lda_b = lda * elt, ldb_b = ldb * elt, k_b = K * elt, n_b = N * elt;
     const bool a_rows = aligned16(A) && lda_b % 16 == 0;
     const bool b_rows = aligned16(B) && ldb_b % 16 == 0 && stride_b % 16 == 0;
@@ -521,7 +521,7 @@ xtc_status conv_impl(int64_t N, int64_t C, int64_t H, int64_t W, int64_t OC, int
         const int64_t HW = H * W;
         default_matmul(dtype, OC, HW, C, N, &s);
         return launch_matmul(s, dtype, (int)OC, (int)HW, (int)C, Wt, (int)C, X, (int)HW, Y, (int)HW, relu, (int)N,
-                             C * HW * elt, OC * HW, stream);
+                             C * HW * elt, OC * HW * 4, stream);
     }
     const ConvInstance *inst = find_conv(dtype, s);
     if (!inst) return XTC_ERR_UNSUPPORTED_SCHEDULE;

@@ -23,13 +23,16 @@ struct GemmArgs {
     int xcd_remap;  // 1: give each XCD a contiguous band of the tile order
     int relu;       // 1: the epilogue writes relu(acc) = (acc < 0 ? 0 : acc) (fused consumer)
     // products of one A with `batch` B (the images of a pointwise conv):
-    // grid row y computes C + y*stride_c from B + y*stride_b bytes
+    // grid row y computes C from B, each y strides on (bytes; all of B and of
+    // C span less than 2^31, so the offsets take 32-bit products)
+    unsigned stride_b, stride_c;
     int batch;
-    long long stride_b, stride_c;   // bytes; elements
-    __device__ __forceinline__ const void *b_of(int y) const {
+    __device__ __forceinline__ const void *b_of(unsigned y) const {
         return static_cast<const unsigned char *>(B) + y * stride_b;
     }
-    __device__ __forceinline__ float *c_of(int y) const { return C + y * stride_c; }
+    __device__ __forceinline__ float *c_of(unsigned y) const {
+        return reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(C) + y * stride_c);
+    }
 };
 
 // Arguments of one conv2d launch (implicit GEMM: M = OC, N = Nb*OH*OW,
