@@ -429,7 +429,9 @@ xtc_status launch_matmul(const xtc_sched &s, xtc_dtype dtype, int M, int N, int 
     if (!inst) return XTC_ERR_UNSUPPORTED_SCHEDULE;
     GemmArgs a;
     a.M = M; a.N = N; a.K = K;
-    a.A = A; a.lda = lda; a.B = B; a.ldb = ldb; a.C = C; a.ldc = ldc;
+    // (an empty B spans nothing whatever its rows' distance: the kernels size
+    // its range check as (K - 1) * ldb + N elements, which must not go below 0)
+    a.A = A; a.lda = lda; a.B = B; a.ldb = K > 0 ? ldb : N; a.C = C; a.ldc = ldc;
     a.raster = s.raster; a.xcd_remap = s.xcd_remap;
     a.relu = relu;
     a.batch = batch; a.stride_b = (unsigned)stride_b; a.stride_c = (unsigned)stride_c;

@@ -482,6 +482,23 @@ def test_K_zero_writes_zeros_and_empty_is_noop(x, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_K_zero_with_padded_rows_of_B(x, dtype):
+    """An empty reduction whose B has rows further apart than N: every
+    instance writes zeros and reads nothing."""
+    import torch
+    dt = x.XTC_F32 if dtype == "f32" else x.XTC_BF16
+    nan = torch.full((1024,), float("nan"), device="cuda")
+    for M, N in ((50, 70), (600, 520)):
+        for s in x.xtc_sched_list(x.XTC_OP_MATMUL, dt) + [None]:
+            c = torch.full((M, N), 5.0, device="cuda")
+            say("K = 0", dtype, M, N, s)
+            st = x.xtc_matmul(M, N, 0, nan.data_ptr(), 1, nan.data_ptr(), N + 24, c.data_ptr(), N, dt, s,
+                              torch.cuda.current_stream().cuda_stream)
+            assert st == 0, x.xtc_status_str(st)
+            assert np.all(to_host(c) == 0.0), s
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_deterministic_and_raster_independent(x, dtype):
     import torch
     A, B = _prep(xi.uniform_f32(17, (1000, 1000)), xi.uniform_f32(18, (1000, 1000)), dtype)
