@@ -116,8 +116,9 @@ typedef enum {
  *                  other shapes run the tap-major kernel.  lds_pad 0 (the
  *                  patch kernels: 3x3 layers of any stride, padding, row
  *                  length and batch) needs C % 8 == 0 and a patch that fits
- *                  in LDS; large layers of the 56-pixel class run the
- *                  block_n = 208 kernel, others the tap-major kernel.  Groups
+ *                  in LDS; layers of the 56-pixel class run the fastest of
+ *                  the halo kernels where that is faster than the patch
+ *                  kernels; outside both, the tap-major kernel.  Groups
  *                  of waves may share a tile, each reducing every second
  *                  (block_m 64, lds_stages 1) or fourth (block_m 16) stage;
  *                  bf16: chunks of 16, k = ((ic/16)*R*S + kh*S + kw)*16 +

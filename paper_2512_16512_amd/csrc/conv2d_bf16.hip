@@ -911,14 +911,22 @@ bool try_patch_bf16(const ConvArgs &a, hipStream_t s, hipError_t *err, bool smal
     return true;
 }
 
-// Outside the patch kernel's class: 64x64 gather tiles up to four 64x128
-// tiles per CU (7x7 stride-2 first layers of 224x224 images, batch 4, 64
-// channels: 15.3 us against 19.0 with 64x128 tiles; batch 16, 784 tiles, 38.2
-// and 38.6), past that 64x128, and 128x128 for more than 64 output channels.
+// Outside the patch kernel's class.  A CU holds five workgroups of 64x64 tiles
+// and four of 64x128 ones, whose round takes about 1.35 times as long (7x7
+// stride-2 first layers into 64 channels, 1176 small or 588 large tiles: 17.1
+// and 20.7 us): small tiles within one round of theirs and, past one round of
+// the large ones, up to two and a half (2156 and 1078: 27.4, 33.8; 3136 and
+// 1568: 37.2, 38.3); else the large ones (1568 and 784: 24.1, 22.9; 3844 and
+// 1922 of a 5x5 layer: 29.1, 27.1).  More than 64 output channels: 128x128 from
+// four 64x128 tiles per CU on.
 hipError_t launch_conv_bf16_gather(const ConvArgs &a, hipStream_t s) {
     const long long N = (long long)a.Nb * a.OH * a.OW;
-    if ((a.OC + 63) / 64 * ((N + 127) / 128) < 1024) return launch_conv_bf16<64, 64, 32, 32, 32, 32, 8>(a, s);
-    if (a.OC > 64) return launch_conv_bf16<128, 128, 32, 64, 64, 32, 8>(a, s);
+    const long long small = (a.OC + 63) / 64 * ((N + 63) / 64), large = (a.OC + 63) / 64 * ((N + 127) / 128);
+    if (a.OC > 64) {
+        if (large < 1024) return launch_conv_bf16<64, 64, 32, 32, 32, 32, 8>(a, s);
+        return launch_conv_bf16<128, 128, 32, 64, 64, 32, 8>(a, s);
+    }
+    if (small <= 1280 || (large > 1024 && small <= 3200)) return launch_conv_bf16<64, 64, 32, 32, 32, 32, 8>(a, s);
     return launch_conv_bf16<64, 128, 32, 32, 64, 32, 8>(a, s);
 }
 

@@ -2051,17 +2051,44 @@ typedef patch_f32::Cfg<4, 4, 2> PatchF32M2;
 typedef patch_f32::Cfg<4, 2, 2> PatchF32N;
 typedef patch_f32::Cfg<1, 2, 4> PatchF32T;
 
-// The patch instances: the balanced halo kernel where the shape is in its
-// class and gives it three quarters of the CUs (8x64x57x57 -> 128: 40.4 us
-// against 43.3), 208-pixel tiles in place of 112-pixel ones past two of those
-// per CU (32x64x57x57 -> 128: 142.7 against 163.0), and outside the patch
-// kernel's class the tap-major kernel.
+// The patch instances.  Layers of the halo kernels' class run the kernel with
+// the least time of its fullest CU, from the microseconds that each took for
+// 1, 2, 3 and 4 tiles on that CU (64 channels, 55 to 57 pixels a side, batch 4
+// to 32, into 64 and 128 channels; the ratios matter, and past four the last
+// step repeats).  A fixed line, the 208-pixel halo kernel from three quarters
+// of the CUs on, had 19x64x56x56 -> 128 at 100 us (64x256 tiles 86),
+// 20x64x56x56 -> 64 at 65.7 (64x416 tiles 60.2) and 9x64x57x57 -> 64 at 41.7
+// (split 64x64 tiles 33.6).  Outside that class: split 64x64 tiles where two
+// of them fill a CU that would take two of 112 pixels (28.9 + 13 against
+// 33.3 us), 208-pixel tiles in place of 112-pixel ones past two of those per
+// CU (32x64x57x57 -> 128: 142.7 against 163.0), and outside the patch kernel's
+// class the tap-major kernel.
 template <typename CFG>
 hipError_t launch_conv_f32_patch(const ConvArgs &a, hipStream_t s) {
-    const long long N = (long long)a.Nb * a.OH * a.OW;
+    const long long OHW = (long long)a.OH * a.OW, N = a.Nb * OHW;
     auto tiles = [&](int bn) { return (a.OC + 63) / 64 * ((N + bn - 1) / bn); };
-    if (tiles(208) >= 192 && halo16_tile_px<1>(a) > 0) return launch_conv_f32_halo16<2, 1>(a, s);
+    // (with 64x112 tiles, the default for layers of more than a 64x64 tile per CU, or large layers)
+    if (halo16_tile_px<1>(a) > 0 && (CFG::NB == 7 || tiles(208) >= 192)) {
+        auto time_of = [](long long n, const double (&us)[4]) {
+            const long long per_cu = (n + 255) / 256;
+            return per_cu <= 4 ? us[per_cu - 1] : us[3] + (double)(per_cu - 4) * (us[3] - us[2]);
+        };
+        // the halo kernels' tiles do not cross images
+        auto per_image = [&](int bn) { return (a.OC + 63) / 64 * a.Nb * ((OHW + bn - 1) / bn); };
+        const double t208 = time_of(per_image(208), {38.3, 66.0, 100.3, 129.0});
+        const double t256 = halo_eligible(a) ? time_of(per_image(256), {49.5, 85.0, 127.5, 166.5}) : 1e30;
+        const double t416 = halo16_tile_px<2>(a) > 0 ? time_of(per_image(416), {60.5, 119.0, 178.0, 237.0}) : 1e30;
+        const double t112 = tiles(112) <= 512 ? time_of(tiles(112), {29.5, 42.3, 0, 0}) : 1e30;
+        const double t64 = tiles(64) <= 768 ? time_of(tiles(64), {17.8, 33.4, 49.0, 0}) : 1e30;
+        const double halo = std::min(std::min(t208, t256), t416);
+        if (halo <= std::min(t112, t64)) {
+            if (t208 <= halo) return launch_conv_f32_halo16<2, 1>(a, s);
+            if (t256 <= halo) return launch_conv_f32_halo<2>(a, s);
+            return launch_conv_f32_halo16<2, 2>(a, s);
+        }
+    }
     hipError_t err;
+    if (CFG::NB == 7 && tiles(112) > 256 && tiles(64) <= 512 && try_patch_f32<PatchF32M2>(a, s, &err)) return err;
     if (CFG::NB == 7 && tiles(112) > 512 && try_patch_f32<PatchF32L>(a, s, &err)) return err;
     if (try_patch_f32<CFG>(a, s, &err) || try_patch_f32<PatchF32N>(a, s, &err) || try_patch_f32<PatchF32M>(a, s, &err))
         return err;

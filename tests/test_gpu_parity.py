@@ -334,6 +334,33 @@ def test_conv_f32_patch_edges(x, N, C, H, W, OC, stride, pad):
             assert np.array_equal(to_host(Yd), ref), (ox, s)
 
 
+@pytest.mark.parametrize("dtype,N,C,H,W,OC,R,stride,pad", [
+    ("f32", 9, 16, 57, 57, 64, 3, 1, 1),    # halo class: two split 64x64 patch tiles per CU
+    ("f32", 20, 16, 56, 56, 64, 3, 1, 1),   # halo class: 416-pixel tiles
+    ("f32", 19, 16, 56, 56, 128, 3, 1, 1),  # halo class: 64x256 tiles, two per CU
+    ("f32", 37, 8, 28, 28, 64, 3, 1, 1),    # outside it: two split 64x64 patch tiles per CU
+    ("bf16", 7, 3, 219, 221, 32, 3, 2, 1),  # gather: past one round of 64x64 tiles
+    ("bf16", 11, 3, 224, 224, 16, 3, 2, 1), # past one round of 64x128 tiles
+    ("bf16", 17, 3, 224, 224, 16, 3, 2, 1), # past two and a half rounds of 64x64 tiles
+])
+def test_conv_default_by_rounds_of_tiles(x, dtype, N, C, H, W, OC, R, stride, pad):
+    """The default conv kernels on both sides of the lines between tile sizes.
+    Bit-exact (small integers)."""
+    import torch
+    X, Wt = xi.small_int_f32(71, (N, C, H, W)), xi.small_int_f32(72, (OC, C, R, R))
+    if dtype == "bf16":
+        X, Wt = xi.f32_to_bf16_bits(X), xi.f32_to_bf16_bits(Wt)
+    ref = oracle.conv2d(X, Wt, stride=stride, pad=pad)
+    Xd, Wd = to_dev(X), to_dev(Wt)
+    Yd = torch.full(ref.shape, 7.0, dtype=torch.float32, device="cuda")
+    say("conv default", dtype, (N, C, H, W, OC, R, stride, pad))
+    st = x.xtc_conv2d_nchw(N, C, H, W, OC, R, R, stride, stride, pad, pad, Xd.data_ptr(), Wd.data_ptr(),
+                           Yd.data_ptr(), x.XTC_F32 if dtype == "f32" else x.XTC_BF16, None,
+                           torch.cuda.current_stream().cuda_stream)
+    assert st == 0, x.xtc_status_str(st)
+    assert np.array_equal(to_host(Yd), ref)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("N,C,H,W,OC,off", [
     (1, 32, 1, 1, 1, 0),       # one pixel, one channel out
