@@ -116,9 +116,9 @@ typedef enum {
  *                  other shapes run the tap-major kernel.  lds_pad 0 (the
  *                  patch kernels: 3x3 layers of any stride, padding, row
  *                  length and batch) needs C % 8 == 0 and a patch that fits
- *                  in LDS; layers of the 56-pixel class run the fastest of
- *                  the halo kernels where that is faster than the patch
- *                  kernels; outside both, the tap-major kernel.  Groups
+ *                  in LDS.  block_n = 112, and all of them for large layers
+ *                  of the 56-pixel class, run the patch, halo or tap-major
+ *                  kernel whose tiles share the CUs best.  Groups
  *                  of waves may share a tile, each reducing every second
  *                  (block_m 64, lds_stages 1) or fourth (block_m 16) stage;
  *                  bf16: chunks of 16, k = ((ic/16)*R*S + kh*S + kw)*16 +

@@ -2051,45 +2051,77 @@ typedef patch_f32::Cfg<4, 4, 2> PatchF32M2;
 typedef patch_f32::Cfg<4, 2, 2> PatchF32N;
 typedef patch_f32::Cfg<1, 2, 4> PatchF32T;
 
-// The patch instances.  Layers of the halo kernels' class run the kernel with
-// the least time of its fullest CU, from the microseconds that each took for
-// 1, 2, 3 and 4 tiles on that CU (64 channels, 55 to 57 pixels a side, batch 4
-// to 32, into 64 and 128 channels; the ratios matter, and past four the last
-// step repeats).  A fixed line, the 208-pixel halo kernel from three quarters
-// of the CUs on, had 19x64x56x56 -> 128 at 100 us (64x256 tiles 86),
-// 20x64x56x56 -> 64 at 65.7 (64x416 tiles 60.2) and 9x64x57x57 -> 64 at 41.7
-// (split 64x64 tiles 33.6).  Outside that class: split 64x64 tiles where two
-// of them fill a CU that would take two of 112 pixels (28.9 + 13 against
-// 33.3 us), 208-pixel tiles in place of 112-pixel ones past two of those per
-// CU (32x64x57x57 -> 128: 142.7 against 163.0), and outside the patch kernel's
-// class the tap-major kernel.
+// Workgroups of the patch kernel with tile CFG that a CU's LDS holds (1 or 2);
+// 0 outside its class.
+template <typename CFG>
+int patch_f32_per_cu(const ConvArgs &a) {
+    PatchF32Args pa;
+    size_t lds;
+    if (!patch_f32_geom<CFG, 10>(a, &pa, &lds) && !patch_f32_geom<CFG, 24>(a, &pa, &lds)) return 0;
+    return lds <= patch_f32::kMaxLds / 2 ? 2 : 1;
+}
+
+// The patch instances.  The one with 64x112 tiles, the default for layers of
+// more than a 64x64 tile per CU, and all of them for large layers of the halo
+// kernels' class, run the kernel with the least time of its fullest CU.  The
+// times are microseconds per 64 channels for 1, 2, ... tiles on that CU
+// (their ratios matter), fitted to 64 to 256 channels, 14 to 64 pixels a side,
+// strides 1 and 2 and batch 4 to 32; past the table its last step repeats.
+// Fixed lines had 19x64x56x56 -> 128 at 100 us (64x256 halo tiles: 86),
+// 20x64x56x56 -> 64 at 65.7 (64x416: 60.2), 9x64x57x57 -> 64 at 41.7 (split
+// 64x64 tiles: 33.6), 20x128x28x28 -> 256 at 133 (tap-major 64x128: 107),
+// 30x64x64x64 -> 128 at 227 (tap-major 128x128: 174) and 32x256x22x22 -> 256 at
+// 258 (split 64x64: 204).  Outside the patch kernel's class the tap-major
+// kernel runs.
 template <typename CFG>
 hipError_t launch_conv_f32_patch(const ConvArgs &a, hipStream_t s) {
-    const long long OHW = (long long)a.OH * a.OW, N = a.Nb * OHW;
-    auto tiles = [&](int bn) { return (a.OC + 63) / 64 * ((N + bn - 1) / bn); };
-    // (with 64x112 tiles, the default for layers of more than a 64x64 tile per CU, or large layers)
-    if (halo16_tile_px<1>(a) > 0 && (CFG::NB == 7 || tiles(208) >= 192)) {
-        auto time_of = [](long long n, const double (&us)[4]) {
+    const long long OHW = (long long)a.OH * a.OW, N = a.Nb * OHW, tm = (a.OC + 63) / 64;
+    auto tiles = [&](int bn) { return tm * ((N + bn - 1) / bn); };
+    const bool halo_class = halo16_tile_px<1>(a) > 0;
+    hipError_t err;
+    if (CFG::NB == 7 || (halo_class && tiles(208) >= 192)) {
+        const double none = 1e30, c = 64.0 / a.C;
+        auto time_of = [](long long n, const double (&us)[4], double step) {
             const long long per_cu = (n + 255) / 256;
-            return per_cu <= 4 ? us[per_cu - 1] : us[3] + (double)(per_cu - 4) * (us[3] - us[2]);
+            return per_cu <= 4 ? us[per_cu - 1] : us[3] + (double)(per_cu - 4) * step;
         };
-        // the halo kernels' tiles do not cross images
-        auto per_image = [&](int bn) { return (a.OC + 63) / 64 * a.Nb * ((OHW + bn - 1) / bn); };
-        const double t208 = time_of(per_image(208), {38.3, 66.0, 100.3, 129.0});
-        const double t256 = halo_eligible(a) ? time_of(per_image(256), {49.5, 85.0, 127.5, 166.5}) : 1e30;
-        const double t416 = halo16_tile_px<2>(a) > 0 ? time_of(per_image(416), {60.5, 119.0, 178.0, 237.0}) : 1e30;
-        const double t112 = tiles(112) <= 512 ? time_of(tiles(112), {29.5, 42.3, 0, 0}) : 1e30;
-        const double t64 = tiles(64) <= 768 ? time_of(tiles(64), {17.8, 33.4, 49.0, 0}) : 1e30;
-        const double halo = std::min(std::min(t208, t256), t416);
-        if (halo <= std::min(t112, t64)) {
-            if (t208 <= halo) return launch_conv_f32_halo16<2, 1>(a, s);
-            if (t256 <= halo) return launch_conv_f32_halo<2>(a, s);
-            return launch_conv_f32_halo16<2, 2>(a, s);
+        auto rounds = [](long long n, int per_cu) { return (double)((n + 256 * per_cu - 1) / (256 * per_cu)); };
+        // halo kernels: their tiles do not cross images
+        auto per_image = [&](int bn) { return tm * a.Nb * ((OHW + bn - 1) / bn); };
+        double h208 = none, h256 = none, h416 = none;
+        if (halo_class) {
+            h208 = time_of(per_image(208), {38.3, 66.0, 100.3, 129.0}, 32);
+            if (halo_eligible(a)) h256 = time_of(per_image(256), {49.5, 85.0, 127.5, 166.5}, 41);
+            if (halo16_tile_px<2>(a) > 0) h416 = rounds(per_image(416), 1) * 60.5;
+        }
+        // patch kernels: a second workgroup on a CU costs half a first one
+        // where LDS holds both
+        const int w64 = patch_f32_per_cu<PatchF32M2>(a), w112 = patch_f32_per_cu<PatchF32M>(a),
+                  w208 = patch_f32_per_cu<PatchF32L>(a);
+        const double one112 = 23 + 6.5 * c;
+        const double p64 = w64 ? rounds(tiles(64), 1) * (11.8 + 4.2 * c) : none;
+        const double p112 = !w112 || tiles(112) > 512   ? none
+                            : w112 == 2 && tiles(112) > 256 ? 36 + 6.3 * c
+                                                            : rounds(tiles(112), 1) * one112;
+        const double p208 = !w208 ? none : w208 == 2 ? rounds(tiles(208), 2) * 67 : rounds(tiles(208), 1) * 45;
+        // tap-major kernels (whole 32-channel steps)
+        const double strided = a.sh > 1 || a.sw > 1 ? 1.15 : 1.0;
+        const double t128 = a.C % 32 ? none : strided * time_of(tiles(128), {33, 53, 69, 94}, 22.3);
+        const double t128x2 =
+            a.C % 32 || a.OC <= 64 ? none
+                                   : strided * time_of((a.OC + 127) / 128 * ((N + 127) / 128), {57, 84, 145, 174}, 43);
+        const double least = std::min({h208, h256, h416, p64, p112, p208, t128, t128x2});
+        if (least < none) {
+            if (least == p64 && try_patch_f32<PatchF32M2>(a, s, &err)) return err;
+            if (least == p112 && try_patch_f32<PatchF32M>(a, s, &err)) return err;
+            if (least == h208) return launch_conv_f32_halo16<2, 1>(a, s);
+            if (least == h256) return launch_conv_f32_halo<2>(a, s);
+            if (least == h416) return launch_conv_f32_halo16<2, 2>(a, s);
+            if (least == p208 && try_patch_f32<PatchF32L>(a, s, &err)) return err;
+            if (least == t128) return launch_conv_f32_tap<64, 128, 32, 64, 2, 3>(a, s);
+            if (least == t128x2) return launch_conv_f32_tap<128, 128, 64, 64, 2, 3>(a, s);
         }
     }
-    hipError_t err;
-    if (CFG::NB == 7 && tiles(112) > 256 && tiles(64) <= 512 && try_patch_f32<PatchF32M2>(a, s, &err)) return err;
-    if (CFG::NB == 7 && tiles(112) > 512 && try_patch_f32<PatchF32L>(a, s, &err)) return err;
     if (try_patch_f32<CFG>(a, s, &err) || try_patch_f32<PatchF32N>(a, s, &err) || try_patch_f32<PatchF32M>(a, s, &err))
         return err;
     if (a.OC > 64) return launch_conv_f32_tap<128, 128, 64, 64, 2, 3>(a, s);

@@ -339,6 +339,8 @@ def test_conv_f32_patch_edges(x, N, C, H, W, OC, stride, pad):
     ("f32", 20, 16, 56, 56, 64, 3, 1, 1),   # halo class: 416-pixel tiles
     ("f32", 19, 16, 56, 56, 128, 3, 1, 1),  # halo class: 64x256 tiles, two per CU
     ("f32", 37, 8, 28, 28, 64, 3, 1, 1),    # outside it: two split 64x64 patch tiles per CU
+    ("f32", 28, 8, 28, 28, 256, 3, 1, 1),   # outside it: 208-pixel patch tiles
+    ("f32", 20, 32, 28, 28, 256, 3, 1, 1),  # outside it: tap-major 64x128 tiles
     ("bf16", 7, 3, 219, 221, 32, 3, 2, 1),  # gather: past one round of 64x64 tiles
     ("bf16", 11, 3, 224, 224, 16, 3, 2, 1), # past one round of 64x128 tiles
     ("bf16", 17, 3, 224, 224, 16, 3, 2, 1), # past two and a half rounds of 64x64 tiles
