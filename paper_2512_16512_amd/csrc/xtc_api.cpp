@@ -239,11 +239,11 @@ void default_matmul(xtc_dtype dt, int64_t M, int64_t N, int64_t K, int64_t batch
                           c64 = sat_mul(cdiv(tiles(64, 32), cus), 104);
             const int bm = c16 <= c32 && c16 <= c64 ? 16 : c32 <= c64 ? 32 : 64;
             *out = make_sched(bm, 32, 32, bm, 32, 16, 16, 32, 0, 0, 0, 0, 4);
-        } else if (tiles(256, 256) >= cus)
+        } else if (tiles(256, 256) >= cus && M > 128)
             *out = make_sched(256, 256, 32, 128, 64, 32, 32, 16, 4, -1, 0);
-        else if (tiles(128, 128) >= cus)
+        else if (tiles(128, 128) >= cus && M > 64)
             *out = make_sched(128, 128, 32, 64, 64, 32, 32, 16, 4, -1, 0);
-        else
+        else   // (and where half of a larger tile's rows would lie past M)
             *out = make_sched(64, 128, 64, 32, 64, 32, 32, 16, 2, -1, 0);
     }
     const int64_t t = tiles(out->block_m, out->block_n);
@@ -517,9 +517,14 @@ xtc_status conv_impl(int64_t N, int64_t C, int64_t H, int64_t W, int64_t OC, int
     // fp32 45.3 and 47.3 us with the conv kernels, 5.6 and 39.8; bf16 43.9 and
     // 45.5, 3.7 and 10.9).  bf16 layers of fewer than 32 channels stay with the
     // gather kernel, whose single small stage they fit (32x16x55x55 -> 64:
-    // 10.0 us, 21.4 with 64-k steps of odd rows).
+    // 10.0 us, 21.4 with 64-k steps of odd rows), and, where images do not
+    // start on 16 bytes, those of up to 64 channels from two of its tiles per
+    // CU on, or from fewer than 64 (26x64x55x55 -> 64: 9.9 us against 18.5;
+    // 13x64x27x27 -> 64, 149 tiles: 5.8, 6.0; 4x64x27x27 -> 64: 5.5, 4.7).
+    const bool gather = dtype == XTC_BF16 &&
+                        (C < 32 || (H * W % 8 != 0 && (C < 64 || (C == 64 && cdiv(OC, 64) * cdiv(Ng, 64) >= 512))));
     if (!sched && R == 1 && S == 1 && stride_h == 1 && stride_w == 1 && pad_h == 0 && pad_w == 0 && N <= 65535 &&
-        (dtype == XTC_F32 || C >= 32)) {
+        !gather) {
         const int64_t HW = H * W;
         default_matmul(dtype, OC, HW, C, N, &s);
         return launch_matmul(s, dtype, (int)OC, (int)HW, (int)C, Wt, (int)C, X, (int)HW, Y, (int)HW, relu, (int)N,
