@@ -18,6 +18,7 @@
 #include "fast_div.h"
 #include "lds_dma.h"
 #include "mfma_bf16.h"
+#include "patch_geom.h"
 #include "tile_map.h"
 #include "xtc_internal.h"
 
@@ -574,8 +575,6 @@ conv2d_bf16_patch_kernel(PatchArgs pa) {
     auto seg_rows = [&](int i) {
         return max(min((i == img1 ? oh1 : OH - 1) * p.sh + 2 - p.ph, H - 1) - seg_first(i) + 1, 0);
     };
-    // 16-byte units that hold `rows` rows from any position
-    auto seg_units = [&](int rows) { return rows > 0 ? (rows * Wd * 2 + 29) >> 4 : 0; };
     const int area_bytes = RD * RAW + CFG::W_BYTES + 2 * HALF;
     unsigned char *const raw = psm + kg * area_bytes;              // [RD][weights | input]
     unsigned char *const cells = raw + RD * RAW;                   // weights | patch halves
@@ -587,8 +586,7 @@ conv2d_bf16_patch_kernel(PatchArgs pa) {
 
     // Two tables, built once by the first threads of each group in its raw
     // area.  Per unit u of a channel's slot: {byte offset of its segment's
-    // first input row in channel 0, 16 * (u within the segment), -1 past the
-    // last unit}.  Per input row r: {that byte offset, position of the row in
+    // first input row in channel 0, its unit_entry}.  Per input row r: {that byte offset, position of the row in
     // the slot (before the segment's misalignment), its patch cell, -}.
     const int plane = __builtin_amdgcn_readfirstlane(H * Wd * 2);   // bytes per channel plane
     const int xmis = (int)(reinterpret_cast<unsigned long long>(p.X) & 15);
@@ -598,9 +596,9 @@ conv2d_bf16_patch_kernel(PatchArgs pa) {
     {
         int ub = 0;
         for (int i = img0; i <= img1; ++i) {
-            const int n = seg_rows(i), f = seg_first(i), nu = seg_units(n);
+            const int n = seg_rows(i), f = seg_first(i), nu = slot_units(n * Wd * 2);
             const int start = xmis + (i * C * H + f) * Wd * 2;
-            for (int u = t; u < nu; u += NTG) utab[ub + u] = make_int2(start, u * 16);
+            for (int u = t; u < nu; u += NTG) utab[ub + u] = make_int2(start, unit_entry(u, n * Wd * 2));
             for (int r = t; r < n; r += NTG)
                 rtab[nrows + r] = make_int4(start, ub * 16 + r * Wd * 2,
                                             ((i - img0) * PH + f + r + p.ph - prow0) * WPA + p.pw, 0);
@@ -627,7 +625,8 @@ conv2d_bf16_patch_kernel(PatchArgs pa) {
     for (int k = 0; k < NBX; ++k) {
         const int v = (wave * NBX + k) * 64 + lane, ch = v / SU;
         const int2 e = utab[v - ch * SU];
-        xoff[k] = e.y >= 0 ? ((e.x + ch * plane) & ~15) + e.y : kOOB;
+        // (unsigned: channels past the last one, masked below, may lie past 2^31)
+        xoff[k] = unit_offset(e.y, (int)((unsigned)e.x + (unsigned)ch * (unsigned)plane), kOOB);
         xhi |= (ch >= 8 ? 1u : 0u) << k;
     }
     const i32x4 rw = make_rsrc(p.Wt, OC * C * NTAP * 2);
