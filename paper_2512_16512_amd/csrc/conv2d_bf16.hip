@@ -14,6 +14,7 @@
 // ds_read_b128 per A fragment from k-contiguous padded rows, and two gfx950
 // transpose reads per B fragment from the pixel-contiguous B tile.
 #include <algorithm>
+#include <type_traits>
 
 #include "fast_div.h"
 #include "lds_dma.h"
@@ -825,24 +826,29 @@ conv2d_bf16_patch_kernel(PatchArgs pa) {
     // Output: pixels and channels outside Y are stored at an out-of-range
     // offset, which drops them.
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.Y, 0, N * OC * 4, 0x00020000);
-    const bool whole = m0 + BM <= OC;
+    auto store = [&](auto WHOLE) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int q = q0 + wn * WN + j * MI + l32;
-        const int img = div_by(q, pa.by_ohw), pix = q - img * OHW;
+        for (int j = 0; j < TN; ++j) {
+            const int q = q0 + wn * WN + j * MI + l32;
+            const int img = div_by(q, pa.by_ohw), pix = q - img * OHW;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int oc = m0 + wm * WM + i * MI + 4 * lgrp;
-            const int off = q < N ? (img * OC + oc) * OHW * 4 + pix * 4 : kOOB;
+            for (int i = 0; i < TM; ++i) {
+                const int oc = m0 + wm * WM + i * MI + 4 * lgrp;
+                const unsigned first = ((unsigned)(img * OC + oc) * (unsigned)OHW + (unsigned)pix) * 4u;
 #pragma unroll
-            for (int r = 0; r < MF::NACC; ++r) {
-                const int row = 8 * (r >> 2) + (r & 3);   // MF::row without the lane's part
-                const float v = (p.relu && acc[i][j][r] < 0.f) ? 0.f : acc[i][j][r];
-                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), ry,
-                                                      whole || oc + row < OC ? off : kOOB, row * OHW * 4, 0);
+                for (int r = 0; r < MF::NACC; ++r) {
+                    const int row = 8 * (r >> 2) + (r & 3);   // MF::row without the lane's part
+                    const float v = (p.relu && acc[i][j][r] < 0.f) ? 0.f : acc[i][j][r];
+                    const StoreOffset o = store_offset(decltype(WHOLE)::value, q < N, oc + row < OC, first,
+                                                       (unsigned)row * (unsigned)OHW * 4u, kOOB);
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), ry, (int)o.lane,
+                                                          (int)o.scalar, 0);
+                }
             }
         }
-    }
+    };
+    if (m0 + BM <= OC) store(std::true_type{});
+    else store(std::false_type{});
 }
 
 // Shapes whose patch kernel launch is laid out in *pa and *lds (bytes): 3x3,

@@ -23,6 +23,7 @@
 #include "fast_div.h"
 #include "lds_dma.h"
 #include "mfma_f32.h"
+#include "patch_geom.h"
 #include "tile_map.h"
 #include "unroll.h"
 #include "xtc_internal.h"
@@ -1926,17 +1927,22 @@ conv2d_f32_patch_kernel(PatchF32Args pa) {
     // channels outside Y go to an out-of-range offset and are dropped.
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(p.Y, 0, N * OC * 4, 0x00020000);
     const int oc = m0 + wave * 16 + 4 * lgrp;
+    auto store = [&](auto WHOLE) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        const int q = q0 + j * 16 + l16, img = div_by(q, pa.by_ohw), pix = q - img * OHW;
-        const int off = q < N ? ((img * OC + oc) * OHW + pix) * 4 : kOOB;
+        for (int j = 0; j < NB; ++j) {
+            const int q = q0 + j * 16 + l16, img = div_by(q, pa.by_ohw), pix = q - img * OHW;
+            const unsigned first = ((unsigned)(img * OC + oc) * (unsigned)OHW + (unsigned)pix) * 4u;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float v = (p.relu && acc[j][r] < 0.f) ? 0.f : acc[j][r];
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), ry, oc + r < OC ? off : kOOB,
-                                                  r * OHW * 4, 0);
+            for (int r = 0; r < 4; ++r) {
+                const float v = (p.relu && acc[j][r] < 0.f) ? 0.f : acc[j][r];
+                const StoreOffset o = store_offset(decltype(WHOLE)::value, q < N, oc + r < OC, first,
+                                                   (unsigned)r * (unsigned)OHW * 4u, kOOB);
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), ry, (int)o.lane, (int)o.scalar, 0);
+            }
         }
-    }
+    };
+    if (m0 + BM <= OC) store(std::true_type{});
+    else store(std::false_type{});
 }
 
 template <typename CFG, int NPB>

@@ -23,4 +23,18 @@ constexpr int unit_offset(int entry, int start, int oob) {
     return entry >= 0 && (entry & 0xffff) < (start & 15) + (entry >> 16) ? (start & ~15) + (entry & 0xffff) : oob;
 }
 
+// Lane and scalar offset (bytes) of the store of one output, `row` bytes past
+// the lane's first one at `first`; `whole`: every output channel of the tile
+// exists.  A store that does not exist goes to an offset past the buffer, which
+// drops it: the sum must stay below 2^32, and `row` itself (27 channel planes)
+// may be past 2^31 where the tile has more channels than Y, so there the row is
+// part of the lane's offset.
+struct StoreOffset {
+    unsigned lane, scalar;
+};
+constexpr StoreOffset store_offset(bool whole, bool pixel, bool channel, unsigned first, unsigned row, unsigned oob) {
+    return whole ? StoreOffset{pixel ? first : oob, row}
+                 : StoreOffset{pixel && channel ? first + row : oob, 0};
+}
+
 }  // namespace xtc
