@@ -116,9 +116,7 @@ typedef enum {
  *                  other shapes run the tap-major kernel.  lds_pad 0 (the
  *                  patch kernels: 3x3 layers of any stride, padding, row
  *                  length and batch) needs C % 8 == 0 and a patch that fits
- *                  in LDS.  block_n = 112, and all of them for large layers
- *                  of the 56-pixel class, run the patch, halo or tap-major
- *                  kernel whose tiles share the CUs best.  Groups
+ *                  in LDS; other shapes run the tap-major kernel.  Groups
  *                  of waves may share a tile, each reducing every second
  *                  (block_m 64, lds_stages 1) or fourth (block_m 16) stage;
  *                  bf16: chunks of 16, k = ((ic/16)*R*S + kh*S + kw)*16 +
@@ -229,7 +227,9 @@ xtc_status xtc_matmul(int64_t M, int64_t N, int64_t K,
  *  XTC_ERR_TOO_LARGE.
  *  dtype XTC_F32 or XTC_BF16 (else XTC_ERR_BAD_DTYPE); each reduces in
  *  the order its schedule's k_order selects (bf16: 0, 2 or 3).
- *  sched NULL selects the default conv schedule, but for pointwise layers
+ *  sched NULL selects the default conv schedule, but for large fp32 3x3
+ *  layers of whole 8-channel groups, which run the patch, halo or tap-major
+ *  kernel whose tiles share the CUs best for their shape, and pointwise layers
  *  (1x1, stride 1, no padding; bf16: C >= 32), which the matmul kernels
  *  compute per image, with xtc_default_schedule's matmul rules.
  * Errors as for xtc_matmul; XTC_ERR_TOO_LARGE also when C*R*S exceeds the

@@ -1975,18 +1975,26 @@ bool patch_f32_geom(const ConvArgs &a, PatchF32Args *pa, size_t *lds) {
     return true;
 }
 
+// The patch kernel with tile CFG that holds the layer's patch, or null if the
+// shape is outside it: up to 10 blocks a channel, or up to 24 where LDS holds
+// more than 10 (it does not where the reduction is split).
+template <typename CFG>
+const void *patch_f32_kernel(const ConvArgs &a, PatchF32Args *pa, size_t *lds) {
+    using namespace patch_f32;
+    if (patch_f32_geom<CFG, 10>(a, pa, lds)) return reinterpret_cast<const void *>(&conv2d_f32_patch_kernel<CFG, 10>);
+    if constexpr (CFG::KS * 2 * (CFG::W_BYTES + CC * (11 * 64 + 16) * 4) <= kMaxLds)
+        if (patch_f32_geom<CFG, 24>(a, pa, lds))
+            return reinterpret_cast<const void *>(&conv2d_f32_patch_kernel<CFG, 24>);
+    return nullptr;
+}
+
 // Tries the patch kernel with tile CFG; false if the shape is outside it.
 template <typename CFG>
 bool try_patch_f32(const ConvArgs &a, hipStream_t s, hipError_t *err) {
     PatchF32Args pa;
     size_t lds;
-    const void *fn;
-    if (patch_f32_geom<CFG, 10>(a, &pa, &lds))
-        fn = reinterpret_cast<const void *>(&conv2d_f32_patch_kernel<CFG, 10>);
-    else if (patch_f32_geom<CFG, 24>(a, &pa, &lds))
-        fn = reinterpret_cast<const void *>(&conv2d_f32_patch_kernel<CFG, 24>);
-    else
-        return false;
+    const void *fn = patch_f32_kernel<CFG>(a, &pa, &lds);
+    if (!fn) return false;
     const int N = a.Nb * a.OH * a.OW;
     const unsigned tiles = (unsigned)(((a.OC + CFG::BM - 1) / CFG::BM) * ((N + CFG::BN - 1) / CFG::BN));
     void *kargs[] = {&pa};
@@ -2063,13 +2071,28 @@ template <typename CFG>
 int patch_f32_per_cu(const ConvArgs &a) {
     PatchF32Args pa;
     size_t lds;
-    if (!patch_f32_geom<CFG, 10>(a, &pa, &lds) && !patch_f32_geom<CFG, 24>(a, &pa, &lds)) return 0;
+    if (!patch_f32_kernel<CFG>(a, &pa, &lds)) return 0;
     return lds <= patch_f32::kMaxLds / 2 ? 2 : 1;
 }
 
-// The patch instances.  The one with 64x112 tiles, the default for layers of
-// more than a 64x64 tile per CU, and all of them for large layers of the halo
-// kernels' class, run the kernel with the least time of its fullest CU.  The
+// Outside the patch kernel's class: the tap-major kernel.
+hipError_t launch_conv_f32_no_patch(const ConvArgs &a, hipStream_t s) {
+    const long long N = (long long)a.Nb * a.OH * a.OW;
+    if (a.OC > 64) return launch_conv_f32_tap<128, 128, 64, 64, 2, 3>(a, s);
+    if ((N + 255) / 256 < 256) return launch_conv_f32_tap<64, 64, 32, 32, 2, 4>(a, s);
+    return launch_conv_f32_tap<64, 256, 64, 64, 2, 2>(a, s);
+}
+
+// An explicit schedule of the patch kernels: the tile it names.
+template <typename CFG>
+hipError_t launch_conv_f32_patch(const ConvArgs &a, hipStream_t s) {
+    hipError_t err;
+    return try_patch_f32<CFG>(a, s, &err) ? err : launch_conv_f32_no_patch(a, s);
+}
+
+// Without a schedule, layers of more than a 64x64 tile per CU (default tile
+// 64x112), and large layers of the halo kernels' class, run the kernel with
+// the least time of its fullest CU.  The
 // times are microseconds per 64 channels for 1, 2, ... tiles on that CU
 // (their ratios matter), fitted to 64 to 256 channels, 14 to 64 pixels a side,
 // strides 1 and 2 and batch 4 to 32; past the table its last step repeats.
@@ -2077,62 +2100,64 @@ int patch_f32_per_cu(const ConvArgs &a) {
 // 20x64x56x56 -> 64 at 65.7 (64x416: 60.2), 9x64x57x57 -> 64 at 41.7 (split
 // 64x64 tiles: 33.6), 20x128x28x28 -> 256 at 133 (tap-major 64x128: 107),
 // 30x64x64x64 -> 128 at 227 (tap-major 128x128: 174) and 32x256x22x22 -> 256 at
-// 258 (split 64x64: 204).  Outside the patch kernel's class the tap-major
-// kernel runs.
-template <typename CFG>
-hipError_t launch_conv_f32_patch(const ConvArgs &a, hipStream_t s) {
+// 258 (split 64x64: 204).  False if no kernel of the table takes the layer.
+bool launch_conv_f32_least(const ConvArgs &a, hipStream_t s, hipError_t *err) {
     const long long OHW = (long long)a.OH * a.OW, N = a.Nb * OHW, tm = (a.OC + 63) / 64;
     auto tiles = [&](int bn) { return tm * ((N + bn - 1) / bn); };
     const bool halo_class = halo16_tile_px<1>(a) > 0;
-    hipError_t err;
-    if (CFG::NB == 7 || (halo_class && tiles(208) >= 192)) {
-        const double none = 1e30, c = 64.0 / a.C;
-        auto time_of = [](long long n, const double (&us)[4], double step) {
-            const long long per_cu = (n + 255) / 256;
-            return per_cu <= 4 ? us[per_cu - 1] : us[3] + (double)(per_cu - 4) * step;
-        };
-        auto rounds = [](long long n, int per_cu) { return (double)((n + 256 * per_cu - 1) / (256 * per_cu)); };
-        // halo kernels: their tiles do not cross images
-        auto per_image = [&](int bn) { return tm * a.Nb * ((OHW + bn - 1) / bn); };
-        double h208 = none, h256 = none, h416 = none;
-        if (halo_class) {
-            h208 = time_of(per_image(208), {38.3, 66.0, 100.3, 129.0}, 32);
-            if (halo_eligible(a)) h256 = time_of(per_image(256), {49.5, 85.0, 127.5, 166.5}, 41);
-            if (halo16_tile_px<2>(a) > 0) h416 = rounds(per_image(416), 1) * 60.5;
-        }
-        // patch kernels: a second workgroup on a CU costs half a first one
-        // where LDS holds both
-        const int w64 = patch_f32_per_cu<PatchF32M2>(a), w112 = patch_f32_per_cu<PatchF32M>(a),
-                  w208 = patch_f32_per_cu<PatchF32L>(a);
-        const double one112 = 23 + 6.5 * c;
-        const double p64 = w64 ? rounds(tiles(64), 1) * (11.8 + 4.2 * c) : none;
-        const double p112 = !w112 || tiles(112) > 512   ? none
-                            : w112 == 2 && tiles(112) > 256 ? 36 + 6.3 * c
-                                                            : rounds(tiles(112), 1) * one112;
-        const double p208 = !w208 ? none : w208 == 2 ? rounds(tiles(208), 2) * 67 : rounds(tiles(208), 1) * 45;
-        // tap-major kernels (whole 32-channel steps)
-        const double strided = a.sh > 1 || a.sw > 1 ? 1.15 : 1.0;
-        const double t128 = a.C % 32 ? none : strided * time_of(tiles(128), {33, 53, 69, 94}, 22.3);
-        const double t128x2 =
-            a.C % 32 || a.OC <= 64 ? none
-                                   : strided * time_of((a.OC + 127) / 128 * ((N + 127) / 128), {57, 84, 145, 174}, 43);
-        const double least = std::min({h208, h256, h416, p64, p112, p208, t128, t128x2});
-        if (least < none) {
-            if (least == p64 && try_patch_f32<PatchF32M2>(a, s, &err)) return err;
-            if (least == p112 && try_patch_f32<PatchF32M>(a, s, &err)) return err;
-            if (least == h208) return launch_conv_f32_halo16<2, 1>(a, s);
-            if (least == h256) return launch_conv_f32_halo<2>(a, s);
-            if (least == h416) return launch_conv_f32_halo16<2, 2>(a, s);
-            if (least == p208 && try_patch_f32<PatchF32L>(a, s, &err)) return err;
-            if (least == t128) return launch_conv_f32_tap<64, 128, 32, 64, 2, 3>(a, s);
-            if (least == t128x2) return launch_conv_f32_tap<128, 128, 64, 64, 2, 3>(a, s);
-        }
+    const double none = 1e30, c = 64.0 / a.C;
+    auto time_of = [](long long n, const double (&us)[4], double step) {
+        const long long per_cu = (n + 255) / 256;
+        return per_cu <= 4 ? us[per_cu - 1] : us[3] + (double)(per_cu - 4) * step;
+    };
+    auto rounds = [](long long n, int per_cu) { return (double)((n + 256 * per_cu - 1) / (256 * per_cu)); };
+    // halo kernels: their tiles do not cross images
+    auto per_image = [&](int bn) { return tm * a.Nb * ((OHW + bn - 1) / bn); };
+    double h208 = none, h256 = none, h416 = none;
+    if (halo_class) {
+        h208 = time_of(per_image(208), {38.3, 66.0, 100.3, 129.0}, 32);
+        if (halo_eligible(a)) h256 = time_of(per_image(256), {49.5, 85.0, 127.5, 166.5}, 41);
+        if (halo16_tile_px<2>(a) > 0) h416 = rounds(per_image(416), 1) * 60.5;
     }
+    // patch kernels: a second workgroup on a CU costs half a first one
+    // where LDS holds both
+    const int w64 = patch_f32_per_cu<PatchF32M2>(a), w112 = patch_f32_per_cu<PatchF32M>(a),
+              w208 = patch_f32_per_cu<PatchF32L>(a);
+    const double one112 = 23 + 6.5 * c;
+    const double p64 = w64 ? rounds(tiles(64), 1) * (11.8 + 4.2 * c) : none;
+    const double p112 = !w112 || tiles(112) > 512   ? none
+                        : w112 == 2 && tiles(112) > 256 ? 36 + 6.3 * c
+                                                        : rounds(tiles(112), 1) * one112;
+    const double p208 = !w208 ? none : w208 == 2 ? rounds(tiles(208), 2) * 67 : rounds(tiles(208), 1) * 45;
+    // tap-major kernels (whole 32-channel steps)
+    const double strided = a.sh > 1 || a.sw > 1 ? 1.15 : 1.0;
+    const double t128 = a.C % 32 ? none : strided * time_of(tiles(128), {33, 53, 69, 94}, 22.3);
+    const double t128x2 =
+        a.C % 32 || a.OC <= 64 ? none
+                               : strided * time_of((a.OC + 127) / 128 * ((N + 127) / 128), {57, 84, 145, 174}, 43);
+    const double least = std::min({h208, h256, h416, p64, p112, p208, t128, t128x2});
+    if (least == none) return false;
+    if (least == p64) return try_patch_f32<PatchF32M2>(a, s, err);
+    if (least == p112) return try_patch_f32<PatchF32M>(a, s, err);
+    if (least == p208) return try_patch_f32<PatchF32L>(a, s, err);
+    if (least == h208) *err = launch_conv_f32_halo16<2, 1>(a, s);
+    else if (least == h256) *err = launch_conv_f32_halo<2>(a, s);
+    else if (least == h416) *err = launch_conv_f32_halo16<2, 2>(a, s);
+    else if (least == t128) *err = launch_conv_f32_tap<64, 128, 32, 64, 2, 3>(a, s);
+    else *err = launch_conv_f32_tap<128, 128, 64, 64, 2, 3>(a, s);
+    return true;
+}
+
+// The default schedule's patch tile, without an explicit one.
+template <typename CFG>
+hipError_t launch_conv_f32_patch_by_shape(const ConvArgs &a, hipStream_t s) {
+    hipError_t err;
+    const bool large = CFG::NB == 7 || (halo16_tile_px<1>(a) > 0 && (a.OC + 63) / 64 *
+                       (((long long)a.Nb * a.OH * a.OW + 207) / 208) >= 192);
+    if (large && launch_conv_f32_least(a, s, &err)) return err;
     if (try_patch_f32<CFG>(a, s, &err) || try_patch_f32<PatchF32N>(a, s, &err) || try_patch_f32<PatchF32M>(a, s, &err))
         return err;
-    if (a.OC > 64) return launch_conv_f32_tap<128, 128, 64, 64, 2, 3>(a, s);
-    if (tiles(256) < 256) return launch_conv_f32_tap<64, 64, 32, 32, 2, 4>(a, s);
-    return launch_conv_f32_tap<64, 256, 64, 64, 2, 2>(a, s);
+    return launch_conv_f32_no_patch(a, s);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int MI, int PAD>
@@ -2178,7 +2203,8 @@ hipError_t launch_conv_f32(const ConvArgs &a, hipStream_t s) {
 #define XTC_CONV_F32_PATCH_INSTANCE(CFG, STAGES)                                              \
     ConvInstance {                                                                            \
         make_sched(CFG::BM, CFG::BN, 8, 16, CFG::BN, 16, 16, 4, STAGES, 0, 0, 2),              \
-            &launch_conv_f32_patch<CFG>, &occupancy_of<&conv2d_f32_patch_kernel<CFG, 10>, CFG::NT, 0> \
+            &launch_conv_f32_patch<CFG>, &occupancy_of<&conv2d_f32_patch_kernel<CFG, 10>, CFG::NT, 0>, \
+            &launch_conv_f32_patch_by_shape<CFG>                                              \
     }
 
 const ConvInstance kConvInstances[] = {

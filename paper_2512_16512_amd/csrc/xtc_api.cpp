@@ -548,7 +548,8 @@ xtc_status conv_impl(int64_t N, int64_t C, int64_t H, int64_t W, int64_t OC, int
     a.raster = s.raster; a.xcd_remap = s.xcd_remap;
     a.relu = relu;
     a.tile_px = 0;
-    return hip_status(inst->launch(a, static_cast<hipStream_t>(stream)));
+    const ConvLaunch fn = !sched && inst->by_shape ? inst->by_shape : inst->launch;
+    return hip_status(fn(a, static_cast<hipStream_t>(stream)));
 }
 
 }  // namespace

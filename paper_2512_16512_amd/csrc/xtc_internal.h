@@ -86,6 +86,9 @@ struct ConvInstance {
     xtc_sched sched;
     ConvLaunch launch;
     OccupancyFn occupancy;  // of the instance's own kernel (not its fallbacks)
+    // what runs where the instance is the default schedule's and the caller
+    // gave none: a kernel chosen by the layer's shape (null: `launch`)
+    ConvLaunch by_shape = nullptr;
 };
 
 const GemmInstance *gemm_f32_instances(int *count);

@@ -305,8 +305,11 @@ def test_conv_bf16_patch_edges(x, N, C, H, W, OC, stride, pad):
     (4, 16, 3, 3, 17, (3, 3), (2, 2)),     # rows between images advance by less than the stride
     (1, 72, 33, 57, 31, (1, 1), (3, 3)),   # padding of a whole kernel
     (2, 16, 1, 1, 40, (1, 1), (1, 1)),     # a single pixel
-    (9, 8, 33, 33, 128, (1, 1), (1, 1)),   # more than two 112-pixel tiles per CU
+    (9, 8, 33, 33, 128, (1, 1), (1, 1)),   # 176 tiles of 64x112, two output channel tiles
     (26, 8, 51, 52, 64, (1, 1), (1, 1)),   # the balanced halo kernel's class
+    (2, 16, 10, 200, 40, (1, 1), (1, 1)),  # a patch of 19 blocks (64x112), past the smaller kernel's 10
+    (1, 8, 5, 380, 24, (1, 1), (1, 1)),    # the most blocks a patch may have, 24
+    (3, 8, 40, 40, 48, (3, 3), (1, 1)),    # stride 3: 18 blocks (64x112), across images
 ])
 def test_conv_f32_patch_edges(x, N, C, H, W, OC, stride, pad):
     """The fp32 patch kernels (every tile and split) where their patch can go
@@ -334,11 +337,62 @@ def test_conv_f32_patch_edges(x, N, C, H, W, OC, stride, pad):
             assert np.array_equal(to_host(Yd), ref), (ox, s)
 
 
+@pytest.mark.parametrize("N,C,H,W,OC", [(60, 64, 28, 28, 64), (26, 32, 51, 52, 64)])
+def test_explicit_patch_schedule_runs_the_tile_it_names(x, N, C, H, W, OC):
+    """A layer large enough that the default choice goes by shape, outside and
+    inside the halo kernels' class: under an explicit schedule of the patch
+    kernels every image is summed as it is alone, bit for bit, so that the batch
+    does not change the kernel."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X = torch.randn(N, C, H, W, device="cuda", generator=g)
+    Wt = torch.randn(OC, C, 3, 3, device="cuda", generator=g)
+    scheds = [s for s in x.xtc_sched_list(x.XTC_OP_CONV2D, x.XTC_F32) if s.k_order == 2 and s.lds_pad == 0]
+    assert {(s.block_m, s.block_n) for s in scheds} == {(16, 32), (64, 32), (64, 64), (64, 112)}
+    for s in scheds:
+        say("explicit patch", (N, C, H, W, OC), s)
+        got = x.conv2d_nchw(X, Wt, pad=1, sched=s)
+        one = x.conv2d_nchw(X[N - 2:N - 1].contiguous(), Wt, pad=1, sched=s)
+        torch.cuda.synchronize()
+        assert torch.equal(got[N - 2:N - 1], one), s
+
+
+@pytest.mark.parametrize("N,C,H,W,OC,stride", [
+    (21, 128, 28, 28, 64, 1),    # 147 tiles: one workgroup per CU
+    (30, 64, 28, 28, 128, 1),    # 420 tiles: two per CU
+    (30, 64, 56, 56, 64, 2),     # stride 2: a patch of 11 blocks, past the smaller kernel's 10
+    (48, 64, 56, 56, 64, 2),     # 64x208 tiles, which reduce in the same order: 18 blocks
+])
+def test_conv_f32_default_runs_unsplit_patch_tiles(x, N, C, H, W, OC, stride):
+    """Layers whose least time is the 64x112 or 64x208 patch tile's, all with
+    tiles across images: bit-exact on small integers, fused relu too, and summed
+    in those tiles' order (the 64x64 one splits the reduction, the tap-major
+    kernel takes it tap by tap) on random values."""
+    import torch
+    X, Wt = xi.small_int_f32(45, (N, C, H, W)), xi.small_int_f32(46, (OC, C, 3, 3))
+    ref = oracle.conv2d(X, Wt, stride=stride, pad=1)
+    say("default 64x112", (N, C, H, W, OC, stride))
+    Xd, Wd = to_dev(X), to_dev(Wt)
+    assert np.array_equal(to_host(x.conv2d_nchw(Xd, Wd, stride=stride, pad=1)), ref)
+    assert np.array_equal(to_host(x.conv2d_nchw(Xd, Wd, stride=stride, pad=1, relu=True)), oracle.relu(ref))
+    g = torch.Generator(device="cuda").manual_seed(6)
+    Xd, Wd = torch.randn(Xd.shape, device="cuda", generator=g), torch.randn(Wd.shape, device="cuda", generator=g)
+    patch = {s.block_n: s for s in x.xtc_sched_list(x.XTC_OP_CONV2D, x.XTC_F32)
+             if s.k_order == 2 and s.lds_pad == 0 and s.block_m == 64}
+    got = x.conv2d_nchw(Xd, Wd, stride=stride, pad=1)
+    same = x.conv2d_nchw(Xd, Wd, stride=stride, pad=1, sched=patch[112])
+    split = x.conv2d_nchw(Xd, Wd, stride=stride, pad=1, sched=patch[64])
+    torch.cuda.synchronize()
+    assert torch.equal(got, same) and not torch.equal(got, split)
+
+
 @pytest.mark.parametrize("dtype,N,C,H,W,OC,R,stride,pad", [
-    ("f32", 9, 16, 57, 57, 64, 3, 1, 1),    # halo class: two split 64x64 patch tiles per CU
+    ("f32", 9, 64, 57, 57, 64, 3, 1, 1),    # halo class: two split 64x64 patch tiles per CU
+    ("f32", 9, 16, 57, 57, 64, 3, 1, 1),    # halo class, few channels: 208-pixel halo tiles
     ("f32", 20, 16, 56, 56, 64, 3, 1, 1),   # halo class: 416-pixel tiles
     ("f32", 19, 16, 56, 56, 128, 3, 1, 1),  # halo class: 64x256 tiles, two per CU
-    ("f32", 37, 8, 28, 28, 64, 3, 1, 1),    # outside it: two split 64x64 patch tiles per CU
+    ("f32", 37, 8, 28, 28, 64, 3, 1, 1),    # outside it, one stage: 208-pixel patch tiles
+    ("f32", 37, 64, 28, 28, 64, 3, 1, 1),   # outside it: two split 64x64 patch tiles per CU
     ("f32", 28, 8, 28, 28, 256, 3, 1, 1),   # outside it: 208-pixel patch tiles
     ("f32", 20, 32, 28, 28, 256, 3, 1, 1),  # outside it: tap-major 64x128 tiles
     ("bf16", 7, 3, 219, 221, 32, 3, 2, 1),  # gather: past one round of 64x64 tiles
