@@ -254,7 +254,13 @@ struct F32DmaCfg {
 // waves and one wave's LDS and barrier waits overlap another's matrix
 // instructions.  At the end the groups' accumulators are added through LDS
 // in the fixed order 0, 1, ..., KSW-1 (deterministic results).
-template <int BM, int BN, int BK, int WM, int WN, int MI_, int STAGES, int KSW = 1, bool TAIL = false>
+//
+// SETS > 1: a wave adds its fragment sets to SETS accumulators in turn, joined
+// at the end, so that a tile of KSW groups has KSW * SETS partial sums, each of
+// as many fewer products: the error against 64 bits is that of the
+// register-fed kernels' 8 (64x32 tiles, two groups, K = 1384: 4.7e-7 with one
+// set, 2.4e-7 with four) for the registers of a small wave tile.
+template <int BM, int BN, int BK, int WM, int WN, int MI_, int STAGES, int KSW = 1, bool TAIL = false, int SETS = 1>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64 * KSW)
 gemm_f32_dma_kernel(GemmArgs p) {
     typedef F32DmaCfg<BM, BN, BK, WM, WN, MI_, STAGES> G;
@@ -334,13 +340,17 @@ gemm_f32_dma_kernel(GemmArgs p) {
     for (int j = 0; j < G::TN; ++j)
         b_off[j] = (4 * lgrp * BN + ((wn * WN + j * MI + lrow) ^ (4 * G::SWB * lgrp))) * 4;
 
-    typename MF::acc_t acc[G::TM][G::TN];
+    static_assert(SETS == 1 || G::NS % SETS == 0, "every set takes the same share of a stage");
+    typename MF::acc_t accs[SETS][G::TM][G::TN];
 #pragma unroll
-    for (int i = 0; i < G::TM; ++i)
+    for (int h = 0; h < SETS; ++h)
 #pragma unroll
-        for (int j = 0; j < G::TN; ++j)
+        for (int i = 0; i < G::TM; ++i)
 #pragma unroll
-            for (int r = 0; r < MF::NACC; ++r) acc[i][j][r] = 0.f;
+            for (int j = 0; j < G::TN; ++j)
+#pragma unroll
+                for (int r = 0; r < MF::NACC; ++r) accs[h][i][j][r] = 0.f;
+    auto &acc = accs[0];
 
     f32x4 af[2][G::TM];
     float bfr[2][G::TN][4];
@@ -370,27 +380,29 @@ gemm_f32_dma_kernel(GemmArgs p) {
                 bfr[buf][j][s] = *reinterpret_cast<const float *>(Bs + (kk + s) * G::RB + b_off[j]);
     };
 
-    auto mfmas = [&](int buf) {
+    auto mfmas = [&](int step) {
+        const int buf = step & 1;
+        auto &a = accs[step % SETS];
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
             for (int i = 0; i < G::TM; ++i)
 #pragma unroll
-                for (int j = 0; j < G::TN; ++j)
-                    acc[i][j] = MF::mma(af[buf][i][s], bfr[buf][j][s], acc[i][j]);
+                for (int j = 0; j < G::TN; ++j) a[i][j] = MF::mma(af[buf][i][s], bfr[buf][j][s], a[i][j]);
     };
 
     // The last fragment set of a stage: its MFMAs with the copies of the
     // stage STAGES ahead spread between them (copies issued all at once by
     // every wave right after the barrier queue at the texture unit and
     // stall the issuing waves); the fences keep the order.
-    auto mfmas_with_copies = [&](int buf, int st) {
+    auto mfmas_with_copies = [&](int st) {
+        constexpr int buf = (G::NS - 1) & 1, NM = 4 * G::TM * G::TN;
         const unsigned base = smem_base + st * G::STAGE_BYTES;
-        constexpr int NM = 4 * G::TM * G::TN;
+        auto &a = accs[(G::NS - 1) % SETS];
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
             const int s = m / (G::TM * G::TN), i = (m / G::TN) % G::TM, j = m % G::TN;
-            acc[i][j] = MF::mma(af[buf][i][s], bfr[buf][j][s], acc[i][j]);
+            a[i][j] = MF::mma(af[buf][i][s], bfr[buf][j][s], a[i][j]);
             const int q0 = m * G::LOADS / NM, q1 = (m + 1) * G::LOADS / NM;
             if (q1 > q0) {
                 __builtin_amdgcn_sched_barrier(0);
@@ -426,7 +438,7 @@ gemm_f32_dma_kernel(GemmArgs p) {
 #pragma unroll
         for (int s = 0; s + 1 < G::NS; ++s) {
             load_frags(kt, st, s + 1, (s + 1) & 1);
-            mfmas(s & 1);
+            mfmas(s);
             // one MFMA, then one LDS read of the next fragment set
 #pragma unroll
             for (int m = 0; m < 4 * G::TM * G::TN; ++m) {
@@ -438,9 +450,19 @@ gemm_f32_dma_kernel(GemmArgs p) {
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         load_frags(kt + 1, (kt + 1) % STAGES, 0, 0);
-        mfmas_with_copies((G::NS - 1) & 1, st);
+        mfmas_with_copies(st);
     }
     wait_vmcnt<0>();  // no copy may still be writing LDS when the workgroup ends
+
+    // the sets, in pairs
+#pragma unroll
+    for (int d = 1; d < SETS; d *= 2)
+#pragma unroll
+        for (int h = 0; h + d < SETS; h += 2 * d)
+#pragma unroll
+            for (int i = 0; i < G::TM; ++i)
+#pragma unroll
+                for (int j = 0; j < G::TN; ++j) accs[h][i][j] += accs[h + d][i][j];
 
     if constexpr (KSW > 1) {
         // groups 1 .. KSW-1 leave their sums in LDS (each lane its own
@@ -489,15 +511,27 @@ gemm_f32_dma_kernel(GemmArgs p) {
         }
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int MI, int STAGES, int KSW = 1, bool TAIL = false>
+template <int BM, int BN, int BK, int WM, int WN, int MI, int STAGES, int KSW = 1, bool TAIL = false, int SETS = 1>
 hipError_t launch_f32_dma(const GemmArgs &a, hipStream_t s) {
     typedef F32DmaCfg<BM, BN, BK, WM, WN, MI, STAGES> G;
     const unsigned tiles = (unsigned)(((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN));
     GemmArgs args = a;
     void *kargs[] = {&args};
     return hipLaunchKernel(
-        reinterpret_cast<const void *>(&gemm_f32_dma_kernel<BM, BN, BK, WM, WN, MI, STAGES, KSW, TAIL>),
+        reinterpret_cast<const void *>(&gemm_f32_dma_kernel<BM, BN, BK, WM, WN, MI, STAGES, KSW, TAIL, SETS>),
         dim3(tiles, (unsigned)a.batch), dim3(G::NT * KSW), kargs, 0, s);
+}
+
+// 64x32 tiles in two groups.  With fewer than half a 64x64 tile per CU the
+// register-fed kernels would otherwise run, whose four or eight partial sums
+// it matches with four accumulators per wave; they cost 2-4% of the time, so
+// larger products, whose other tiles have one or two sums, take one
+// (1531x1021x2047: 64.5 us, 65.7 with four).
+template <bool TAIL>
+hipError_t launch_f32_fine(const GemmArgs &a, hipStream_t s) {
+    const long long tiles = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch;
+    return tiles < 128 ? launch_f32_dma<64, 32, 32, 32, 32, 32, 2, 2, TAIL, 4>(a, s)
+                       : launch_f32_dma<64, 32, 32, 32, 32, 32, 2, 2, TAIL, 1>(a, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -740,7 +774,9 @@ const GemmInstance kF32Instances[] = {
     XTC_F32_DMA_KSW_INSTANCE(64, 64, 32, 32, 32, 2, 2),   // two K groups of four 32x32 waves
     XTC_F32_DMA_KSW_INSTANCE(64, 64, 32, 32, 32, 2, 4),
     XTC_F32_DMA_INSTANCE(128, 64, 32, 64, 32, 2),
-    XTC_F32_DMA_KSW_INSTANCE(64, 32, 32, 32, 32, 2, 2),   // finer tiles, so that the CUs share them evenly
+    GemmInstance{make_sched(64, 32, 32, 32, 32, 32, 32, 2, 2, -1, 0, 0, 2),  // finer tiles, so that the CUs share them evenly
+                 &launch_f32_fine<false>, &launch_f32_fine<true>, kWholeK,
+                 &occupancy_of<&gemm_f32_dma_kernel<64, 32, 32, 32, 32, 32, 2, 2>, 256, 0>},
     XTC_F32_INSTANCE(128, 128, 32, 64, 64, 32, 4),
     XTC_F32_INSTANCE(128, 128, 16, 64, 64, 32, 4),
     XTC_F32_INSTANCE(64, 64, 32, 32, 32, 32, 4),     // small problems: more tiles

@@ -174,7 +174,10 @@ void default_matmul(xtc_dtype dt, int64_t M, int64_t N, int64_t K, int64_t batch
                 out->raster = 4;
             }
             return;
-        } else if (tiles(64, 64) >= cus / 2 || tiles(64, 32) >= 160) {
+        } else if (tiles(64, 64) >= cus / 2 || (tiles(64, 32) >= 160 && (M < N ? M : N) > 32)) {
+            // (narrow operands below half a 64x64 tile per CU leave half of a
+            // 64x32 tile empty: 16x5120x1024 13.6 us, 8.0 with 16x16
+            // register-fed tiles; 64x5200x1024 14.2 and 19.5)
             // The CU with the most tiles sets the time: ceil(tiles / 256)
             // tiles of block_m * block_n work at the rate the kernel reaches
             // with that many of its workgroups on a CU.  The rates (shares of

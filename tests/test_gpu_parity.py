@@ -234,6 +234,26 @@ def test_conv_small_int_exact_every_instance(x, shape):
             assert np.array_equal(got, ref), "conv %s %s: not bit-exact" % (shape, s)
 
 
+@pytest.mark.parametrize("M,N,K", [(608, 520, 1384), (624, 720, 824), (517, 769, 1819), (92, 3752, 1072)])
+def test_f32_split_tiles_sum_as_finely_as_the_register_fed_ones(x, M, N, K):
+    """Products with too few tiles for the CUs: the default's error against 64
+    bits is that of the register-fed kernel that adds eight partial sums. With
+    the same number of sums the ratio is 1 but for the order inside them (a few
+    percent over so many outputs); half as many would give 1.4."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(3)
+    a = torch.randn(M, K, device="cuda", generator=g)
+    b = torch.randn(K, N, device="cuda", generator=g)
+    exact = a.double() @ b.double()
+
+    def err(s):
+        say("f32 error", (M, N, K), s)
+        return float((x.matmul(a, b, sched=s).double() - exact).norm() / exact.norm())
+
+    eight = [s for s in x.xtc_sched_list(x.XTC_OP_MATMUL, x.XTC_F32) if (s.block_m, s.block_n, s.k_split) == (32, 32, 8)]
+    assert err(None) <= 1.15 * err(eight[0])
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (16, 32, 32), (17, 33, 33), (5, 31, 7), (64, 32, 128), (65, 66, 390),
                                    (3, 300, 1030), (130, 2, 96), (129, 127, 63), (127, 253, 129), (33, 126, 64)])
 @pytest.mark.parametrize("oa,ob,pa,pb", [(0, 0, 0, 0), (2, 4, 2, 6), (1, 0, 0, 1), (3, 7, 1, 3)])
