@@ -993,6 +993,53 @@ hipError_t launch_bf16(const GemmArgs &a, hipStream_t s) {
         dim3(tiles, (unsigned)a.batch), dim3(G::NT), kargs, 0, s);
 }
 
+// Rows at any 2-byte boundary, for the direct-to-LDS instances.  The odd-row
+// kernel reduces faster, but its tiles of 126 columns write C in pieces of
+// lines, and 17 of them cover what 16 of 128 columns do: short reductions stay
+// with the register-staged kernel of the same tile.  Both times in us, from
+// rounds of 256 tiles (28 shapes from 777x1500 to 8192^2, K = 1 to 1025; within
+// 15%): 4096x4096x1 28.4 with the odd-row kernel, 14.3; x65 31.6, 18.1; x1025
+// 75.6, 75.7; 2048x2047x129 15.0, 12.0; x513 21.3, 24.6; 1531x1021x65 7.3, 6.1;
+// x257 8.8, 9.8.
+template <int BM>
+hipError_t launch_bf16_unaligned(const GemmArgs &a, hipStream_t s) {
+    auto rounds = [&](int bm, int bn) {
+        const long long t = (long long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.batch;
+        return (double)((t + 255) / 256);
+    };
+    if constexpr (BM == 64) {
+        // (of the register-staged tiles the small one up to three per CU:
+        // 1001x3003x1 6.4 us, 7.0 with 64x128; 1900x2040x1 8.0, 7.2; two of the
+        // others share a CU, so the 126 columns cost a round where they need a
+        // third: 3000x1280x129 14.1, 11.3; x385 18.7, 19.1)
+        const bool third = rounds(64, 126) > 2 && rounds(64, 128) <= 2;
+        if (a.K > (third ? 320 : 128)) return launch_bf16_odd<64, 32>(a, s);
+        return rounds(64, 64) <= 3 ? launch_bf16<64, 64, 64, 32, 32, 32, 8, false>(a, s)
+                                   : launch_bf16<64, 128, 64, 32, 64, 32, 8, false>(a, s);
+    } else {
+        const double n = rounds(128, 126), r = rounds(BM, BM);
+        const double odd = n == 1 ? 10.5 + .0135 * a.K : 3 + n * (5 + .009 * a.K);
+        if constexpr (BM == 256) {
+            if (1 + r * (11 + .0605 * a.K) < odd) return launch_bf16<256, 256, 32, 128, 64, 32, 8, false>(a, s);
+        } else {
+            if (4 + 3 * r + a.K * (r <= 2 ? .04 : r == 3 ? .053 : .021 * r) < odd)
+                return launch_bf16<128, 128, 32, 64, 64, 32, 8, false>(a, s);
+        }
+        return launch_bf16_odd<128, 64>(a, s);
+    }
+}
+
+// The same for the register-fed instances: 2-byte loads of B against two
+// 64-k steps of the register-staged kernel (101x203x33 4.3 us, 3.8; x65 4.3,
+// 4.6), or three where its tiles outnumber the CUs (40000x3x129 11.1, 8.1;
+// 31x20000x257 9.2, 9.2; 1000000x1x16 128, 58).
+template <int TM, int KS, int D>
+hipError_t launch_bf16_ksplit_odd(const GemmArgs &a, hipStream_t s) {
+    const long long tiles = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch;
+    if (a.K <= (tiles > 256 ? 192 : 64)) return launch_bf16<64, 64, 64, 32, 32, 32, 8, false>(a, s);
+    return launch_bf16_ksplit<TM, KS, D, true>(a, s);
+}
+
 #define XTC_BF16_INSTANCE(BM, BN, BK, WM, WN, MI, PAD)                                        \
     GemmInstance {                                                                            \
         make_sched(BM, BN, BK, WM, WN, MI, MI, (MI == 32 ? 16 : 32), 2, PAD, 0),               \
@@ -1005,12 +1052,12 @@ hipError_t launch_bf16(const GemmArgs &a, hipStream_t s) {
 // Direct-to-LDS ring (lds_pad = -1: swizzled, unpadded LDS rows), b128 A
 // reads, MFMA / LDS-read interleaving.  Unaligned or non-16-byte-granular
 // operands run the kernel for rows at any 2-byte boundary, with 128- or
-// 64-row tiles.
+// 64-row tiles, or for short reductions the register-staged one.
 #define XTC_BF16_DMA_INSTANCE(BM, BN, BK, WM, WN, MI, STAGES)                                 \
     GemmInstance {                                                                            \
         make_sched(BM, BN, BK, WM, WN, MI, MI, (MI == 32 ? 16 : 32), STAGES, -1, 0),           \
             &launch_bf16_dma<BM, BN, BK, WM, WN, MI, STAGES>,                                 \
-            &launch_bf16_odd<(BM >= 128 ? 128 : 64), (BM >= 128 ? 64 : 32)>, kWholeChunks,    \
+            &launch_bf16_unaligned<BM>, kWholeChunks,                                         \
             &occupancy_of<&gemm_bf16_dma_kernel<BM, BN, BK, WM, WN, MI, STAGES>,              \
                           (BM / WM) * (BN / WN) * 64, 0>                                      \
     }
@@ -1020,7 +1067,7 @@ hipError_t launch_bf16(const GemmArgs &a, hipStream_t s) {
 #define XTC_BF16_KSPLIT_INSTANCE(TM, KS, D)                                                   \
     GemmInstance {                                                                            \
         make_sched(16 * TM, 32, 32, 16 * TM, 32, 16, 16, 32, 0, 0, 0, 0, KS),                  \
-            &launch_bf16_ksplit<TM, KS, D, false>, &launch_bf16_ksplit<TM, KS, D, true>,      \
+            &launch_bf16_ksplit<TM, KS, D, false>, &launch_bf16_ksplit_odd<TM, KS, D>,        \
             kRowsDword, &occupancy_of<&gemm_bf16_ksplit_kernel<TM, KS, D, false>, KS * 64, 0> \
     }
 

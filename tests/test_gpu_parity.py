@@ -255,12 +255,14 @@ def test_f32_split_tiles_sum_as_finely_as_the_register_fed_ones(x, M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (16, 32, 32), (17, 33, 33), (5, 31, 7), (64, 32, 128), (65, 66, 390),
-                                   (3, 300, 1030), (130, 2, 96), (129, 127, 63), (127, 253, 129), (33, 126, 64)])
+                                   (3, 300, 1030), (130, 2, 96), (129, 127, 63), (127, 253, 129), (33, 126, 64),
+                                   (129, 127, 191), (33, 253, 256), (257, 126, 193), (17, 31, 65)])
 @pytest.mark.parametrize("oa,ob,pa,pb", [(0, 0, 0, 0), (2, 4, 2, 6), (1, 0, 0, 1), (3, 7, 1, 3)])
 def test_bf16_row_alignment_and_tile_edges(x, M, N, K, oa, ob, pa, pb):
     """The bf16 register-fed reduction-split tiles and the direct-to-LDS ones
-    (their form for rows at any 2-byte boundary: 126 columns a tile, 64 k a
-    step) at the edges of their tiles and k-steps, with operands ``oa``/``ob`` elements past a 16-byte boundary
+    (their forms for rows at any 2-byte boundary: 126 columns a tile, 64 k a
+    step, past 64 and 128 k, and the register-staged kernel before) at the edges
+    of their tiles and k-steps, with operands ``oa``/``ob`` elements past a 16-byte boundary
     and rows padded by ``pa``/``pb``: 4-byte aligned rows and rows at any
     2-byte boundary.  Infinities around and between the rows must not reach
     the result.  Bit-exact (small integers)."""
