@@ -1221,8 +1221,8 @@ conv2d_bf16_rows_kernel(ConvArgs p) {
         soff[s4] = (oc < OC) & (px_rd < OW) ? (unsigned)((((img * OC + oc) * OH + oh_a) * OW + px_rd) * 4)
                                              : (unsigned)kOOB;
     }
-    // relu as a lower bound (-inf: none); accumulators start at +0, so a
-    // -0 result, which the bound would not keep, cannot occur
+    // relu as a lower bound (-inf: none), by comparison: a maximum would turn
+    // a NaN into the bound
     const float lo = p.relu ? 0.f : -__builtin_inff();
     // A step's outputs are stored during the next step, one store per
     // k-step group, and its row loads are spread the same way: with one
@@ -1321,7 +1321,7 @@ conv2d_bf16_rows_kernel(ConvArgs p) {
             for (int i = 0; i < 4; ++i) {
                 f32x4 v;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaxf(acc[o][4 * i + r], lo);
+                for (int r = 0; r < 4; ++r) v[r] = acc[o][4 * i + r] < lo ? lo : acc[o][4 * i + r];
                 *reinterpret_cast<f32x4 *>(stg + l32 * 128 + (((2 * i + lg) ^ (l32 & 7)) << 4)) = v;
             }
             const bool rok = RO * st + o < rows;   // uniform

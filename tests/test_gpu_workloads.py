@@ -207,6 +207,30 @@ def test_graph_replay_matches_eager(x):
     assert_parity(to_host(c), ref, "f32", "graph replay")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,C,H,W,OC", [(2, 64, 9, 56, 40), (1, 16, 12, 20, 70)])
+def test_conv_relu_keeps_nan_and_infinities_in_every_instance(x, dtype, N, C, H, W, OC):
+    """A NaN and both infinities in the input reach the outputs that read them,
+    with and without relu (a NaN stays NaN), and no others. Positive weights, so
+    that the infinities keep their signs."""
+    X = xi.small_int_f32(13, (N, C, H, W))
+    Wt = np.abs(xi.small_int_f32(14, (OC, C, 3, 3))) + 1
+    X[0, 3, 4, 5], X[0, 7, 1, 1], X[N - 1, 2, 7, 15] = np.nan, np.inf, -np.inf
+    ref = oracle.conv2d(X, Wt, stride=1, pad=1)
+    assert np.isnan(ref).sum() == 9 * OC and np.isinf(ref).sum() == 18 * OC
+    if dtype == "bf16":
+        bits = xi.f32_to_bf16_bits(np.nan_to_num(X, nan=0.0))
+        bits[np.isnan(X)] = 0x7FC0
+        X, Wt = bits, xi.f32_to_bf16_bits(Wt)
+    code = x.XTC_F32 if dtype == "f32" else x.XTC_BF16
+    Xd, Wd = to_dev(X), to_dev(Wt)
+    for s in x.xtc_sched_list(x.XTC_OP_CONV2D, code) + [None]:
+        for relu in (False, True):
+            say("conv non-finite", dtype, (N, C, H, W, OC), relu, s)
+            got = to_host(x.conv2d_nchw(Xd, Wd, stride=1, pad=1, sched=s, relu=relu))
+            assert np.array_equal(got, oracle.relu(ref) if relu else ref, equal_nan=True), s
+
+
 def test_every_instance_fits_on_a_cu(x):
     # the occupancy query: every compiled instance has at least one resident
     # workgroup per CU at the reduction lengths it is used with
