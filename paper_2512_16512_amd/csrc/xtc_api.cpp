@@ -233,14 +233,15 @@ void default_matmul(xtc_dtype dt, int64_t M, int64_t N, int64_t K, int64_t batch
         // tiles win: 1024^3 10.7 against 13.1) or one operand is narrow
         // (10000x30x2000: 70.7, 13.0; 32768x16x4096: 48.2, 46.4); else the
         // direct-to-LDS tiles from 256x256 down to 64x128.
-        if (tiles(64, 32) <= cus || (M < N ? M : N) <= 32) {
-            // Of the three, the tile with the least work on the fullest CU: a
-            // k-step of 16*TM rows costs TM row loads and 8 column loads,
-            // about 56, 72 and 104 clocks (the order it gives matches the
-            // measured one on 14 of 15 shapes, and is 17% off on the other).
-            const int64_t c16 = sat_mul(cdiv(tiles(16, 32), cus), 56), c32 = sat_mul(cdiv(tiles(32, 32), cus), 72),
-                          c64 = sat_mul(cdiv(tiles(64, 32), cus), 104);
-            const int bm = c16 <= c32 && c16 <= c64 ? 16 : c32 <= c64 ? 32 : 64;
+        // Of the three, the tile with the least work on the fullest CU: a
+        // k-step of 16*TM rows costs TM row loads and 8 column loads,
+        // about 56, 72 and 104 clocks (the order it gives matches the
+        // measured one on 14 of 15 shapes, and is 17% off on the other).
+        const int64_t c16 = sat_mul(cdiv(tiles(16, 32), cus), 56), c32 = sat_mul(cdiv(tiles(32, 32), cus), 72),
+                      c64 = sat_mul(cdiv(tiles(64, 32), cus), 104);
+        const int bm = c16 <= c32 && c16 <= c64 ? 16 : c32 <= c64 ? 32 : 64;
+        // (a launch has less than 2^32 threads, 256 per tile)
+        if ((tiles(64, 32) <= cus || (M < N ? M : N) <= 32) && tiles(bm, 32) < int64_t(1) << 24) {
             *out = make_sched(bm, 32, 32, bm, 32, 16, 16, 32, 0, 0, 0, 0, 4);
         } else if (tiles(256, 256) >= cus && M > 128)
             *out = make_sched(256, 256, 32, 128, 64, 32, 32, 16, 4, -1, 0);

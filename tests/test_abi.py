@@ -218,6 +218,23 @@ def test_default_schedules_are_compiled(x):
                 assert x.xtc_sched_check(op, dt, s) == 0
 
 
+@pytest.mark.parametrize("dt,elt", [(0, 4), (1, 2)])
+def test_default_matmul_launches_fit_the_largest_extents(x, dt, elt):
+    """A launch has less than 2^32 threads: with the largest outputs the checks
+    accept, the default tile leaves room for it."""
+    span = 0x7FFFFFD0
+    for K in (0, 1, 2, 3, 8, 64, 512, 4096):
+        for M in (1, 2, 16, 17, 32, 33, 64, 129):
+            N = min(span // 4 // M, span // elt // max(K, 1))
+            for m, n in ((M, N), (N, M)):
+                if m * K * elt > span or K * n * elt > span:
+                    continue
+                s = x.xtc_default_schedule(0, dt, m, n, K)
+                tiles = -(-m // s.block_m) * -(-n // s.block_n)
+                threads = 64 * (s.block_m // s.wave_m) * (s.block_n // s.wave_n) * s.k_split
+                assert tiles * threads < 2**32, (m, n, K, s)
+
+
 def test_no_hip_error_recorded_by_validation(x):
     assert x.xtc_last_hip_error() == 0
     assert x.xtc_conv_max_k() >= 576
