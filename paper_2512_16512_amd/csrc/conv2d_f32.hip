@@ -2100,7 +2100,9 @@ hipError_t launch_conv_f32_patch(const ConvArgs &a, hipStream_t s) {
 // 20x64x56x56 -> 64 at 65.7 (64x416: 60.2), 9x64x57x57 -> 64 at 41.7 (split
 // 64x64 tiles: 33.6), 20x128x28x28 -> 256 at 133 (tap-major 64x128: 107),
 // 30x64x64x64 -> 128 at 227 (tap-major 128x128: 174) and 32x256x22x22 -> 256 at
-// 258 (split 64x64: 204).  False if no kernel of the table takes the layer.
+// 258 (split 64x64: 204); without the 64x256 tap-major tiles 8x32x128x128 -> 32
+// took 54.0 (50.7 with) and 8x128x128x128 -> 64 197 (179).  False if no kernel of
+// the table takes the layer.
 bool launch_conv_f32_least(const ConvArgs &a, hipStream_t s, hipError_t *err) {
     const long long OHW = (long long)a.OH * a.OW, N = a.Nb * OHW, tm = (a.OC + 63) / 64;
     auto tiles = [&](int bn) { return tm * ((N + bn - 1) / bn); };
@@ -2135,7 +2137,9 @@ bool launch_conv_f32_least(const ConvArgs &a, hipStream_t s, hipError_t *err) {
     const double t128x2 =
         a.C % 32 || a.OC <= 64 ? none
                                : strided * time_of((a.OC + 127) / 128 * ((N + 127) / 128), {57, 84, 145, 174}, 43);
-    const double least = std::min({h208, h256, h416, p64, p112, p208, t128, t128x2});
+    const double t256 =
+        a.C % 32 || a.OC > 64 ? none : strided * time_of(tiles(256), {60, 91, 145, 176}, 44);
+    const double least = std::min({h208, h256, h416, p64, p112, p208, t128, t128x2, t256});
     if (least == none) return false;
     if (least == p64) return try_patch_f32<PatchF32M2>(a, s, err);
     if (least == p112) return try_patch_f32<PatchF32M>(a, s, err);
@@ -2144,6 +2148,7 @@ bool launch_conv_f32_least(const ConvArgs &a, hipStream_t s, hipError_t *err) {
     else if (least == h256) *err = launch_conv_f32_halo<2>(a, s);
     else if (least == h416) *err = launch_conv_f32_halo16<2, 2>(a, s);
     else if (least == t128) *err = launch_conv_f32_tap<64, 128, 32, 64, 2, 3>(a, s);
+    else if (least == t256) *err = launch_conv_f32_tap<64, 256, 64, 64, 2, 2>(a, s);
     else *err = launch_conv_f32_tap<128, 128, 64, 64, 2, 3>(a, s);
     return true;
 }
@@ -2158,6 +2163,14 @@ hipError_t launch_conv_f32_patch_by_shape(const ConvArgs &a, hipStream_t s) {
     if (try_patch_f32<CFG>(a, s, &err) || try_patch_f32<PatchF32N>(a, s, &err) || try_patch_f32<PatchF32M>(a, s, &err))
         return err;
     return launch_conv_f32_no_patch(a, s);
+}
+
+// The default schedule of large layers up to 64 channels, without an explicit
+// one: the table for 3x3 layers, else as named.
+hipError_t launch_conv_f32_halo16_by_shape(const ConvArgs &a, hipStream_t s) {
+    hipError_t err;
+    if (a.R == 3 && a.S == 3 && a.C % 8 == 0 && launch_conv_f32_least(a, s, &err)) return err;
+    return launch_conv_f32_halo16<2, 2>(a, s);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int MI, int PAD>
@@ -2213,7 +2226,8 @@ const ConvInstance kConvInstances[] = {
                  &occupancy_of<&conv2d_f32_halo16_kernel<2, 1>, halo16::Cfg<1>::NT, 0>},
     ConvInstance{make_sched(64, 416, 8, 16, 208, 16, 16, 4, 2, -1, 0, 2),  // the same, two pixel halves
                  &launch_conv_f32_halo16<2, 2>,
-                 &occupancy_of<&conv2d_f32_halo16_kernel<2, 2>, halo16::Cfg<2>::NT, 0>},
+                 &occupancy_of<&conv2d_f32_halo16_kernel<2, 2>, halo16::Cfg<2>::NT, 0>,
+                 &launch_conv_f32_halo16_by_shape},
     ConvInstance{make_sched(64, 256, 8, 64, 64, 32, 32, 2, 2, -1, 0, 2),   // halo, 3x3 stride 1
                  &launch_conv_f32_halo<2>,
                  &occupancy_of<&conv2d_f32_halo_kernel<2>, halo::NT, 0>},

@@ -335,9 +335,9 @@ xtc_status xtc_default_schedule(xtc_op op, xtc_dtype dt, int64_t M, int64_t N, i
             out->raster = 0;
             return XTC_OK;
         }
-        if (K % 72 == 0 && !(M <= 64 && K == 576 && tiles(64, 416) >= cus - cus / 8)) {
-            // 3x3 layers of whole 8-channel stages, but for the benchmark
-            // layer's kind: the patch kernels, with the largest tile that
+        if (K % 72 == 0 && (M > 64 || tiles(64, 416) < cus - cus / 8)) {
+            // 3x3 layers of whole 8-channel stages, but for large ones up to
+            // 64 channels (below): the patch kernels, with the largest tile that
             // stays within a workgroup per CU (each of the split ones takes
             // most of a CU's LDS), 64x112 past that (64x128 output channels x
             // pixels at 28x28, batch 1, 8, 32: 16x32 tiles 10.1, 63.9, - us;
@@ -354,7 +354,7 @@ xtc_status xtc_default_schedule(xtc_op op, xtc_dtype dt, int64_t M, int64_t N, i
             out->raster = 0;
             return XTC_OK;
         }
-        if (M <= 64 && K % 32 != 0) {
+        if (M <= 64 && K % 32 != 0 && K % 72 != 0) {
             // outside every staged kernel's class: the k-table kernels, whose
             // 64x256 tiles, register-staged for these K, ran a 7x7 first
             // layer into 64 channels at batch 16 in 157 us, 64x64 ones in 70

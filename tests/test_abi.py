@@ -218,6 +218,16 @@ def test_default_schedules_are_compiled(x):
                 assert x.xtc_sched_check(op, dt, s) == 0
 
 
+def test_default_fp32_conv_tile_goes_by_the_kind_of_reduction(x):
+    """3x3 layers of 64, 128, 192 and 256 channels (whole stages of every
+    kernel) get the same tile for the same output: none of them is a case of
+    its own."""
+    for M in (33, 64, 65, 128, 256):
+        for N in (196, 3136, 12544, 50176, 100352, 131072, 401408):
+            tiles = {tuple(sorted(x.xtc_default_schedule(1, 0, M, N, 9 * C).as_dict().items())) for C in (64, 128, 192, 256)}
+            assert len(tiles) == 1, (M, N, tiles)
+
+
 @pytest.mark.parametrize("dt,elt", [(0, 4), (1, 2)])
 def test_default_matmul_launches_fit_the_largest_extents(x, dt, elt):
     """A launch has less than 2^32 threads: with the largest outputs the checks
