@@ -2101,25 +2101,29 @@ hipError_t launch_conv_f32_patch(const ConvArgs &a, hipStream_t s) {
 // 64x64 tiles: 33.6), 20x128x28x28 -> 256 at 133 (tap-major 64x128: 107),
 // 30x64x64x64 -> 128 at 227 (tap-major 128x128: 174) and 32x256x22x22 -> 256 at
 // 258 (split 64x64: 204); without the 64x256 tap-major tiles 8x32x128x128 -> 32
-// took 54.0 (50.7 with) and 8x128x128x128 -> 64 197 (179).  False if no kernel of
-// the table takes the layer.
+// took 54.0 (50.7 with) and 8x128x128x128 -> 64 197 (179), without those for any
+// C 10x40x114x114/2 -> 96 71 (47.5).  False if no kernel of the table takes the
+// layer.
 bool launch_conv_f32_least(const ConvArgs &a, hipStream_t s, hipError_t *err) {
     const long long OHW = (long long)a.OH * a.OW, N = a.Nb * OHW, tm = (a.OC + 63) / 64;
     auto tiles = [&](int bn) { return tm * ((N + bn - 1) / bn); };
     const bool halo_class = halo16_tile_px<1>(a) > 0;
-    const double none = 1e30, c = 64.0 / a.C;
-    auto time_of = [](long long n, const double (&us)[4], double step) {
+    // (what a tile costs whatever the channels counts c times per 64 of them;
+    // the tables have it once, in layers of fewer it shows: 8x8x56x56 -> 32
+    // 12.2 us without it, in 208-pixel halo tiles, 7.8)
+    const double none = 1e30, c = 64.0 / a.C, fewer = std::max(c - 1, 0.0);
+    auto time_of = [&](long long n, const double (&us)[4], double step, double fixed) {
         const long long per_cu = (n + 255) / 256;
-        return per_cu <= 4 ? us[per_cu - 1] : us[3] + (double)(per_cu - 4) * step;
+        return (per_cu <= 4 ? us[per_cu - 1] : us[3] + (double)(per_cu - 4) * step) + fixed * fewer * (double)per_cu;
     };
     auto rounds = [](long long n, int per_cu) { return (double)((n + 256 * per_cu - 1) / (256 * per_cu)); };
     // halo kernels: their tiles do not cross images
     auto per_image = [&](int bn) { return tm * a.Nb * ((OHW + bn - 1) / bn); };
     double h208 = none, h256 = none, h416 = none;
     if (halo_class) {
-        h208 = time_of(per_image(208), {38.3, 66.0, 100.3, 129.0}, 32);
-        if (halo_eligible(a)) h256 = time_of(per_image(256), {49.5, 85.0, 127.5, 166.5}, 41);
-        if (halo16_tile_px<2>(a) > 0) h416 = rounds(per_image(416), 1) * 60.5;
+        h208 = time_of(per_image(208), {38.3, 66.0, 100.3, 129.0}, 32, 8.4);
+        if (halo_eligible(a)) h256 = time_of(per_image(256), {49.5, 85.0, 127.5, 166.5}, 41, 10);
+        if (halo16_tile_px<2>(a) > 0) h416 = rounds(per_image(416), 1) * (60.5 + 6.5 * fewer);
     }
     // patch kernels: a second workgroup on a CU costs half a first one
     // where LDS holds both
@@ -2130,16 +2134,22 @@ bool launch_conv_f32_least(const ConvArgs &a, hipStream_t s, hipError_t *err) {
     const double p112 = !w112 || tiles(112) > 512   ? none
                         : w112 == 2 && tiles(112) > 256 ? 36 + 6.3 * c
                                                         : rounds(tiles(112), 1) * one112;
-    const double p208 = !w208 ? none : w208 == 2 ? rounds(tiles(208), 2) * 67 : rounds(tiles(208), 1) * 45;
-    // tap-major kernels (whole 32-channel steps)
+    const double p208 = !w208       ? none
+                        : w208 == 2 ? rounds(tiles(208), 2) * (67 + 10 * fewer)
+                                    : rounds(tiles(208), 1) * (45 + 6.7 * fewer);
+    // tap-major kernels, or the k-table kernels with their tiles where C is no
+    // whole number of 32-channel steps
     const double strided = a.sh > 1 || a.sw > 1 ? 1.15 : 1.0;
-    const double t128 = a.C % 32 ? none : strided * time_of(tiles(128), {33, 53, 69, 94}, 22.3);
-    const double t128x2 =
-        a.C % 32 || a.OC <= 64 ? none
-                               : strided * time_of((a.OC + 127) / 128 * ((N + 127) / 128), {57, 84, 145, 174}, 43);
-    const double t256 =
-        a.C % 32 || a.OC > 64 ? none : strided * time_of(tiles(256), {60, 91, 145, 176}, 44);
-    const double least = std::min({h208, h256, h416, p64, p112, p208, t128, t128x2, t256});
+    const double t128 = a.C % 32 ? none : strided * time_of(tiles(128), {33, 53, 69, 94}, 22.3, 4);
+    const long long n128x2 = (a.OC + 127) / 128 * ((N + 127) / 128);
+    const double t128x2 = a.OC <= 64 ? none
+                          : a.C % 32 ? time_of(n128x2, {76, 142, 205, 270}, 65, 8)
+                                     : strided * time_of(n128x2, {57, 84, 145, 174}, 43, 8);
+    const double t64 = a.OC > 64  ? none
+                       : a.C % 32 ? time_of(tiles(64), {27, 38, 62, 78}, 18, 3.5)
+                                  : time_of(tiles(64), {30, 35, 50, 61}, 15, 0);
+    const double t256 = a.C % 32 == 0 && a.OC <= 64 ? strided * time_of(tiles(256), {60, 91, 145, 176}, 44, 7) : none;
+    const double least = std::min({h208, h256, h416, p64, p112, p208, t64, t128, t128x2, t256});
     if (least == none) return false;
     if (least == p64) return try_patch_f32<PatchF32M2>(a, s, err);
     if (least == p112) return try_patch_f32<PatchF32M>(a, s, err);
@@ -2147,6 +2157,7 @@ bool launch_conv_f32_least(const ConvArgs &a, hipStream_t s, hipError_t *err) {
     if (least == h208) *err = launch_conv_f32_halo16<2, 1>(a, s);
     else if (least == h256) *err = launch_conv_f32_halo<2>(a, s);
     else if (least == h416) *err = launch_conv_f32_halo16<2, 2>(a, s);
+    else if (least == t64) *err = launch_conv_f32_tap<64, 64, 32, 32, 2, 4>(a, s);
     else if (least == t128) *err = launch_conv_f32_tap<64, 128, 32, 64, 2, 3>(a, s);
     else if (least == t256) *err = launch_conv_f32_tap<64, 256, 64, 64, 2, 2>(a, s);
     else *err = launch_conv_f32_tap<128, 128, 64, 64, 2, 3>(a, s);
@@ -2160,8 +2171,11 @@ hipError_t launch_conv_f32_patch_by_shape(const ConvArgs &a, hipStream_t s) {
     const bool large = CFG::NB == 7 || (halo16_tile_px<1>(a) > 0 && (a.OC + 63) / 64 *
                        (((long long)a.Nb * a.OH * a.OW + 207) / 208) >= 192);
     if (large && launch_conv_f32_least(a, s, &err)) return err;
-    if (try_patch_f32<CFG>(a, s, &err) || try_patch_f32<PatchF32N>(a, s, &err) || try_patch_f32<PatchF32M>(a, s, &err))
-        return err;
+    if (try_patch_f32<CFG>(a, s, &err) || try_patch_f32<PatchF32N>(a, s, &err)) return err;
+    // rows too long for the small tiles' patches: few 64x112 tiles against four
+    // times as many 64x64 ones without a patch (2x32x114x114/2 -> 64 19.1 us,
+    // 14.5), or a quarter as many 128x128 ones (1x32x160x160/2 -> 128 20.0, 34.8)
+    if (a.OC > 64 && try_patch_f32<PatchF32M>(a, s, &err)) return err;
     return launch_conv_f32_no_patch(a, s);
 }
 
@@ -2171,6 +2185,35 @@ hipError_t launch_conv_f32_halo16_by_shape(const ConvArgs &a, hipStream_t s) {
     hipError_t err;
     if (a.R == 3 && a.S == 3 && a.C % 8 == 0 && launch_conv_f32_least(a, s, &err)) return err;
     return launch_conv_f32_halo16<2, 2>(a, s);
+}
+
+// The default schedule of layers up to 32 channels from a short reduction,
+// without an explicit one.  For 17 to 32 channels the two 16-channel tiles are
+// the best only where their patch form fits (else one gathers, which pays while
+// the tiles share no CU) and images fill its tiles:
+//  - 3x3 layers of whole 8-channel groups and rows up to 60 pixels: the patch
+//    and halo kernels (1024x16x3x3 -> 24 54 us with 16-channel tiles, 7.5;
+//    64x24x14x14 -> 24 13.8, 10.2; 16x16x56x56 -> 32 20.7, 15.3; but
+//    32x16x64x64 -> 32 38.3, 46.9);
+//  - small images of rows that are no whole 16 bytes: 64x64 tiles
+//    (256x12x7x7 -> 24 11.1, 8.5; 64x20x14x14 -> 32 12.1, 10.8);
+//  - past one gather tile per CU: 64x64 tiles (4x16x224x224 -> 32 120, 72;
+//    8x200x200 -> 24, 5x5: 34, 25; 4x100x28x28 -> 24, 1x1/2: 5.5, 8.2).
+hipError_t launch_conv_f32_smallm_by_shape(const ConvArgs &a, hipStream_t s) {
+    if (a.OC > 16) {
+        const long long OHW = (long long)a.OH * a.OW, N = a.Nb * OHW, tm = (a.OC + 15) / 16;
+        if (a.R == 3 && a.S == 3 && a.C % 8 == 0 && a.OW <= 60) {
+            if (tm * ((N + 31) / 32) <= 256) return launch_conv_f32_patch_by_shape<PatchF32T>(a, s);
+            if ((N + 31) / 32 <= 256) return launch_conv_f32_patch_by_shape<PatchF32N>(a, s);
+            if ((N + 63) / 64 <= 256) return launch_conv_f32_patch_by_shape<PatchF32M2>(a, s);
+            return launch_conv_f32_patch_by_shape<PatchF32M>(a, s);
+        }
+        const bool patch = smallm::patch_geom(a, 64, false).PR > 0;
+        const bool small_rows = a.W % 4 != 0 && a.OW <= 16 && a.R * a.S <= 9;
+        if (patch ? small_rows && tm * a.Nb * ((OHW + 63) / 64) > 256 : tm * ((N + 63) / 64) > 256)
+            return launch_conv_f32_tap<64, 64, 32, 32, 2, 4>(a, s);
+    }
+    return launch_conv_f32_smallm<1, 32>(a, s);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int MI, int PAD>
@@ -2249,7 +2292,8 @@ const ConvInstance kConvInstances[] = {
     // few output channels: 16 x 64 tiles, operands straight to registers
     ConvInstance{make_sched(16, 64, 128, 16, 16, 16, 16, 4, 0, 0, 0, 0),
                  &launch_conv_f32_smallm<1, 32>,
-                 &occupancy_of<&conv2d_f32_smallm_kernel<1, 32>, smallm::NT, (int)sizeof(int2)>},
+                 &occupancy_of<&conv2d_f32_smallm_kernel<1, 32>, smallm::NT, (int)sizeof(int2)>,
+                 &launch_conv_f32_smallm_by_shape},
 };
 
 }  // namespace

@@ -323,7 +323,7 @@ xtc_status xtc_default_schedule(xtc_op op, xtc_dtype dt, int64_t M, int64_t N, i
         // (5x5 from 3 channels where 64x64 tiles nearly fill one round of four
         // per CU: 929 tiles 15.5 us, these 16.4; 743 tiles 13.0, 13.1; 1114
         // tiles 20.7, 18.0)
-        const bool full_round = M > 16 && K < 128 && tiles(64, 64) > cus * 7 / 2 && tiles(64, 64) <= cus * 4;
+        const bool full_round = M > 16 && K < 128 && K % 72 != 0 && tiles(64, 64) > cus * 7 / 2 && tiles(64, 64) <= cus * 4;
         if (M <= 16 || (M <= 32 && K % 32 != 0 && K >= 48 && K <= 256 && !full_round)) {
             // up to 32 channels from a short reduction that is no multiple of
             // 32 (the first layer of an image network): two tiles of 16 (7x7

@@ -410,13 +410,22 @@ def test_conv_f32_default_runs_unsplit_patch_tiles(x, N, C, H, W, OC, stride):
 
 @pytest.mark.parametrize("dtype,N,C,H,W,OC,R,stride,pad", [
     ("f32", 9, 64, 57, 57, 64, 3, 1, 1),    # halo class: two split 64x64 patch tiles per CU
-    ("f32", 9, 16, 57, 57, 64, 3, 1, 1),    # halo class, few channels: 208-pixel halo tiles
+    ("f32", 9, 16, 57, 57, 64, 3, 1, 1),    # the same from fewer channels
+    ("f32", 33, 32, 28, 28, 64, 3, 1, 1),   # outside it, from fewer channels: tap-major 64x64 tiles
+    ("f32", 4, 24, 96, 96, 64, 3, 2, 1),    # long rows at stride 2: k-table 64x64 tiles
     ("f32", 20, 16, 56, 56, 64, 3, 1, 1),   # halo class: 416-pixel tiles
     ("f32", 19, 16, 56, 56, 128, 3, 1, 1),  # halo class: 64x256 tiles, two per CU
-    ("f32", 37, 8, 28, 28, 64, 3, 1, 1),    # outside it, one stage: 208-pixel patch tiles
+    ("f32", 37, 8, 28, 28, 64, 3, 1, 1),    # outside it, one stage: 64x112 patch tiles
     ("f32", 37, 64, 28, 28, 64, 3, 1, 1),   # outside it: two split 64x64 patch tiles per CU
     ("f32", 28, 8, 28, 28, 256, 3, 1, 1),   # outside it: 208-pixel patch tiles
     ("f32", 20, 32, 28, 28, 256, 3, 1, 1),  # outside it: tap-major 64x128 tiles
+    ("f32", 64, 16, 14, 14, 24, 3, 2, 1),   # 17 to 32 channels: 16x32 patch tiles
+    ("f32", 96, 16, 6, 6, 20, 3, 1, 1),     # the same, 64x32 patch tiles
+    ("f32", 400, 8, 3, 5, 32, 3, 1, 1),     # 64x64 patch tiles, many images in each
+    ("f32", 130, 12, 7, 7, 24, 3, 1, 1),    # odd rows of small images: 64x64 k-table tiles
+    ("f32", 1, 16, 140, 140, 20, 3, 1, 1),  # a patch past the 16-channel tiles': 64x64 k-table tiles
+    ("f32", 1, 100, 28, 28, 24, 1, 2, 0),   # a few 16-channel tiles, gathered
+    ("f32", 1, 8, 90, 90, 17, 3, 1, 1),     # wide rows: 16-channel tiles with their patch
     ("bf16", 7, 3, 219, 221, 32, 3, 2, 1),  # gather: past one round of 64x64 tiles
     ("bf16", 11, 3, 224, 224, 16, 3, 2, 1), # past one round of 64x128 tiles
     ("bf16", 17, 3, 224, 224, 16, 3, 2, 1), # past two and a half rounds of 64x64 tiles
