@@ -917,24 +917,38 @@ bool try_patch_bf16(const ConvArgs &a, hipStream_t s, hipError_t *err, bool smal
 }
 
 // Outside the patch kernel's class.  A CU holds five workgroups of 64x64 tiles
-// and four of 64x128 ones, whose round takes about 1.35 times as long (7x7
-// stride-2 first layers into 64 channels, 1176 small or 588 large tiles: 17.1
-// and 20.7 us): small tiles within one round of theirs and, past one round of
-// the large ones, up to two and a half (2156 and 1078: 27.4, 33.8; 3136 and
-// 1568: 37.2, 38.3); else the large ones (1568 and 784: 24.1, 22.9; 3844 and
-// 1922 of a 5x5 layer: 29.1, 27.1).  More than 64 output channels: 128x128 from
-// four 64x128 tiles per CU on.
+// and four of 64x128 ones, fewer where the k-offset table of a long reduction
+// takes their LDS (K = 3200: three and two).  A round of the large ones takes
+// about 1.35 times as long (7x7 stride-2 first layers into 64 channels, 1176
+// small or 588 large tiles: 17.1 and 20.7 us): small tiles within one round of
+// theirs and, past one round of the large ones, up to two and a half (2156 and
+// 1078: 27.4, 33.8; 3136 and 1568: 37.2, 38.3); else the large ones (1568 and
+// 784: 24.1, 22.9; 3844 and 1922 of a 5x5 layer: 29.1, 27.1).  With fewer per CU
+// a large round takes 1.7 times as long (K = 3136, 2813 and 1407: 575, 742; 980
+// and 490 of K = 3200: 264, 251).  More than 64
+// output channels: small tiles within a round, else 128x128 (K = 512, 980 small
+// tiles 40.7 us, 245 large 46.2; 1568 72.5, 392 50.9; K = 3200, 784 258, 196 244;
+// 1568 394, 392 269).
 hipError_t launch_conv_bf16_gather(const ConvArgs &a, hipStream_t s) {
     const long long N = (long long)a.Nb * a.OH * a.OW;
     const long long small = (a.OC + 63) / 64 * ((N + 63) / 64), large = (a.OC + 63) / 64 * ((N + 127) / 128);
+    auto round_of = [&](int bn, int most) {   // tiles of 64 x bn that run at once
+        const int lds = 2 * 2 * (64 * (32 + 8) + 32 * (bn + 32)) + 8 * a.C * a.R * a.S;
+        return 256LL * std::min(most, 160 * 1024 / lds);
+    };
+    const long long small_round = round_of(64, 5), large_round = round_of(128, 4);
     // pointwise layers of a stage or two move more than they compute
     // (26x64x55x55 -> 256: 24.3 us, 26.0 with 64x128 tiles, 29.2 with 128x128)
     if (a.R * a.S == 1 && a.C <= 64) return launch_conv_bf16<64, 64, 32, 32, 32, 32, 8>(a, s);
     if (a.OC > 64) {
-        if (large < 1024) return launch_conv_bf16<64, 64, 32, 32, 32, 32, 8>(a, s);
+        if (small <= small_round) return launch_conv_bf16<64, 64, 32, 32, 32, 32, 8>(a, s);
         return launch_conv_bf16<128, 128, 32, 64, 64, 32, 8>(a, s);
     }
-    if (small <= 1280 || (large > 1024 && small <= 3200)) return launch_conv_bf16<64, 64, 32, 32, 32, 32, 8>(a, s);
+    const bool few = small_round < 1280;
+    const double small_rounds = (double)((small + small_round - 1) / small_round);
+    const double large_rounds = (double)((large + large_round - 1) / large_round);
+    if (small <= small_round || (few ? small_rounds < 1.7 * large_rounds : large > large_round && small <= 3200))
+        return launch_conv_bf16<64, 64, 32, 32, 32, 32, 8>(a, s);
     return launch_conv_bf16<64, 128, 32, 32, 64, 32, 8>(a, s);
 }
 

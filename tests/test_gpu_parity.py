@@ -429,6 +429,8 @@ def test_conv_f32_default_runs_unsplit_patch_tiles(x, N, C, H, W, OC, stride):
     ("bf16", 7, 3, 219, 221, 32, 3, 2, 1),  # gather: past one round of 64x64 tiles
     ("bf16", 11, 3, 224, 224, 16, 3, 2, 1), # past one round of 64x128 tiles
     ("bf16", 17, 3, 224, 224, 16, 3, 2, 1), # past two and a half rounds of 64x64 tiles
+    ("bf16", 3, 12, 128, 128, 96, 3, 1, 1), # more than 64 channels: past one round of 64x64 tiles
+    ("bf16", 1, 128, 100, 100, 272, 5, 1, 2),  # a long reduction, whose rounds are smaller
 ])
 def test_conv_default_by_rounds_of_tiles(x, dtype, N, C, H, W, OC, R, stride, pad):
     """The default conv kernels on both sides of the lines between tile sizes.
