@@ -971,14 +971,22 @@ hipError_t launch_conv_bf16_patch(const ConvArgs &a, hipStream_t s) {
 // (128x28x28 -> 128 at batch 1, 8, 32: 32x64/4 9.0, 20.8, - us; 64x128/2
 // 11.6, 12.4, 24.2; 64x256 16.3, 16.9, 19.0; 64x128 12.5, 13.5, 20.2), and
 // past that 64x128 tiles, of which two fit a CU (64x57x57 -> 128 at batch 32:
-// 40.1 us against 50.9 with 64x256).
+// 40.1 us against 50.9 with 64x256).  The reduction is split no further than
+// it has chunks of 16 channels: a group without one costs its barriers and sums
+// (256x8x8x8 -> 8: 6.8 us in four groups, 5.5 in two; 8x8x56x56 -> 16: 7.6 with
+// 64x128/2, 6.2 with 64x128).  A single half chunk pays for its patch only where
+// that is small: 8 channels at stride 2 or in rows past 64 pixels gather
+// (64x8x28x28/2 -> 16 7.4 us, 6.4; 7x8x100x100 -> 33 19.5, 12.4).
 hipError_t launch_conv_bf16_patch_auto(const ConvArgs &a, hipStream_t s) {
     const long long N = (long long)a.Nb * a.OH * a.OW;
     auto tiles = [&](int bm, int bn) { return (a.OC + bm - 1) / bm * ((N + bn - 1) / bn); };
     hipError_t err;
-    if (tiles(32, 64) <= 256 && (try_patch_bf16<PatchS4>(a, s, &err) || try_patch_bf16<PatchS2>(a, s, &err)))
+    const int chunks = (a.C + patch_bf16::CC - 1) / patch_bf16::CC;
+    if (a.C <= 8 && (a.sh > 1 || a.sw > 1 || a.OW > 64)) return launch_conv_bf16_gather(a, s);
+    if (tiles(32, 64) <= 256 &&
+        ((chunks > 2 && try_patch_bf16<PatchS4>(a, s, &err)) || try_patch_bf16<PatchS2>(a, s, &err)))
         return err;
-    if (tiles(64, 128) <= 256 && try_patch_bf16<PatchM2>(a, s, &err)) return err;
+    if (tiles(64, 128) <= 256 && chunks > 1 && try_patch_bf16<PatchM2>(a, s, &err)) return err;
     if (tiles(64, 128) > 256 && tiles(64, 256) <= 256 && try_patch_bf16<PatchL>(a, s, &err, true)) return err;
     if (try_patch_bf16<PatchM>(a, s, &err) || try_patch_bf16<PatchS2>(a, s, &err)) return err;
     return launch_conv_bf16_gather(a, s);

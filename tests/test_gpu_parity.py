@@ -429,6 +429,10 @@ def test_conv_f32_default_runs_unsplit_patch_tiles(x, N, C, H, W, OC, stride):
     ("bf16", 7, 3, 219, 221, 32, 3, 2, 1),  # gather: past one round of 64x64 tiles
     ("bf16", 11, 3, 224, 224, 16, 3, 2, 1), # past one round of 64x128 tiles
     ("bf16", 17, 3, 224, 224, 16, 3, 2, 1), # past two and a half rounds of 64x64 tiles
+    ("bf16", 3, 8, 20, 20, 40, 3, 1, 1),    # patch kernels with one chunk: no group without one
+    ("bf16", 9, 16, 60, 60, 20, 3, 1, 1),   # the same, 64x128 tiles
+    ("bf16", 3, 24, 20, 20, 40, 3, 1, 1),   # two chunks
+    ("bf16", 3, 8, 20, 20, 40, 3, 2, 1),    # half a chunk at stride 2: gather
     ("bf16", 3, 12, 128, 128, 96, 3, 1, 1), # more than 64 channels: past one round of 64x64 tiles
     ("bf16", 1, 128, 100, 100, 272, 5, 1, 2),  # a long reduction, whose rounds are smaller
 ])
