@@ -230,8 +230,10 @@ xtc_status xtc_matmul(int64_t M, int64_t N, int64_t K,
  *  sched NULL selects the default conv schedule, but for large fp32 3x3
  *  layers of whole 8-channel groups, which run the patch, halo or tap-major
  *  kernel whose tiles share the CUs best for their shape, and pointwise layers
- *  (1x1, stride 1, no padding; bf16: C >= 32), which the matmul kernels
- *  compute per image, with xtc_default_schedule's matmul rules.
+ *  (1x1, stride 1, no padding), which the matmul kernels compute per image,
+ *  with xtc_default_schedule's matmul rules, where that is the faster route
+ *  (not for many images smaller than a tile, nor for bf16 layers of fewer than
+ *  32 channels, or of up to 64 whose images do not start on 16 bytes).
  * Errors as for xtc_matmul; XTC_ERR_TOO_LARGE also when C*R*S exceeds the
  * kernel's k-offset table capacity (xtc_conv_max_k()).
  */

@@ -266,6 +266,54 @@ void default_matmul(xtc_dtype dt, int64_t M, int64_t N, int64_t K, int64_t batch
     }
 }
 
+// Microseconds of a pointwise layer on either route, from the tiles on the
+// fullest CU (fitted to 2388 layers: 11 pairs of channels from 16 to 2048,
+// images of 1 to 784 pixels, batch 2 to 1024; four of five within 20%).
+
+// One product per image with schedule s: a tile costs a fixed part and its
+// products, those of columns past the image's included.
+double pointwise_per_image_us(xtc_dtype dt, int64_t N, int64_t HW, int64_t C, int64_t OC, const xtc_sched &s) {
+    auto per_cu = [&](int64_t bm, int64_t bn) { return (double)cdiv(cdiv(OC, bm) * cdiv(HW, bn) * N, 256); };
+    const double c = (double)C, area = (double)s.block_m * s.block_n, n = per_cu(s.block_m, s.block_n);
+    const bool fed = s.lds_stages == 0;   // the register-fed kernels
+    if (dt == XTC_F32)
+        return fed ? 3.5 + n * (.4 + c * area * (area <= 512 ? 11e-6 : 7e-6)) : 3 + n * (1 + c * area * 4e-6);
+    const double staged64 = 3.3 + per_cu(64, 64) * (.45 + .0055 * c);   // register-staged 64x64 tiles
+    if (fed) {
+        if (HW % 2 && C <= (cdiv(OC, 64) * cdiv(HW, 64) * N > 256 ? 192 : 64)) return staged64;
+        return 3.3 + n * (.25 + c * (HW % 2 ? .0125 : HW % 8 ? .0085 : .0044) * (.4 + .6 / 64 * s.block_m));
+    }
+    if (HW % 8 == 0) return 3.3 + n * area * (1e-4 + c * 3.3e-7);
+    if (s.block_m < 128) return C <= 128 ? staged64 : 3.3 + per_cu(64, 126) * (1.6 + .0052 * c);
+    return 3.3 + per_cu(128, 126) * (3 + .0098 * c);
+}
+
+// The conv kernels on the pixels of all images in a row: their chain over the
+// channels, and the rounds of their tiles.
+double pointwise_flat_us(xtc_dtype dt, int64_t pixels, int64_t C, int64_t OC) {
+    const double c = (double)C, f = c / 576, fixed = C < 512 ? 1 - c / 512 : 0;
+    auto tiles = [&](int64_t bm, int64_t bn) { return cdiv(OC, bm) * cdiv(pixels, bn); };
+    auto per_cu = [](int64_t t, const double (&us)[4], double step) {
+        const int64_t n = cdiv(t, 256);
+        return n <= 4 ? us[n - 1] : us[3] + (double)(n - 4) * step;
+    };
+    if (dt == XTC_F32) {
+        if (OC > 64) {
+            const int64_t t = tiles(128, 128);
+            return 4.5 + f * (C % 32 ? per_cu(t, {76, 142, 205, 270}, 65) : per_cu(t, {50, 80, 145, 174}, 43)) +
+                   2.5 * fixed * (double)cdiv(t, 256);
+        }
+        if (C % 32) return 4 + f * per_cu(tiles(64, 64), {27, 38, 62, 78}, 18) + 2 * (double)cdiv(tiles(64, 64), 256);
+        if (tiles(64, 256) < 256) return 4 + f * per_cu(tiles(64, 64), {18, 28, 38, 48}, 12);
+        return 4 + f * per_cu(tiles(64, 256), {60, 91, 145, 176}, 44) + 3.5 * fixed * (double)cdiv(tiles(64, 256), 256);
+    }
+    const double n = (double)cdiv(tiles(64, 64), 256);
+    if (C <= 64) return 3.5 + .0405 * c + n * (.25 + .0125 * c);
+    if (n <= 5) return 3.5 + c * (.0405 + .005 * (n - 1)) + .3 * n;
+    if (OC > 64) return 4 + (double)cdiv(tiles(128, 128), C > 1700 ? 512 : 768) * (3 + .09 * c);
+    return 3.5 + (double)cdiv(tiles(64, 128), 1024) * (3 + .06 * c);
+}
+
 }  // namespace
 
 extern "C" {
@@ -529,14 +577,24 @@ xtc_status conv_impl(int64_t N, int64_t C, int64_t H, int64_t W, int64_t OC, int
     // start on 16 bytes, those of up to 64 channels from two of its tiles per
     // CU on, or from fewer than 64 (26x64x55x55 -> 64: 9.9 us against 18.5;
     // 13x64x27x27 -> 64, 149 tiles: 5.8, 6.0; 4x64x27x27 -> 64: 5.5, 4.7).
+    // Images smaller than a tile leave most of it empty and read all weights
+    // each: from some batch on the conv kernels, which run the pixels of all
+    // images in a row, are faster (2048x1x1 -> 1000 at batch 8, 64, 512: fp32
+    // 15, 112, 856 us per image, 157, 172, 200 in a row; bf16 16, 82, 622, and 97,
+    // 87, 88).
     const bool gather = dtype == XTC_BF16 &&
                         (C < 32 || (H * W % 8 != 0 && (C < 64 || (C == 64 && cdiv(OC, 64) * cdiv(Ng, 64) >= 512))));
     if (!sched && R == 1 && S == 1 && stride_h == 1 && stride_w == 1 && pad_h == 0 && pad_w == 0 && N <= 65535 &&
         !gather) {
         const int64_t HW = H * W;
-        default_matmul(dtype, OC, HW, C, N, &s);
-        return launch_matmul(s, dtype, (int)OC, (int)HW, (int)C, Wt, (int)C, X, (int)HW, Y, (int)HW, relu, (int)N,
-                             C * HW * elt, OC * HW * 4, stream);
+        xtc_sched p;
+        default_matmul(dtype, OC, HW, C, N, &p);
+        // (below two tiles per CU the products always are; so they are up to
+        // 16 channels in fp32, whose conv tiles gather)
+        if (cdiv(OC, p.block_m) * cdiv(HW, p.block_n) * N < 512 || (dtype == XTC_F32 && OC <= 16) ||
+            pointwise_flat_us(dtype, N * HW, C, OC) >= .95 * pointwise_per_image_us(dtype, N, HW, C, OC, p))
+            return launch_matmul(p, dtype, (int)OC, (int)HW, (int)C, Wt, (int)C, X, (int)HW, Y, (int)HW, relu, (int)N,
+                                 C * HW * elt, OC * HW * 4, stream);
     }
     const ConvInstance *inst = find_conv(dtype, s);
     if (!inst) return XTC_ERR_UNSUPPORTED_SCHEDULE;

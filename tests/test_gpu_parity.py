@@ -462,10 +462,14 @@ def test_conv_default_by_rounds_of_tiles(x, dtype, N, C, H, W, OC, R, stride, pa
     (2, 128, 28, 28, 256, 0),  # whole 16-byte rows
     (2, 96, 14, 14, 64, 2),    # 8-byte rows, 4-byte aligned base
     (2, 16, 13, 13, 16, 0),    # fewer than 32 channels
+    (9, 64, 1, 1, 40, 1),      # images of one pixel
+    (1100, 64, 1, 1, 256, 0),  # so many that the conv kernels run them in a row
+    (1100, 72, 2, 3, 200, 0),  # the same from channels that are no whole step, into ragged tiles
+    (1100, 32, 3, 3, 32, 2),   # up to 64 channels out
 ])
 def test_pointwise_conv_by_the_matmul_kernels(x, dtype, N, C, H, W, OC, off):
-    """1x1, stride 1, no padding without a schedule: one product per image.
-    X starts ``off`` elements past a 16-byte boundary, with infinities around
+    """1x1, stride 1, no padding without a schedule: one product per image, or
+    many small images in a row by the conv kernels.  X starts ``off`` elements past a 16-byte boundary, with infinities around
     it.  Bit-exact (small integers)."""
     import torch
     X, Wt = xi.small_int_f32(61, (N, C, H, W)), xi.small_int_f32(62, (OC, C, 1, 1))
