@@ -310,7 +310,10 @@ int32_t xtc_sched_list(xtc_op op, xtc_dtype dtype, xtc_sched *out, int32_t cap);
  * registers, LDS and threads), for reduction length K (matmul: K; conv2d:
  * C*R*S, which sizes the conv kernels' LDS k-offset table).  For a conv
  * tap-major instance the figure is that of the tap-major kernel itself, not
- * of the channel-major kernel it falls back to when C % 32 != 0.  Queries
+ * of the channel-major kernel it falls back to when C % 32 != 0.  The LDS of
+ * the patch kernels (k_order 2, lds_pad 0) holds a tile's input patch, which
+ * depends on the layer: their figure is that of a 28x28 image at stride 1 and
+ * padding 1, whatever K; longer rows, strides or a batch may leave fewer.  Queries
  * the current HIP device; enqueues nothing.  Errors: XTC_ERR_NULL_POINTER,
  * the codes of xtc_sched_check, XTC_ERR_BAD_SHAPE (K < 0),
  * XTC_ERR_TOO_LARGE (conv K above xtc_conv_max_k(), or K > 2^30),

@@ -898,6 +898,20 @@ hipError_t launch_patch(const PatchArgs &pa, size_t lds, hipStream_t s) {
                            dim3(tiles), dim3(CFG::NT), kargs, lds, s);
 }
 
+// Workgroups of the tile's kernel that a CU holds in the reference layer.
+template <typename CFG>
+hipError_t patch_bf16_occupancy(int, int *wg_per_cu) {
+    const ConvArgs a = patch_reference_layer();
+    PatchArgs pa;
+    size_t lds;
+    const void *fn = reinterpret_cast<const void *>(&conv2d_bf16_patch_kernel<CFG, CFG::SU0, 4, true>);
+    if (!patch_bf16_geom<CFG, CFG::SU0, 4>(a, true, &pa, &lds)) {
+        fn = reinterpret_cast<const void *>(&conv2d_bf16_patch_kernel<CFG, 2 * CFG::SU0, 9, true>);
+        if (!patch_bf16_geom<CFG, 2 * CFG::SU0, 9>(a, true, &pa, &lds)) return hipErrorInvalidValue;
+    }
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(wg_per_cu, fn, CFG::NT, lds);
+}
+
 // Tries the patch kernel with tile CFG (with its smaller slot and item count
 // only, if `small_only`: long rows leave the others little to gain); false if
 // the shape is outside it.
@@ -965,8 +979,8 @@ hipError_t launch_conv_bf16_patch(const ConvArgs &a, hipStream_t s) {
     return launch_conv_bf16_gather(a, s);
 }
 
-// The tile and split for a shape.  Every tile but PatchM's takes the LDS of a
-// whole CU, so its time doubles when the workgroups pass 256: the smallest
+// The tile and split for a shape.  Every tile but PatchM's (and PatchS2's in
+// short rows) takes the LDS of a whole CU, so its time doubles when the workgroups pass 256: the smallest
 // tile, with the reduction split furthest, that stays within one round
 // (128x28x28 -> 128 at batch 1, 8, 32: 32x64/4 9.0, 20.8, - us; 64x128/2
 // 11.6, 12.4, 24.2; 64x256 16.3, 16.9, 19.0; 64x128 12.5, 13.5, 20.2), and
@@ -1411,8 +1425,7 @@ hipError_t launch_conv_bf16_rows(const ConvArgs &a, hipStream_t s) {
 #define XTC_CONV_BF16_PATCH_INSTANCE(CFG, STAGES)                                             \
     ConvInstance {                                                                            \
         make_sched(CFG::BM, CFG::BN, 16, CFG::WM, CFG::WN, 32, 32, 16, STAGES, 0, 0, 2),       \
-            &launch_conv_bf16_patch<CFG>,                                                     \
-            &occupancy_of<&conv2d_bf16_patch_kernel<CFG, CFG::SU0, 4, true>, CFG::NT, 0>       \
+            &launch_conv_bf16_patch<CFG>, &patch_bf16_occupancy<CFG>                          \
     }
 
 const ConvInstance kConvBf16Instances[] = {

@@ -1988,6 +1988,15 @@ const void *patch_f32_kernel(const ConvArgs &a, PatchF32Args *pa, size_t *lds) {
     return nullptr;
 }
 
+// Workgroups of the tile's kernel that a CU holds in the reference layer.
+template <typename CFG>
+hipError_t patch_f32_occupancy(int, int *wg_per_cu) {
+    PatchF32Args pa;
+    size_t lds;
+    const void *fn = patch_f32_kernel<CFG>(patch_reference_layer(), &pa, &lds);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(wg_per_cu, fn, CFG::NT, lds);
+}
+
 // Tries the patch kernel with tile CFG; false if the shape is outside it.
 template <typename CFG>
 bool try_patch_f32(const ConvArgs &a, hipStream_t s, hipError_t *err) {
@@ -2259,8 +2268,7 @@ hipError_t launch_conv_f32(const ConvArgs &a, hipStream_t s) {
 #define XTC_CONV_F32_PATCH_INSTANCE(CFG, STAGES)                                              \
     ConvInstance {                                                                            \
         make_sched(CFG::BM, CFG::BN, 8, 16, CFG::BN, 16, 16, 4, STAGES, 0, 0, 2),              \
-            &launch_conv_f32_patch<CFG>, &occupancy_of<&conv2d_f32_patch_kernel<CFG, 10>, CFG::NT, 0>, \
-            &launch_conv_f32_patch_by_shape<CFG>                                              \
+            &launch_conv_f32_patch<CFG>, &patch_f32_occupancy<CFG>, &launch_conv_f32_patch_by_shape<CFG> \
     }
 
 const ConvInstance kConvInstances[] = {

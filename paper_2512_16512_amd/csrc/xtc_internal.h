@@ -64,6 +64,17 @@ hipError_t occupancy_of(int K, int *wg_per_cu) {
         (size_t)DYN_BYTES_PER_K * (size_t)K);
 }
 
+// The layer that stands for the occupancy of the conv patch kernels, whose LDS
+// holds the input patch of a tile: 3x3 taps on a 28x28 image, stride 1, padding 1.
+inline ConvArgs patch_reference_layer() {
+    ConvArgs a = {};
+    a.Nb = 1; a.C = 64; a.H = a.W = 28; a.OC = 64;
+    a.R = a.S = 3;
+    a.sh = a.sw = 1; a.ph = a.pw = 1;
+    a.OH = a.OW = 28;
+    return a;
+}
+
 // What `vec_launch` of an instance requires; `any_launch` has no
 // requirement.
 enum VecRule {

@@ -240,3 +240,16 @@ def test_every_instance_fits_on_a_cu(x):
             for K in (1, 576, 4096):
                 n = x.xtc_sched_occupancy(op, dt, K, s)
                 assert 1 <= n <= 32, (op, dt, K, s, n)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_occupancy_of_the_patch_kernels_counts_their_lds(x, dtype):
+    # the patch of 28-pixel rows takes more than half a CU's LDS in every tile
+    # but those that hold two workgroups
+    code = x.XTC_F32 if dtype == "f32" else x.XTC_BF16
+    two = {"f32": [(64, 112, 2)], "bf16": [(64, 128, 2), (32, 64, 2)]}[dtype]
+    patch = [s for s in x.xtc_sched_list(x.XTC_OP_CONV2D, code) if s.k_order == 2 and s.lds_pad == 0]
+    assert len(patch) == {"f32": 4, "bf16": 5}[dtype]
+    for s in patch:
+        n = x.xtc_sched_occupancy(x.XTC_OP_CONV2D, code, 576, s)
+        assert n == (2 if (s.block_m, s.block_n, s.lds_stages) in two else 1), (s, n)
