@@ -11,8 +11,10 @@ current stream, nothing else); the plain calls among theirs go through
 ``_binding.so`` (csrc/torch_binding.cpp), which saves the interpreter's share
 of a call.
 
-If the library or the binding has not been built, importing this package raises
-``ImportError``: there is no fallback implementation.
+If the library has not been built, importing this package raises
+``ImportError``: there is no fallback implementation.  Without the native
+binding (not built, or for another torch) it warns, and the conveniences check
+their arguments and call the same library from Python.
 """
 from __future__ import annotations
 
@@ -126,7 +128,13 @@ def _load_binding():
         import torch  # noqa: F401
     except ImportError:
         return None
-    from . import _binding
+    try:
+        from . import _binding
+    except ImportError as e:
+        import warnings
+        warnings.warn("the native binding does not load (%s): matmul() and conv2d_nchw() take 6 us longer "
+                      "per call; run `python paper_2512_16512_amd/build.py`" % e, RuntimeWarning, stacklevel=3)
+        return None
     return _binding
 
 

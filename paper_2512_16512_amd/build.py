@@ -3,8 +3,8 @@
 
 Every translation unit of the library is compiled with hipcc for gfx950 only,
 with packed-fp32 instruction selection disabled, then linked into one shared
-library next to this file; the binding is compiled against torch's headers and
-linked to it.  Run ``python paper_2512_16512_amd/build.py`` (a plain script: importing the
+library next to this file; where torch is installed, the binding is compiled
+against its headers with hipcc's own clang and linked to the library.  Run ``python paper_2512_16512_amd/build.py`` (a plain script: importing the
 package needs the built library) or call ``build()``.
 """
 from __future__ import annotations
@@ -51,11 +51,18 @@ def _run(cmd, what: str, verbose: bool) -> None:
         raise RuntimeError("%s failed:\n%s%s" % (what, r.stdout, r.stderr))
 
 
-def _compile_binding(verbose: bool) -> str:
-    import torch
+# the host compiler of the ROCm installation hipcc belongs to
+CXX = os.path.join(os.path.dirname(HIPCC), "amdclang++")
+
+
+def _compile_binding(verbose: bool) -> str | None:
+    try:
+        import torch
+    except ImportError:
+        return None      # the C ABI needs no torch
     inc = os.path.join(os.path.dirname(torch.__file__), "include")
     obj = os.path.join(OBJDIR, "torch_binding.o")
-    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    _run([CXX, "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
           "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
           "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
@@ -69,7 +76,7 @@ def _link_binding(obj: str, verbose: bool) -> None:
     # libxtc.so is found next to it
     import torch
     tmp = BINDING + ".tmp%d" % os.getpid()
-    _run(["g++", "-shared", "-o", tmp, obj, "-L" + HERE, "-l:libxtc.so", "-Wl,-rpath,$ORIGIN",
+    _run([CXX, "-shared", "-o", tmp, obj, "-L" + HERE, "-l:libxtc.so", "-Wl,-rpath,$ORIGIN",
           "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"),
           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], "link of _binding.so", verbose)
     os.replace(tmp, BINDING)
@@ -80,7 +87,6 @@ def build(verbose: bool = False) -> str:
     with ThreadPoolExecutor(min(len(SOURCES) + 1, os.cpu_count() or 1)) as ex:
         binding = ex.submit(_compile_binding, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
-        binding_obj = binding.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
     if verbose:
@@ -89,7 +95,9 @@ def build(verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s%s" % (r.stdout, r.stderr))
     os.replace(tmp, LIB)
-    _link_binding(binding_obj, verbose)
+    binding_obj = binding.result()   # (the library is there, whatever became of the binding)
+    if binding_obj is not None:
+        _link_binding(binding_obj, verbose)
     return LIB
 
 

@@ -21,6 +21,30 @@ def test_everything_but_plain_gpu_tensors_is_left_to_the_python_path():
         x.matmul(a, a.bfloat16())
 
 
+@pytest.mark.parametrize("binding", [None, b"no shared object"])
+def test_the_library_imports_without_its_binding(tmp_path, binding):
+    """A binding that is missing or does not load is reported and leaves the C
+    ABI usable."""
+    import os
+    import shutil
+    import subprocess
+    import sys
+    pkg = os.path.dirname(x.__file__)
+    dst = tmp_path / "paper_2512_16512_amd"
+    dst.mkdir()
+    for f in ("__init__.py", "libxtc.so"):
+        shutil.copy(os.path.join(pkg, f), dst / f)
+    if binding is not None:
+        (dst / "_binding.so").write_bytes(binding)
+    code = ("import paper_2512_16512_amd as x\n"
+            "assert x.__file__.startswith(%r)\n"
+            "print(x._fast, x.xtc_version(), len(x.xtc_sched_list(0, 0)) > 0)" % str(tmp_path))
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    assert r.stdout.split() == ["None", "100", "True"]
+    assert "native binding does not load" in r.stderr and "build.py" in r.stderr
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["float32", "bfloat16"])
 def test_native_and_python_paths_agree(dtype):
