@@ -38,6 +38,8 @@ from __future__ import annotations
 import json
 from dataclasses import dataclass
 
+from .traffic_model import bf16_gather_tile, bf16_patch_tile
+
 BANKS = 64
 
 _B128 = [[0, 1, 2, 3, 12, 13, 14, 15, 20, 21, 22, 23, 24, 25, 26, 27],
@@ -570,9 +572,19 @@ def matmul_launch(dtype: str, s: dict, M: int, N: int, K: int):
     is not modelled.  The instance's kernel is the one its launcher picks for
     such operands: the direct-to-LDS kernel for lds_pad -1, else the
     register-staged kernel, or for k_split > 1 the reduction-split kernel
-    (lds_stages 0) or the direct-to-LDS kernel in k_split wave groups."""
+    (lds_stages 0) or the direct-to-LDS kernel in k_split wave groups.  Rows
+    that do not all start on 16 bytes (K or N in no whole chunks) run other
+    kernels in the bf16 direct-to-LDS instances, and rows off a 4-byte boundary
+    in the register-fed ones: not modelled; the fp32 256x256 tiles run 128x128
+    ones there."""
     BM, BN, BK = s["block_m"], s["block_n"], s["block_k"]
     WM, WN, MI = s["wave_m"], s["wave_n"], s["mfma_m"]
+    if dtype == "bf16" and s["lds_pad"] < 0 and (K % 8 or N % 8):
+        return None
+    if dtype == "bf16" and s.get("k_split", 1) > 1 and (K % 2 or N % 2):
+        return None
+    if dtype == "f32" and s["lds_pad"] < 0 and BM == 256 and BN == 256 and (K % 4 or N % 4):
+        BM, BN, BK, WM, WN = 128, 128, 32, 64, 64
     tiles = _cdiv(M, BM) * _cdiv(N, BN)
     kt = _cdiv(K, BK)
     if s.get("k_split", 1) > 1 and s.get("lds_stages", 0) > 0 and dtype == "f32" and s["lds_pad"] < 0:
@@ -969,10 +981,10 @@ def conv_launch(dtype: str, s: dict, N, C, H, W, OC, R, S, stride, pad):
                                          store_order=True)
         # then the patch kernel (not modelled) for 3x3 layers of whole
         # 8-channel groups, then the gather kernel with a tile by shape
-        if R == 3 and S == 3 and C % 8 == 0:
+        only = (s["block_m"], s["block_n"], s["lds_stages"]) if s.get("lds_pad", -1) == 0 else None
+        if bf16_patch_tile(N, C, H, W, OC, R, S, stride, pad, only):
             return None
-        few = _cdiv(OC, 64) * _cdiv(N * OH * OW, 128) < 1024
-        bm, bn = (64, 64) if few else (128, 128) if OC > 64 else (64, 128)
+        bm, bn = (64, 64) if R * S == 1 and C <= 64 else bf16_gather_tile(OC, N * OH * OW, C * R * S)
         s = dict(s, k_order=0, block_m=bm, block_n=bn, block_k=32, wave_m=bm // 2, wave_n=bn // 2, mfma_m=32,
                  lds_pad=8)
     if dtype == "bf16" and s["k_order"] == 0:

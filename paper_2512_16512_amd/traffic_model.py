@@ -376,16 +376,46 @@ def _block_lines(starts, length: int, line: int = LINE) -> int:
     return int((last - first + 1).sum() - (last[:-1] >= first[1:]).sum())
 
 
+def _bf16_unaligned_tile(bm: int, M: int, N: int, K: int):
+    """Tile of the kernel a bf16 direct-to-LDS instance of ``bm`` rows runs on
+    rows off a 16-byte boundary: the one for rows at any 2-byte boundary (126
+    columns of output per tile, 64-k steps), or for short reductions the
+    register-staged one.  Follows the launcher."""
+    def rounds(m, n):
+        return _cdiv(_cdiv(M, m) * _cdiv(N, n), 256)
+
+    if bm == 64:
+        third = rounds(64, 126) > 2 and rounds(64, 128) <= 2
+        if K > (320 if third else 128):
+            return 64, 126, 64
+        return (64, 64, 64) if rounds(64, 64) <= 3 else (64, 128, 64)
+    n, r = rounds(128, 126), rounds(bm, bm)
+    odd = 10.5 + .0135 * K if n == 1 else 3 + n * (5 + .009 * K)
+    if bm == 256:
+        staged = 1 + r * (11 + .0605 * K)
+    else:
+        staged = 4 + 3 * r + K * (.04 if r <= 2 else .053 if r == 3 else .021 * r)
+    return (bm, bm, 32) if staged < odd else (128, 126, 64)
+
+
 def gemm_tile(dtype: str, s: dict, M: int, N: int, K: int):
     """(block_m, block_n, block_k) of the kernel a matmul instance runs on
-    this shape (contiguous operands, 16-byte aligned bases): the fp32
-    256x256 direct-to-LDS instances fall back to the register-staged
-    128x128x32 kernel when K or N is not a whole number of 16-byte chunks;
-    every other instance keeps its tile."""
+    this shape (contiguous operands, 16-byte aligned bases).  Where K or N is
+    not a whole number of 16-byte chunks, the fp32 256x256 direct-to-LDS
+    instances run 128x128x32 tiles and the bf16 direct-to-LDS instances the
+    kernels for unaligned rows; bf16 register-fed instances run register-staged
+    64x64x64 tiles on short reductions of rows off a 4-byte boundary; every
+    other instance keeps its tile."""
     elt = 4 if dtype == "f32" else 2
     whole = (K * elt) % 16 == 0 and (N * elt) % 16 == 0
-    if dtype == "f32" and s["lds_pad"] == -1 and s["block_m"] == 256 and s["block_n"] == 256 and not whole:
-        return 128, 128, 32
+    if s["lds_pad"] == -1 and not whole:
+        if dtype == "bf16":
+            return _bf16_unaligned_tile(s["block_m"], M, N, K)
+        if s["block_m"] == 256 and s["block_n"] == 256:
+            return 128, 128, 32
+    if dtype == "bf16" and s.get("k_split", 1) > 1 and (K % 2 or N % 2):
+        if K <= (192 if _cdiv(M, 64) * _cdiv(N, 64) > 256 else 64):
+            return 64, 64, 64
     return s["block_m"], s["block_n"], s["block_k"]
 
 
@@ -474,12 +504,31 @@ _BF16_PATCH = {(64, 256, 2): (4, 1, 2), (64, 128, 2): (4, 1, 1), (64, 128, 1): (
                (32, 64, 2): (2, 2, 1), (32, 64, 1): (2, 4, 1)}
 
 
+def bf16_gather_tile(OC: int, pixels: int, K: int):
+    """(block_m, block_n) that the bf16 gather kernel runs where the library
+    chooses them, by the rounds of each tile (the k-offset table of a long
+    reduction leaves fewer workgroups per CU).  Follows the launcher, but for
+    its pointwise layers of up to 64 channels, always 64x64."""
+    small, large = _cdiv(OC, 64) * _cdiv(pixels, 64), _cdiv(OC, 64) * _cdiv(pixels, 128)
+
+    def round_of(bn, most):
+        return 256 * min(most, 160 * 1024 // (4 * (64 * 40 + 32 * (bn + 32)) + 8 * K))
+
+    sr, lr = round_of(64, 5), round_of(128, 4)
+    if OC > 64:
+        return (64, 64) if small <= sr else (128, 128)
+    few = sr < 1280
+    if small <= sr or (_cdiv(small, sr) < 1.7 * _cdiv(large, lr) if few else large > lr and small <= 3200):
+        return 64, 64
+    return 64, 128
+
+
 def bf16_patch_tile(N, C, H, W, OC, R, S, stride, pad, only=None):
     """(block_m, block_n) of the bf16 patch kernel the library runs for this
     layer (16-byte aligned operands), or None outside its class; ``only``: the
     one compiled tile an explicit schedule names.  Follows the launcher."""
-    sh = sw = stride
-    ph = pw = pad
+    sh, sw = (stride, stride) if isinstance(stride, int) else stride
+    ph, pw = (pad, pad) if isinstance(pad, int) else pad
     OH, OW = (H + 2 * ph - R) // sh + 1, (W + 2 * pw - S) // sw + 1
     OHW, pix = OH * OW, N * OH * OW
 
@@ -512,9 +561,12 @@ def bf16_patch_tile(N, C, H, W, OC, R, S, stride, pad, only=None):
 
     if only is not None:
         return only[:2] if fits(only) else None
-    if tiles(32, 64) <= 256 and (fits((32, 64, 1)) or fits((32, 64, 2))):
+    if C <= 8 and (sh > 1 or sw > 1 or OW > 64):
+        return None
+    chunks = _cdiv(C, 16)
+    if tiles(32, 64) <= 256 and ((chunks > 2 and fits((32, 64, 1))) or fits((32, 64, 2))):
         return 32, 64
-    if tiles(64, 128) <= 256 and fits((64, 128, 1)):
+    if tiles(64, 128) <= 256 and chunks > 1 and fits((64, 128, 1)):
         return 64, 128
     if tiles(64, 128) > 256 and tiles(64, 256) <= 256 and fits((64, 256, 2), True):
         return 64, 256
@@ -588,7 +640,7 @@ def conv_grid(dtype: str, s: dict, N, C, H, W, OC, R, S, stride, pad):
         only = None if s["lds_pad"] < 0 else (s["block_m"], s["block_n"], s["lds_stages"])
         bm, bn = bf16_patch_tile(N, C, H, W, OC, R, S, stride, pad, only) or (
             # the gather kernel, its tile by shape
-            (64, 64) if _cdiv(OC, 64) * _cdiv(N * OHW, 128) < 1024 else (128, 128) if OC > 64 else (64, 128))
+            (64, 64) if R * S == 1 and C <= 64 else bf16_gather_tile(OC, N * OHW, C * R * S))
         s = dict(s, block_m=bm, block_n=bn)
     if dtype == "bf16":
         tn, seg = flattened(s["block_n"])

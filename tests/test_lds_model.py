@@ -190,6 +190,25 @@ def test_gather_conv_kernels_match_counters(dims, s, active, conflict):
     assert c.active == active and c.conflict == conflict
 
 
+def test_layers_the_launchers_give_to_another_kernel():
+    # rows off a 16-byte boundary run kernels that are not modelled, or the
+    # fp32 256x256 instance its 128x128 tiles
+    bf = dict(block_m=128, block_n=128, block_k=32, wave_m=64, wave_n=64, mfma_m=32, lds_stages=4, lds_pad=-1, k_split=1)
+    assert L.matmul_launch("bf16", bf, 512, 512, 511) is None
+    assert L.matmul_launch("bf16", bf, 512, 512, 512) is not None
+    fed = dict(bf, block_m=16, block_n=32, wave_m=16, wave_n=32, mfma_m=16, lds_stages=0, lds_pad=0, k_split=4)
+    assert L.matmul_launch("bf16", fed, 64, 63, 512) is None
+    big = dict(block_m=256, block_n=256, block_k=32, wave_m=128, wave_n=64, mfma_m=32, lds_stages=2, lds_pad=-1, k_split=1)
+    small = dict(big, block_m=128, block_n=128, wave_m=64, wave_n=64)
+    assert L.matmul_launch("f32", big, 999, 999, 999) == L.matmul_launch("f32", small, 999, 999, 999)
+    # bf16 3x3 layers outside the patch kernel's class run the gather kernel
+    halo = dict(k_order=2, block_n=256, block_m=64, lds_stages=2, lds_pad=-1)
+    assert L.conv_launch("bf16", halo, 8, 128, 28, 28, 128, 3, 3, 1, 1) is None
+    dims = (64, 8, 28, 28, 16, 3, 3, 2, 1)
+    want = dict(k_order=0, block_m=64, block_n=64, block_k=32, wave_m=32, wave_n=32, mfma_m=32, lds_pad=8, lds_stages=2)
+    assert L.conv_launch("bf16", halo, *dims) == L.conv_launch("bf16", want, *dims)
+
+
 def test_gather_conv_fallbacks_match_counters():
     # C*R*S = 147 and 45 are not multiples of 4: every gather instance runs
     # the register-staged kernel (measured 367010 and 11074 for 64x128 tiles)

@@ -247,6 +247,42 @@ def test_l2_tile_follows_the_fallback():
     assert tm.gemm_tile("f32", s, 256, 258, 512) == (128, 128, 32)    # N = 258: rows not whole chunks
     assert tm.gemm_tile("f32", s, 4096, 4096, 4096) == (256, 256, 32)
     assert tm.gemm_tile("bf16", s, 1000, 1000, 1000) == (256, 256, 32)
+    # bf16 rows off a 16-byte boundary: 126 columns of output per tile, or for
+    # short reductions the register-staged tile
+    assert tm.gemm_tile("bf16", s, 8192, 2056, 1025) == (128, 126, 64)
+    assert tm.gemm_tile("bf16", s, 4096, 4096, 33) == (256, 256, 32)
+    s = _sched(block_m=128, block_n=128, block_k=32, lds_pad=-1)
+    assert tm.gemm_tile("bf16", s, 2047, 3001, 1999) == (128, 126, 64)
+    assert tm.gemm_tile("bf16", s, 2048, 2047, 129) == (128, 128, 32)
+    s = _sched(block_m=64, block_n=128, block_k=64, lds_pad=-1)
+    assert tm.gemm_tile("bf16", s, 1531, 1021, 2047) == (64, 126, 64)
+    assert tm.gemm_tile("bf16", s, 1531, 1021, 65) == (64, 64, 64)
+    assert tm.gemm_tile("bf16", s, 1900, 2040, 65) == (64, 128, 64)
+    assert tm.gemm_tile("bf16", s, 3000, 1280, 257) == (64, 128, 64)   # the odd tiles would need a third round
+    fed = _sched(block_m=16, block_n=32, block_k=32, lds_pad=0, lds_stages=0, k_split=4)
+    assert tm.gemm_tile("bf16", fed, 101, 203, 33) == (64, 64, 64)
+    assert tm.gemm_tile("bf16", fed, 101, 203, 65) == (16, 32, 32)
+    assert tm.gemm_tile("bf16", fed, 102, 204, 32) == (16, 32, 32)
+
+
+def test_bf16_conv_tiles_follow_the_launchers():
+    # gather: within a round of 64x64 tiles, past it, and where a long
+    # reduction's table leaves fewer per CU
+    assert tm.bf16_gather_tile(128, 40 * 784, 512) == (64, 64)      # 980 tiles, five per CU
+    assert tm.bf16_gather_tile(128, 64 * 784, 512) == (128, 128)    # 1568
+    assert tm.bf16_gather_tile(128, 32 * 784, 3200) == (128, 128)   # 784, three per CU
+    assert tm.bf16_gather_tile(64, 18 * 10000, 3136) == (64, 64)    # 2813: four rounds against three of 64x128
+    assert tm.bf16_gather_tile(64, 62720, 3200) == (64, 128)        # 980: two against one
+    assert tm.bf16_gather_tile(64, 100352, 147) == (64, 128)        # 1568 small, 784 large
+    s = _sched(block_n=64, k_order=3, lds_pad=-1)
+    bm, tmm, tn, seg, force = tm.conv_grid("bf16", s, 64, 512, 56, 56, 512, 1, 1, 2, 0)
+    assert (bm, tmm, tn) == (128, 4, 64 * 784 // 128)
+    # patch kernels: the split stops at the chunks of 16 channels; half a chunk
+    # at stride 2 or in long rows gathers
+    assert tm.bf16_patch_tile(256, 8, 8, 8, 8, 3, 3, 1, 1) == (32, 64)
+    assert tm.bf16_patch_tile(8, 8, 56, 56, 16, 3, 3, 1, 1) == (64, 128)
+    assert tm.bf16_patch_tile(64, 8, 28, 28, 16, 3, 3, 2, 1) is None
+    assert tm.bf16_patch_tile(7, 8, 100, 100, 33, 3, 3, 1, 1) is None
 
 
 # TCC_READ_SECTORS_sum x 32 bytes per launch (mean of two), one counter
