@@ -1257,8 +1257,10 @@ conv2d_bf16_rows_kernel(ConvArgs p) {
         soff[s4] = (oc < OC) & (px_rd < OW) ? (unsigned)((((img * OC + oc) * OH + oh_a) * OW + px_rd) * 4)
                                              : (unsigned)kOOB;
     }
-    // relu as a lower bound (-inf: none), by comparison: a maximum would turn
-    // a NaN into the bound
+    // relu as a lower bound (-inf: none), by the maximum that keeps a NaN (fmax
+    // would give the bound); one instruction where a comparison and a select
+    // took the 32x64x56x56 layer from 15.2 to 15.5 us.  Accumulators start at
+    // +0, so a -0 result, which the bound would not keep, cannot occur
     const float lo = p.relu ? 0.f : -__builtin_inff();
     // A step's outputs are stored during the next step, one store per
     // k-step group, and its row loads are spread the same way: with one
@@ -1357,7 +1359,7 @@ conv2d_bf16_rows_kernel(ConvArgs p) {
             for (int i = 0; i < 4; ++i) {
                 f32x4 v;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = acc[o][4 * i + r] < lo ? lo : acc[o][4 * i + r];
+                for (int r = 0; r < 4; ++r) v[r] = __builtin_elementwise_maximum(acc[o][4 * i + r], lo);
                 *reinterpret_cast<f32x4 *>(stg + l32 * 128 + (((2 * i + lg) ^ (l32 & 7)) << 4)) = v;
             }
             const bool rok = RO * st + o < rows;   // uniform
