@@ -227,9 +227,11 @@ xtc_status xtc_matmul(int64_t M, int64_t N, int64_t K,
  *  XTC_ERR_TOO_LARGE.
  *  dtype XTC_F32 or XTC_BF16 (else XTC_ERR_BAD_DTYPE); each reduces in
  *  the order its schedule's k_order selects (bf16: 0, 2 or 3).
- *  sched NULL selects the default conv schedule, but for large fp32 3x3
- *  layers of whole 8-channel groups, which run the patch, halo or tap-major
- *  kernel whose tiles share the CUs best for their shape, and pointwise layers
+ *  sched NULL selects the default conv schedule's kernel, with three
+ *  exceptions by shape: large fp32 3x3 layers of whole 8-channel groups run
+ *  the patch, halo, tap-major or k-table kernel whose tiles share the CUs
+ *  best; fp32 layers of 17 to 32 output channels and a short reduction the
+ *  16-channel, patch or 64x64 tiles likewise; and pointwise layers
  *  (1x1, stride 1, no padding), which the matmul kernels compute per image,
  *  with xtc_default_schedule's matmul rules, where that is the faster route
  *  (not for many images smaller than a tile, nor for bf16 layers of fewer than

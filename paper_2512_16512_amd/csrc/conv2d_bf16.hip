@@ -479,9 +479,11 @@ conv2d_bf16_halo_kernel(ConvArgs p) {
 // every input value once per tap, two bytes at a time, and its reduction is
 // one serial chain of small steps: 32x128x28x28 -> 128 took 92.7 us (80
 // TFLOP/s) and one image of it 90.7 us, both bound by that chain; this kernel
-// takes 19.0 us (390 TFLOP/s; per chunk LDS is busy about 2300 clocks, half
-// of it with fragments, and the matrix cores 1152) and 9.0 us.  Here, as
-// in the halo kernel, a stage of 16 channels stages its input patch once for
+// takes 17.8 us (416 TFLOP/s; 19.0 by a kernel trace) and 9.0 us.  By counters
+// a wave lives 38000 clocks there, of which the matrix cores are busy 24% and
+// LDS 29% (a quarter of that conflicts); over half are waits for copies and at
+// the two barriers of a chunk, with one wave per SIMD to run.  Here, as in
+// the halo kernel, a stage of 16 channels stages its input patch once for
 // all nine taps, without that kernel's restrictions:
 //  - a workgroup computes BM output channels x BN consecutive pixels of the
 //    flattened (image, output row, output column) order.  Padded input rows
@@ -495,7 +497,7 @@ conv2d_bf16_halo_kernel(ConvArgs p) {
 //    nine copy instructions per wave and chunk, no registers, RD chunks ahead
 //    of the matrix cores.  Loads to registers of the cells' own pieces (one
 //    dword per channel and column pair, 16 bytes per weight slab at 144-byte
-//    strides) took 24.2 us where this takes 19.0;
+//    strides) took 24.2 us where this took 19.0;
 //  - between two barriers the waves then turn the raw chunk into cells: 16
 //    bytes hold 8 channels of one padded row and column ([8-channel
 //    half][row][column], WPA columns per row), or 8 channels of one (tap,

@@ -5,7 +5,9 @@
 
 namespace xtc {
 
-// Division of n < 2^31 by a launch constant d: (n * mul) >> (32 + shift) with
+// Division of n < 2^31 by a launch constant d, by multiplication (Granlund and
+// Montgomery, "Division by invariant integers using multiplication", PLDI
+// 1994): (n * mul) >> (32 + shift) with
 // mul = ceil(2^(31 + l) / d), l = ceil(log2 d): the rounding of mul adds less
 // than n / 2^(31 + l) < 1 / d.
 struct FastDiv {

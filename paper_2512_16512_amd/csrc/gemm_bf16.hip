@@ -747,7 +747,7 @@ hipError_t launch_bf16_dma(const GemmArgs &a, hipStream_t s) {
 // registers (two 16-byte loads, four lane shuffles and 15 selects and shifts
 // per chunk), ran 2047x3001x1999 at 275 TFLOP/s (89.4 us); here both operands
 // are copied as they lie, from the dword that holds their first element, and
-// the shift is undone where it costs least (55.0 us; 1531x1021x2047 with 64-row
+// the shift is undone where it costs least (48.2 us; 1531x1021x2047 with 64-row
 // tiles: 78.0 -> 24.0):
 //  - A rows: a lane's row has one parity for the whole reduction; its 16
 //    elements of a 32-k step are read with the dword after them and shifted
@@ -762,9 +762,12 @@ hipError_t launch_bf16_dma(const GemmArgs &a, hipStream_t s) {
 //    apart where their parities differ, meet at the end through LDS.  The
 //    column that the shift costs is the tile's: 126 columns of output per
 //    128 stored.
-// Twice the accumulators of the aligned kernel, the same instructions per
-// FLOP.  Two LDS slots; barriers on both sides of a stage's reads, hidden by
-// the CU's second workgroup.
+// Twice the accumulators of the aligned kernel, the same matrix instructions
+// per FLOP.  Two LDS slots; barriers on both sides of a stage's reads, hidden by
+// the CU's second workgroup where it has one: 2047x3001x1999 has 384 tiles for
+// 256 CUs, and its counters show the matrix cores busy 19% of the launch, LDS
+// 16%, and of a wave's life 26% vector instructions (shifts and permutes), 34%
+// waits to issue and the rest waits for copies and at barriers.
 template <int BM, int WM>
 struct Bf16OddCfg {
     static constexpr int BN = 128, WN = 64, BK = 64, MI = 32, NOUT = BN - 2;
