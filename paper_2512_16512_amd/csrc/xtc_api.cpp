@@ -266,6 +266,30 @@ void default_matmul(xtc_dtype dt, int64_t M, int64_t N, int64_t K, int64_t batch
     }
 }
 
+// fp32 pointwise layers of up to 16 output channels: the tile of the product
+// with each image, or false for the conv kernel.  That kernel adds two partial
+// sums, or more of a short reduction, so the product needs as many not to sum
+// more coarsely: four waves on 16x16 tiles from 128 channels (32x128x28x28 -> 16:
+// error against 64 bits 1.11e-7, 1.48e-7 by the conv kernel and 2.04e-7 by
+// 64x64 tiles; 8.7, 10.0 and 7.6 us; 12x512x28x28: 2.1e-7, 2.9e-7; 7.0, 18.3),
+// but for many tiles of a reduction below 256 (12x128x55x55 -> 8 11.0, 9.6;
+// 32x128x55x55 -> 16 26.3, 25.1; x256 14.0, 25.4 at batch 12); four on 64x32
+// tiles, whose steps are 16 channels, from 64 (32x64x56x56: 8.4e-8, 8.4e-8;
+// 22.8, 25.8), but for many tiles from about 96, whose input patch the conv
+// kernel can stage (4x96x55x55 6.4, 5.7; 32x96x14x14 4.6, 19.6).  Below 64
+// channels no tile's sums are as fine (32x16x56x56: 7.3e-8 with all, 6.0e-8;
+// 9.4, 15.1).
+bool pointwise_f32_few(int64_t N, int64_t HW, int64_t C, int64_t OC, xtc_sched *out) {
+    if (C >= 128) {
+        *out = make_sched(16, 16, 32, 16, 16, 16, 16, 4, 0, 0, 0, 0, 4);
+        out->raster = 1;
+        return C >= 256 || cdiv(HW, 16) * N <= (OC > 8 ? 4096 : 1024);
+    }
+    *out = make_sched(64, 32, 16, 64, 32, 32, 32, 2, 0, 0, 0, 0, 4);
+    out->raster = 1;
+    return C >= 64 && (C < 80 || cdiv(HW, 32) * N <= 256);
+}
+
 // Microseconds of a pointwise layer on either route, from the tiles on the
 // fullest CU (fitted to 2388 layers: 11 pairs of channels from 16 to 2048,
 // images of 1 to 784 pixels, batch 2 to 1024; four of five within 20%).
@@ -588,11 +612,16 @@ xtc_status conv_impl(int64_t N, int64_t C, int64_t H, int64_t W, int64_t OC, int
         !gather) {
         const int64_t HW = H * W;
         xtc_sched p;
-        default_matmul(dtype, OC, HW, C, N, &p);
-        // (below two tiles per CU the products always are; so they are up to
-        // 16 channels in fp32, whose conv tiles gather)
-        if (cdiv(OC, p.block_m) * cdiv(HW, p.block_n) * N < 512 || (dtype == XTC_F32 && OC <= 16) ||
-            pointwise_flat_us(dtype, N * HW, C, OC) >= .95 * pointwise_per_image_us(dtype, N, HW, C, OC, p))
+        bool product;
+        if (dtype == XTC_F32 && OC <= 16)
+            product = pointwise_f32_few(N, HW, C, OC, &p);
+        else {
+            default_matmul(dtype, OC, HW, C, N, &p);
+            // (below two tiles per CU the products always are the faster)
+            product = cdiv(OC, p.block_m) * cdiv(HW, p.block_n) * N < 512;
+        }
+        if (product || (!(dtype == XTC_F32 && OC <= 16) &&
+            pointwise_flat_us(dtype, N * HW, C, OC) >= .95 * pointwise_per_image_us(dtype, N, HW, C, OC, p)))
             return launch_matmul(p, dtype, (int)OC, (int)HW, (int)C, Wt, (int)C, X, (int)HW, Y, (int)HW, relu, (int)N,
                                  C * HW * elt, OC * HW * 4, stream);
     }
