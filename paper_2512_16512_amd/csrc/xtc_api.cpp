@@ -291,8 +291,8 @@ bool pointwise_f32_few(int64_t N, int64_t HW, int64_t C, int64_t OC, xtc_sched *
 }
 
 // Microseconds of a pointwise layer on either route, from the tiles on the
-// fullest CU (fitted to 2388 layers: 11 pairs of channels from 16 to 2048,
-// images of 1 to 784 pixels, batch 2 to 1024; four of five within 20%).
+// fullest CU (fitted to 2808 layers of 16 to 2048 channels, images of 1 to 900
+// pixels, batch 2 to 1448; of those with two tiles per CU 94% are within 20%).
 
 // One product per image with schedule s: a tile costs a fixed part and its
 // products, those of columns past the image's included.
@@ -300,16 +300,25 @@ double pointwise_per_image_us(xtc_dtype dt, int64_t N, int64_t HW, int64_t C, in
     auto per_cu = [&](int64_t bm, int64_t bn) { return (double)cdiv(cdiv(OC, bm) * cdiv(HW, bn) * N, 256); };
     const double c = (double)C, area = (double)s.block_m * s.block_n, n = per_cu(s.block_m, s.block_n);
     const bool fed = s.lds_stages == 0;   // the register-fed kernels
-    if (dt == XTC_F32)
-        return fed ? 3.5 + n * (.4 + c * area * (area <= 512 ? 11e-6 : 7e-6)) : 3 + n * (1 + c * area * 4e-6);
-    const double staged64 = 3.3 + per_cu(64, 64) * (.45 + .0055 * c);   // register-staged 64x64 tiles
-    if (fed) {
-        if (HW % 2 && C <= (cdiv(OC, 64) * cdiv(HW, 64) * N > 256 ? 192 : 64)) return staged64;
-        return 3.3 + n * (.25 + c * (HW % 2 ? .0125 : HW % 8 ? .0085 : .0044) * (.4 + .6 / 64 * s.block_m));
+    if (dt == XTC_F32) {
+        if (fed) return area <= 512 ? 4 + n * c * area * 11.8e-6 : 3.5 + n * (.4 + c * area * 7e-6);
+        if (area <= 64 * 32) return 2.3 + n * (1.19 + c * area * 4e-6);
+        if (area <= 64 * 64) return 3 + n * (.745 + c * area * 3.84e-6);
+        return 4.7 + n * ((area <= 128 * 64 ? 1.26 : 3) + c * area * 3.76e-6);
     }
-    if (HW % 8 == 0) return 3.3 + n * area * (1e-4 + c * 3.3e-7);
-    if (s.block_m < 128) return C <= 128 ? staged64 : 3.3 + per_cu(64, 126) * (1.6 + .0052 * c);
-    return 3.3 + per_cu(128, 126) * (3 + .0098 * c);
+    // register-staged 64x64 tiles, past three per CU 64x128 ones
+    const double n64 = per_cu(64, 64);
+    const double staged64 = n64 <= 3 ? 2.3 + n64 * (.37 + .01 * c) : 5.4 + 2.6 * per_cu(64, 128);
+    if (fed) {
+        if (HW % 2 && C <= (cdiv(OC, 64) * cdiv(HW, 64) * N > 256 ? 192 : 64)) return 2.3 + n64 * (.37 + .01 * c);
+        const double rows = c * (.4 + .6 / 64 * s.block_m);
+        return HW % 2   ? 4.4 + n * (.24 + .01015 * rows)
+               : HW % 8 ? 3 + n * (.71 + .0053 * rows)
+                        : 2.85 + n * (.32 + .0048 * rows);
+    }
+    if (HW % 8 == 0) return 3.8 + n * (.5 + area * (.91e-4 + c * 4.1e-7));
+    if (s.block_m < 128) return C <= 128 ? staged64 : 1.4 + per_cu(64, 126) * (2.6 + .0079 * c);
+    return 4.5 + per_cu(128, 126) * (3.8 + .0092 * c);
 }
 
 // The conv kernels on the pixels of all images in a row: their chain over the
@@ -321,21 +330,23 @@ double pointwise_flat_us(xtc_dtype dt, int64_t pixels, int64_t C, int64_t OC) {
         const int64_t n = cdiv(t, 256);
         return n <= 4 ? us[n - 1] : us[3] + (double)(n - 4) * step;
     };
+    auto rounds = [](int64_t t) { return (double)cdiv(t, 256); };
     if (dt == XTC_F32) {
         if (OC > 64) {
             const int64_t t = tiles(128, 128);
-            return 4.5 + f * (C % 32 ? per_cu(t, {76, 142, 205, 270}, 65) : per_cu(t, {50, 80, 145, 174}, 43)) +
-                   2.5 * fixed * (double)cdiv(t, 256);
+            if (C % 32) return .9 + .885 * f * per_cu(t, {76, 142, 205, 270}, 65) + 8.5 * fixed * rounds(t);
+            return 4.8 + .945 * f * per_cu(t, {50, 80, 145, 174}, 43) + 3.5 * fixed * rounds(t);
         }
-        if (C % 32) return 4 + f * per_cu(tiles(64, 64), {27, 38, 62, 78}, 18) + 2 * (double)cdiv(tiles(64, 64), 256);
-        if (tiles(64, 256) < 256) return 4 + f * per_cu(tiles(64, 64), {18, 28, 38, 48}, 12);
-        return 4 + f * per_cu(tiles(64, 256), {60, 91, 145, 176}, 44) + 3.5 * fixed * (double)cdiv(tiles(64, 256), 256);
+        const int64_t t64 = tiles(64, 64), t256 = tiles(64, 256);
+        if (C % 32) return 2.8 + .82 * f * per_cu(t64, {27, 38, 62, 78}, 18) + 2.05 * fixed * rounds(t64);
+        if (t256 < 256) return 3 + .925 * f * per_cu(t64, {18, 28, 38, 48}, 12) + .83 * fixed * rounds(t64);
+        return 3.3 + .985 * f * per_cu(t256, {60, 91, 145, 176}, 44) + 3.3 * fixed * rounds(t256);
     }
-    const double n = (double)cdiv(tiles(64, 64), 256);
-    if (C <= 64) return 3.5 + .0405 * c + n * (.25 + .0125 * c);
-    if (n <= 5) return 3.5 + c * (.0405 + .005 * (n - 1)) + .3 * n;
-    if (OC > 64) return 4 + (double)cdiv(tiles(128, 128), C > 1700 ? 512 : 768) * (3 + .09 * c);
-    return 3.5 + (double)cdiv(tiles(64, 128), 1024) * (3 + .06 * c);
+    const double n = rounds(tiles(64, 64));
+    if (C <= 64) return 2.6 + .037 * c + n * (.41 + .0095 * c);
+    if (n <= 5) return 2.8 + c * (.04 + .0052 * (n - 1)) + .48 * n;
+    if (OC > 64) return 5.6 + (double)cdiv(tiles(128, 128), C > 1700 ? 512 : 768) * (5.2 + .081 * c);
+    return 8.9 + (double)cdiv(tiles(64, 128), 1024) * .07 * c;
 }
 
 }  // namespace
