@@ -235,7 +235,9 @@ xtc_status xtc_matmul(int64_t M, int64_t N, int64_t K,
  *  (1x1, stride 1, no padding), which the matmul kernels compute per image,
  *  with xtc_default_schedule's matmul rules, where that is the faster route
  *  (not for many images smaller than a tile, nor for bf16 layers of fewer than
- *  32 channels, or of up to 64 whose images do not start on 16 bytes).
+ *  32 channels, or of up to 64 whose images do not start on 16 bytes; fp32
+ *  layers of up to 16 output channels take tiles that add as many partial sums
+ *  as the conv kernel, from 64 channels on).
  * Errors as for xtc_matmul; XTC_ERR_TOO_LARGE also when C*R*S exceeds the
  * kernel's k-offset table capacity (xtc_conv_max_k()).
  */
